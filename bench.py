@@ -48,7 +48,8 @@ METRIC = "tabu moves/sec (population, 1 GPU) + time-to-legal-k-coloring, learned
 MEASURED_TRAFFIC = {"sources_sha256": "90f622ede0f2d30055248402ea1008c515523046e0683b22b3d379670c082e06",
                     "table": "wave8", "block": 64, "bytes": 27144576}  # profiles/tabucol_wave8_gnp500.md
 KERNEL_SOURCES = ("paper_2109_05948_amd/csrc/tabu_body.h", "paper_2109_05948_amd/csrc/tabucol.hip",
-                  "paper_2109_05948_amd/csrc/dlm_common.h", "paper_2109_05948_amd/csrc/tabu_wave.h")
+                  "paper_2109_05948_amd/csrc/dlm_common.h", "paper_2109_05948_amd/csrc/tabu_wave.h",
+                  "paper_2109_05948_amd/csrc/tabu_wave_kernel.h")
 
 
 # HBM bytes of the two distance launches of one diversity step (old x new

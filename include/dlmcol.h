@@ -128,12 +128,12 @@ int dlm_init_population(const dlm_graph* g, int32_t k, int32_t pop, uint64_t see
 #define DLM_TABLE_SPLIT8 5     /* gamma 8 bits in LDS, tabu 16 bits in device memory; an individual
                                   whose colour classes would pass 255 vertices is rerun from its
                                   start with GLOBAL16 (same results) */
-#define DLM_TABLE_WAVE8 6      /* one wavefront (block 64) per individual, all in LDS: a byte per (v,c)
-                                  holding gamma (7 bits) and a flag for "current colour or tabu", and a
-                                  list of the live tabu pairs with their expiries; needs k <= 256 and
-                                  n * kp <= 2^17.  An individual whose colour classes would pass 127
-                                  vertices, or whose live tabu pairs would overflow the list, is rerun
-                                  from its start with GLOBAL16 (same results) */
+#define DLM_TABLE_WAVE8 6      /* one to four wavefronts per individual (the library's choice, block 0 or 64), all
+                                  in LDS: 4 or 8 bits per (v,c) holding gamma, or an escape for the current colour,
+                                  tabu pairs and gammas that do not fit, and a side list of the escaped pairs;
+                                  needs k <= 256 and n * kp <= 2^17.  An individual whose colour classes would pass
+                                  127 vertices, or whose side list would overflow, is rerun from its start with
+                                  GLOBAL16 (same results) */
 
 typedef struct dlm_tabu_params {
   int32_t k;          /* colours, 1 <= k <= 32767 */
@@ -143,9 +143,10 @@ typedef struct dlm_tabu_params {
   int32_t ten_rand;   /* L uniform in [0, ten_rand), 1..1024 */
   int32_t ind_base;   /* global index of row 0 of the population */
   uint64_t seed;      /* Philox key */
-  int32_t block;      /* threads per workgroup: 0 = auto (64 with the WAVE8 table; otherwise 256, or
+  int32_t block;      /* threads per workgroup: 0 = auto (64 to 256 with the WAVE8 table; otherwise 256, or
                          512 when AUTO storage fits only one individual per CU), else 64, 128, 256,
-                         512 or 1024 (WAVE8 takes only 0 or 64) */
+                         512 or 1024 (WAVE8 takes only 0 or 64, and
+                         picks 64 to 256 itself in both cases) */
   int32_t table;      /* DLM_TABLE_* storage of the n x k table */
   int32_t trace_cap;  /* records per individual in trace_dev (0 = none) */
   int32_t reserved;   /* must be 0 */

@@ -5,6 +5,8 @@
 #include <stdint.h>
 
 #include <string>
+#include <utility>
+#include <vector>
 
 #include "../../include/dlmcol.h"
 
@@ -156,6 +158,8 @@ int device_lds_per_cu();  // LDS bytes of one CU on the current device
     if (e_ != hipSuccess) return ::dlm::hip_fail(e_, #call); \
   } while (0)
 
+constexpr int kEllMaxVertices = 20480;  // 160 KB of LDS / 8 bytes: a row of 4 colours, its state and list entry
+
 }  // namespace dlm
 
 struct dlm_graph {
@@ -167,6 +171,16 @@ struct dlm_graph {
   int32_t* row_ptr = nullptr;  // device int32[n+1]
   int32_t* col_idx = nullptr;  // device int32[nnz]
   int32_t* erow = nullptr;     // device int32[nnz]: source vertex of each CSR entry
+  // Two more forms of the adjacency, null above kEllMaxVertices, where no wave
+  // table fits the LDS:
+  // device uint16[n][ell_stride], the neighbours of v, then n + 1 (at least once).
+  // Rows start on 128-byte lines, so a row's address needs no row_ptr and a row
+  // of 250 neighbours is 4 lines instead of 9;
+  // device uint32[n][n / 32 + 1], the adjacency bits of v (bit n is 0).
+  uint16_t* ell = nullptr;
+  uint32_t* adj = nullptr;
+  int32_t ell_stride = 0;
+  std::vector<std::pair<int32_t, int32_t>> degrees;  // (degree, vertices that have it), ascending
   int32_t* weights = nullptr;  // device int32[n] or null
   int32_t* order = nullptr;    // device int32[n]: greedy WVCP vertex order (weighted graphs only)
 };

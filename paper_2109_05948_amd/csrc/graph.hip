@@ -112,6 +112,27 @@ __global__ __launch_bounds__(256) void evaluate_kernel(const int32_t* __restrict
   }
 }
 
+// padded 16-bit neighbour rows and adjacency bits, one workgroup per vertex
+__global__ __launch_bounds__(64) void adjacency_kernel(const int32_t* __restrict__ row_ptr,
+                                                       const int32_t* __restrict__ col_idx, int32_t n, int32_t stride,
+                                                       uint16_t* __restrict__ ell, uint32_t* __restrict__ adj) {
+  const int v = blockIdx.x, rs = row_ptr[v], deg = row_ptr[v + 1] - rs, aw = (n >> 5) + 1;
+  for (int e = threadIdx.x; e < stride; e += 64)
+    ell[(int64_t)v * stride + e] = e < deg ? (uint16_t)col_idx[rs + e] : (uint16_t)(n + 1);
+  for (int w = threadIdx.x; w < aw; w += 64) {
+    // the row is ascending: first entry >= 32 w
+    int lo = 0, hi = deg;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (col_idx[rs + mid] < 32 * w) lo = mid + 1;
+      else hi = mid;
+    }
+    uint32_t bits = 0u;
+    for (; lo < deg && col_idx[rs + lo] < 32 * w + 32; ++lo) bits |= 1u << (col_idx[rs + lo] & 31);
+    adj[(int64_t)v * aw + w] = bits;
+  }
+}
+
 }  // namespace dlm
 
 using namespace dlm;
@@ -201,6 +222,15 @@ int dlm_graph_create(int32_t n, const int32_t* row_ptr, const int32_t* col_idx,
   g->nnz = nnz;
   g->max_deg = max_deg;
   g->max_w = max_w;
+  {
+    std::vector<int32_t> d((size_t)n);
+    for (int32_t v = 0; v < n; ++v) d[(size_t)v] = row_ptr[v + 1] - row_ptr[v];
+    std::sort(d.begin(), d.end());
+    for (int32_t x : d) {
+      if (g->degrees.empty() || g->degrees.back().first != x) g->degrees.emplace_back(x, 0);
+      ++g->degrees.back().second;
+    }
+  }
   (void)hipGetDevice(&g->device);
   hipStream_t s = (hipStream_t)stream;
   auto fail = [&](hipError_t e, const char* what) {
@@ -222,6 +252,15 @@ int dlm_graph_create(int32_t n, const int32_t* row_ptr, const int32_t* col_idx,
     if ((e = upload(&g->weights, weights, n)) != hipSuccess) return fail(e, "graph upload (weights)");
     if ((e = upload(&g->order, order.data(), n)) != hipSuccess) return fail(e, "graph upload (order)");
   }
+  if (n <= kEllMaxVertices) {
+    g->ell_stride = (max_deg + 64) & ~63;
+    if ((e = hipMalloc(&g->ell, sizeof(uint16_t) * (size_t)n * (size_t)g->ell_stride)) != hipSuccess ||
+        (e = hipMalloc(&g->adj, sizeof(uint32_t) * (size_t)n * (size_t)(n / 32 + 1))) != hipSuccess)
+      return fail(e, "graph upload (adjacency)");
+    hipLaunchKernelGGL(adjacency_kernel, dim3((unsigned)n), dim3(64), 0, s, g->row_ptr, g->col_idx, n, g->ell_stride,
+                       g->ell, g->adj);
+    if ((e = hipGetLastError()) != hipSuccess) return fail(e, "graph upload (adjacency)");
+  }
   // the host arrays (the caller's and the local ones) are read synchronously
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail(e, "hipStreamSynchronize");
   *out = g;
@@ -233,6 +272,8 @@ int dlm_graph_destroy(dlm_graph* g) {
   (void)hipFree(g->row_ptr);
   (void)hipFree(g->col_idx);
   (void)hipFree(g->erow);
+  (void)hipFree(g->ell);
+  (void)hipFree(g->adj);
   (void)hipFree(g->weights);
   (void)hipFree(g->order);
   delete g;

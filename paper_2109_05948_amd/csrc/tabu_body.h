@@ -298,6 +298,9 @@ struct TabuArgs {
   unsigned char* gtab;  // device-memory table storage (global and split tiers)
   Key key;
   int32_t n, k, T, ten_num, ten_den, ten_rand, ind_base, trace_cap;
+  const uint16_t* ell = nullptr;  // padded neighbour rows and adjacency bits (dlm_graph), or null
+  const uint32_t* adj = nullptr;
+  int32_t ell_stride = 0;
 };
 
 struct TabuLayout {

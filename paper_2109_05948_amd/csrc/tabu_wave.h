@@ -1,92 +1,106 @@
-// TabuCol with one wavefront per individual (the WAVE8 table tier).
+// TabuCol with one to four wavefronts per individual and a 4- or 8-bit table
+// entry per (vertex, colour) (the WAVE8 table tier).
 //
 // Per individual, all in LDS:
-//   tab[v*kp + c]  one byte: gamma[v][c] in bits 0..6, a flag in bit 7.  The
-//                  flag is set exactly when c is v's current colour, c is a
-//                  padding colour (c >= k), or the pair (v, c) is tabu.  A
-//                  byte without the flag is therefore a move that no tenure
-//                  forbids, and the smallest such byte of a row is the row's
-//                  best non-tabu move.
-//   act[]          the tabu pairs: ((v*kp + c) << 15) | (expiry mod 2^15).
-//                  Only about 0.6 f + 5 of them are live at a time, so they
-//                  are walked one by one after every move: an entry whose
-//                  expiry arrives clears its flag, the others are checked
-//                  for aspiration (f + delta < f_best).
-//   cg[v]          colour (bits 0..7) | gamma[v][col v] (bits 8..14) |
-//                  "listed" (bit 15)
-//   list           the listed vertices: every conflicting vertex once, plus
-//                  vertices that stopped conflicting ("stale", rebuilt away
-//                  when they cost a scan round)
-//   rowkey[i]      best biased delta of list entry i (scans of several rounds)
-//   stage          tied moves waiting for their Philox hash
-//   csize          colour class sizes (gamma <= class size <= 127 keeps bit 7
-//                  free; a run that would pass it gives up with iters = -2
-//                  and is rerun with the 16-bit device table)
+//   tab[v][c]   BITS bits: gamma[v][c], or all ones ("escaped") when c is v's
+//               current colour, c is a padding colour (c >= k), the pair
+//               (v, c) is tabu, or gamma does not fit.  An entry that is not
+//               escaped is a move that no tenure forbids, and the smallest
+//               entry of a row is the row's best such move.
+//   side list   the escaped pairs other than the current and the padding
+//               colours, each with its gamma, its expiry and whether it is
+//               still tabu.  About 0.6 f + 5 tabu pairs are live at a time, and
+//               4-bit tables are taken where few entries reach 15, so the list
+//               is walked whole in every iteration: gamma follows the move by
+//               v*'s adjacency bits, expired pairs lose their tabu state, and a
+//               pair that is neither tabu nor too large returns to the table.
+//               128 entries live in registers of the last wave, one or two per
+//               lane; the rest in act[] = (v*kp + c) << 15 | expiry mod 2^15 and
+//               actg[] = gamma | 0x80 on a pair that is not tabu
+//   cg[v]       colour (bits 0..7) | gamma[v][col v] (bits 8..14) |
+//               "listed" (bit 15)
+//   list[w]     per wave, the listed vertices it scans: every conflicting
+//               vertex is in one wave's list once, beside vertices that
+//               stopped conflicting ("stale", compacted away when they cost a
+//               scan round)
+//   stage[w]    rows at the wave's best delta
+//   slot[w]     the wave's best move
+//   The colour class sizes live in registers of every wave (gamma <= class
+//   size <= 127 fits seven bits; a run that would pass it gives up with iters =
+//   -2 and is rerun with the 16-bit device table).
 //
-// One iteration, with no workgroup barrier (the wave owns the individual):
-//   scan   lane i takes list entry i (64 per round) and reads its row: the
-//          smallest non-flagged byte in three VALU per four colours (two
-//          packed 16-bit minima over the byte pairs);
-//   min    DPP minimum of the rows' and the aspiring tabu pairs' biased
-//          deltas;
-//   ties   the rows at the minimum are read again, 64 / W rows at a time
-//          (W lanes per row), and their bytes equal to the target value
-//          staged; tabu pairs at the minimum come from the list;
-//   hash   one Philox evaluation per lane over the staged moves, DPP
-//          minimum of (hash, v, c);
-//   apply  the CSR row of v* from device memory, one neighbour per lane:
-//          two byte adds in its row, its cg word, list membership; v*'s flag,
-//          class sizes, the new tabu pair;
-//   list   expiries of the next iteration and its aspiration candidates.
+// One iteration, two barriers (none for a single wave):
+//   scan   lane i takes list entry i of its wave (64 per round) and reads its
+//          row: the smallest entry in packed 16-bit minima whose top bits are
+//          the entries; the last wave adds the side list's admissible pairs;
+//   ties   the rows at the wave's minimum (DPP) are staged and read again, one
+//          dword per lane; each lane hashes its tied moves (Philox);
+//   fold   the waves publish (delta, hash, v, c); after the barrier each folds
+//          the slots to the smallest;
+//   apply  the neighbours of v* (16-bit padded rows in device memory) are split
+//          over the waves; a neighbour's row and cg word belong to one lane;
+//          the last wave also writes v*'s state and walks the side list.
+//
+// What bounds it: one wave's chain of dependent steps.  Measured here, in
+// cycles: a vector operation 4, an LDS read 57, a neighbour row from the L2
+// about 200, a vector result brought to the scalar unit 31, a branch on it
+// 52, a lane-masked block 44.  So Philox (about 190) is cheaper than avoiding
+// it, and the code selects addresses and values instead of branching.
 #pragma once
+
+#include <type_traits>
 
 #include "tabu_body.h"
 
 namespace dlm {
 
-constexpr uint32_t kW8Flag = 0x80u;
 constexpr uint32_t kW8ClassMax = 127u;
 constexpr uint32_t kW8None = 255u;        // biased delta (delta + 128) of "no admissible move"
-constexpr int kW8Stage = 320;             // staged ties: < 64 left over + at most 256 from one pass
 constexpr uint32_t kW8ExpMask = 0x7fffu;  // expiries are kept modulo 2^15
 constexpr uint32_t kW8NoKey = 0xffffffffu;
+constexpr uint32_t kW8Free = 0x80u;  // actg: not tabu
+constexpr int kW8Stage = 128;        // tied rows a wave stages: up to 64 waiting and 64 more
+constexpr int kW8Mail = 64;          // entries that can escape by growth in one move
 
 struct W8Layout {
-  uint32_t tab, cg, list, rowkey, stage, csize, sink, act, bytes;
+  uint32_t tab, cg, list, stage, slot, mail, act, actg, bytes;
 };
 
-// LDS of one individual with room for acap tabu pairs.  A row read covers
-// up to KQ dwords; reads past the last row land in the arrays that follow
-// the table (the stage alone is larger than any such overrun).
-__host__ __device__ inline W8Layout w8_layout(int n, int k, int acap) {
-  const uint32_t kp = (uint32_t)tab_stride(k);
+__host__ __device__ constexpr int w8_row_dwords(int k, int bits) { return (k * bits + 31) >> 5; }
+
+// LDS of one individual searched by nw waves, with room for acap side-list
+// entries (a multiple of 64).  A row read covers up to RW dwords; reads past
+// the last row land in the arrays that follow the table.  list and stage,
+// adjacent, are the scratch of the construction.  Two rows follow the
+// vertices', all escaped: n, read by scan lanes without a vertex, and n + 1,
+// where the ends of neighbour rows point.
+__host__ __device__ inline W8Layout w8_layout(int n, int k, int bits, int nw, int acap) {
   W8Layout L;
   uint32_t o = 0;
   L.tab = o;
-  o += align16((uint32_t)(n + 1) * kp);
+  o += align16(4u * (uint32_t)(n + 2) * (uint32_t)w8_row_dwords(k, bits));
   L.cg = o;
-  o += align16(2u * (uint32_t)(n + 1));
+  o += align16(2u * (uint32_t)(n + 2));
   L.list = o;
-  o += align16(2u * (uint32_t)n);
-  L.rowkey = o;
-  o += align16((uint32_t)n);
-  L.stage = o;
-  o += 4u * kW8Stage;
-  L.csize = o;
-  o += align16(2u * kp);
-  L.sink = o;  // lanes with nothing to store or add aim here (no branch around them)
-  o += 16;
-  L.act = o;
-  o += 4u * (uint32_t)acap;
+  o += (uint32_t)nw * align16(2u * (uint32_t)(n + 1));
+  L.stage = o;  // one entry more than kW8Stage: where lanes without a tied row write
+  o += (uint32_t)nw * 4u * (kW8Stage + 4);
+  L.slot = o;  // 16 bytes per wave, then "give up" and the mail count
+  o += 16u * ((uint32_t)nw + 1u);
+  L.mail = o;
+  o += bits == 8 ? 0u : 4u * kW8Mail;
+  L.act = o;  // one entry more than acap: where lanes without an entry write
+  o += 4u * (uint32_t)acap + 4u;
+  L.actg = o;
+  o += (uint32_t)acap + 12u;
   L.bytes = o;
   return L;
 }
 
-// dwords per row bucket of the scan (rows of 9 to 15 and 17 to 23 dwords
-// are launched at their exact width)
-__host__ __device__ constexpr int w8_bucket(int k) {
-  const int kq = tab_stride(k) >> 2;
-  return kq <= 8 ? 8 : kq <= 16 ? 16 : kq <= 24 ? 24 : kq <= 32 ? 32 : kq <= 64 ? 64 : 0;
+// dwords a kernel reads per row: exact up to 12, then buckets (0: k > 256)
+__host__ __device__ constexpr int w8_bucket(int k, int bits) {
+  const int w = w8_row_dwords(k, bits);
+  return k > 256 ? 0 : w <= 12 ? w : w <= 16 ? 16 : w <= 24 ? 24 : w <= 32 ? 32 : 64;
 }
 
 typedef unsigned short w8_u16x2 __attribute__((ext_vector_type(2)));
@@ -138,13 +152,25 @@ __device__ __forceinline__ W8RoundKeys w8_round_keys(Key key) {
   return rk;
 }
 
+// one v_bitop3_b32
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
+}
+
+// Ends the block after a lane-masked one.  Without it the two paths of a
+// lane-masked block at the end of a uniform one meet where the uniform paths
+// do, and the compiler then takes every value that differs between the uniform
+// paths for lane-dependent: vector registers, masked loops and branches
+// (14,000 instead of 8,000 cycles an iteration at G(500, 0.5)).
+__device__ __forceinline__ void lanes_joined() { asm volatile(""); }
+
 // Philox4x32-10 word 0 (the same function as philox_w0) from precomputed round keys
 __device__ __forceinline__ uint32_t philox_w0_rk(uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3,
                                                  const W8RoundKeys& rk) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     const uint64_t p0 = (uint64_t)0xD2511F53u * x0, p1 = (uint64_t)0xCD9E8D57u * x2;
-    const uint32_t y0 = (uint32_t)(p1 >> 32) ^ x1 ^ rk.k[2 * r], y2 = (uint32_t)(p0 >> 32) ^ x3 ^ rk.k[2 * r + 1];
+    const uint32_t y0 = xor3((uint32_t)(p1 >> 32), x1, rk.k[2 * r]), y2 = xor3((uint32_t)(p0 >> 32), x3, rk.k[2 * r + 1]);
     x1 = (uint32_t)p1;
     x3 = (uint32_t)p0;
     x0 = y0;
@@ -157,35 +183,45 @@ __device__ __forceinline__ uint32_t rfl(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
 }
 
-// The conflicting vertices in vertex order; sets "listed" on exactly those.
-// Returns the list length.
-__device__ __forceinline__ int w8_build_list(uint16_t* cg, uint16_t* list, int n, int lane) {
+// The kernel's arguments, read again where they are needed late and rarely:
+// output pointers would otherwise hold (and spill) scalar registers all along.
+// The kernel's first argument is the TabuArgs block.
+__device__ __forceinline__ const TabuArgs* late_args() {
+  uint64_t p = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return (const TabuArgs*)p;
+}
+
+// Barrier of the waves that share an individual.
+template <int NW>
+__device__ __forceinline__ void team_sync() {
+  if constexpr (NW == 1)
+    wave_sync();
+  else
+    __syncthreads();
+}
+
+// The conflicting vertices of every NW-th group of 64, in vertex order, as
+// this wave's list; sets "listed" on exactly those.  Returns the list length.
+template <int NW>
+__device__ __forceinline__ int w8_build_list(uint16_t* cg, uint16_t* list, int n, int wid, int lane) {
   int base = 0;
-  for (int v0 = 0; v0 < n; v0 += 4 * kWave) {
-    uint32_t x[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int v = v0 + r * kWave + lane;
-      x[r] = v < n ? cg[v] : 0u;
+  for (int v0 = wid * kWave; v0 < n; v0 += NW * kWave) {
+    const int v = v0 + lane;
+    const uint32_t x = v < n ? (uint32_t)cg[v] : 0u;
+    const bool cf = ((x >> 8) & 0x7fu) != 0u;
+    const uint64_t m = __ballot(cf);
+    if (cf) {
+      cg[v] = (uint16_t)(x | 0x8000u);
+      list[base + (int)lane_rank(m)] = (uint16_t)v;
     }
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int v = v0 + r * kWave + lane;
-      const bool cf = ((x[r] >> 8) & 0x7fu) != 0u;
-      const uint64_t m = __ballot(cf);
-      if (v < n) {
-        const uint32_t y = (x[r] & 0x7fffu) | (cf ? 0x8000u : 0u);
-        if (y != x[r]) cg[v] = (uint16_t)y;
-      }
-      if (cf) list[base + (int)lane_rank(m)] = (uint16_t)v;
-      base += __popcll(m);
-    }
+    base += __popcll(m);
   }
   return base;
 }
 
-// Drops the stale entries (vertices no longer conflicting) from the list in
-// place and clears their "listed" bit.  Returns the new length.
+// Drops the stale entries (vertices no longer conflicting) from a wave's list
+// in place and clears their "listed" bit.  Returns the new length.
 __device__ __forceinline__ int w8_compact_list(uint16_t* cg, uint16_t* list, int len, int lane) {
   int base = 0;
   for (int i0 = 0; i0 < len; i0 += kWave) {
@@ -194,411 +230,702 @@ __device__ __forceinline__ int w8_compact_list(uint16_t* cg, uint16_t* list, int
     const uint32_t x = i < len ? (uint32_t)cg[v] : 0u;
     const bool keep = ((x >> 8) & 0x7fu) != 0u;
     if (i < len && !keep) cg[v] = (uint16_t)(x & 0x7fffu);
+    lanes_joined();
     const uint64_t m = __ballot(keep);
     if (keep) list[base + (int)lane_rank(m)] = (uint16_t)v;  // base <= i0: entries are read before they are overwritten
+    lanes_joined();
     base += __popcll(m);
   }
   return base;
 }
 
-// One individual (row li of a.colors) searched by the calling wavefront.
-// KQ: dwords read per row, kp / 4 <= KQ (the exact width for rows of 9 to 15
-// and 17 to 23 dwords, else the bucket of w8_bucket); acap: tabu pairs the
-// LDS holds.
-template <int KQ>
+// One individual (row li of a.colors) searched by the NW waves of the calling
+// workgroup.  RW: dwords read per row (exact up to 12, else the bucket of
+// w8_bucket); acap: side-list entries the LDS holds.
+template <int BITS, int NW, int RW>
 __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, int acap, unsigned char* smem) {
-  // a bucket (8, 16, 24, 32, 64 dwords) masks what it reads past the row; any
-  // other KQ is the exact row width (kq == KQ): nothing to mask
-  constexpr bool bucket = KQ == 8 || KQ == 16 || KQ == 24 || KQ == 32 || KQ == 64;
-  constexpr int KQ_LO = !bucket ? KQ : KQ == 8 ? 0 : KQ == 16 ? 8 : KQ == 24 ? 16 : KQ == 32 ? 24 : 32;
-  const int lane = threadIdx.x;
+  constexpr int BLOCK = NW * kWave;
+  constexpr uint32_t PER = 32u / BITS, ESC = (1u << BITS) - 1u;  // entries per dword, the escaped entry
+  constexpr uint32_t ONES = BITS == 4 ? 0x11111111u : 0x01010101u;
+  constexpr uint32_t LOW = ONES * (ESC >> 1), TOP = ~LOW;  // the lower bits and the top bit of every entry
+  // dwords q < RLO of a row always lie in it
+  constexpr int RLO = RW <= 12 ? RW : RW == 16 ? 12 : RW == 24 ? 16 : RW == 32 ? 24 : 32;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wid = NW == 1 ? 0 : (int)rfl((uint32_t)tid / kWave);
+  const bool tail_wave = wid == NW - 1;  // keeps v*'s state and the side list
   // every field the search needs, as a value of its own: the argument block
   // as a whole (about 30 scalar registers) would otherwise stay live in, and
   // spill from, scalar registers
   const uint32_t ind = own_u32((uint32_t)(a.ind_base + li));
   const int n = (int)own_u32((uint32_t)a.n), k = (int)own_u32((uint32_t)a.k);
-  const uint32_t kp = (uint32_t)tab_stride(k), kq = kp >> 2;
-  const gptr<const int32_t> col_idx = own_sgpr(a.col_idx);
-  const gptr<int32_t> trace = own_sgpr(a.trace);
-  const gptr<int32_t> iters_out = own_sgpr(a.iters + li);
-  const gptr<int32_t> f_best_out = own_sgpr(a.f_best + li);
-  const gptr<int64_t> stats_out = own_sgpr(a.stats ? a.stats + (size_t)li * DLM_NSTATS : nullptr);
-  const gptr<uint64_t> hash_out = own_sgpr(a.hash ? a.hash + li : nullptr);
-  const int trace_cap = (int)own_u32((uint32_t)a.trace_cap), T = (int)own_u32((uint32_t)a.T);
+  const uint32_t rw = (uint32_t)w8_row_dwords(k, BITS), kp = rw * PER;
+  const gptr<const uint16_t> ell = own_sgpr(a.ell);
+  const gptr<const uint32_t> adj = own_sgpr(a.adj);
+  const uint32_t stride = own_u32((uint32_t)a.ell_stride), aw = ((uint32_t)n >> 5) + 1u;
+  const int trace_cap = (int)own_u32((uint32_t)(a.trace ? a.trace_cap : 0)), T = (int)own_u32((uint32_t)a.T);
   const Key key{own_u32(a.key.k0), own_u32(a.key.k1)};
   const uint32_t ten_num = own_u32((uint32_t)a.ten_num), ten_den = own_u32((uint32_t)a.ten_den);
   const uint32_t ten_rand = own_u32((uint32_t)a.ten_rand);
   const uint32_t den_inv = 0xffffffffu / ten_den;
   // ceil(2^32 / kp): v = umulhi(v*kp + c, kp_inv) is exact for v*kp + c < 2^17
   const uint32_t kp_inv = (uint32_t)((0x100000000ull + kp - 1u) / kp);
-  const W8Layout L = w8_layout(n, k, acap);
-  uint8_t* tab = smem + L.tab;
+  const W8Layout L = w8_layout(n, k, BITS, NW, acap);
   uint32_t* tabw = reinterpret_cast<uint32_t*>(smem + L.tab);
   uint16_t* cg = reinterpret_cast<uint16_t*>(smem + L.cg);
-  uint16_t* list = reinterpret_cast<uint16_t*>(smem + L.list);
-  uint8_t* rowkey = smem + L.rowkey;
-  uint32_t* stage = reinterpret_cast<uint32_t*>(smem + L.stage);
-  uint32_t* csw = reinterpret_cast<uint32_t*>(smem + L.csize);  // class sizes, two 16-bit counts per word
+  uint16_t* list = reinterpret_cast<uint16_t*>(smem + L.list + (uint32_t)wid * align16(2u * (uint32_t)(n + 1)));
+  uint32_t* stage = reinterpret_cast<uint32_t*>(smem + L.stage + (uint32_t)wid * 4u * (kW8Stage + 4));
+  uint4* slot = reinterpret_cast<uint4*>(smem + L.slot);
+  // "give up" is written between the fold's barrier and the iteration's last
+  // one, and read by every wave before the next fold
+  uint32_t* full = reinterpret_cast<uint32_t*>(smem + L.slot + 16u * NW);
+  uint32_t* mailn = full + 1;
+  uint32_t* mail = reinterpret_cast<uint32_t*>(smem + L.mail);
   uint32_t* act = reinterpret_cast<uint32_t*>(smem + L.act);
-  uint32_t* sink = reinterpret_cast<uint32_t*>(smem + L.sink);
+  uint8_t* actg = smem + L.actg;
   const gptr<int16_t> gcol = own_sgpr(a.colors + (size_t)li * n);
-  const gptr<const int32_t> erow = own_sgpr(a.erow);
   const __attribute__((address_space(4))) int32_t* row_c =
       (const __attribute__((address_space(4))) int32_t*)(const int32_t*)own_sgpr(a.row_ptr);
-  // tie pass: LPR lanes per row (two dwords each), rpp rows per pass; this
-  // lane's row within a pass and its dword pair
-  const int lpr = (int)((kq + 1u) >> 1), rpp = kWave / lpr;
-  const int lrow = lane / lpr, lj = lane - lrow * lpr;
-  auto csize = [&](uint32_t c) { return (csw[c >> 1] >> (16u * (c & 1u))) & 0xffffu; };
-  auto give_up = [&]() {
-    if (lane == 0) *iters_out = -2;
-  };
+  // tie pass: one dword per lane, rpp rows per pass; this lane's row within a pass and its dword
+  const int rpp = kWave / (int)rw;
+  const int lrow = lane / (int)rw, lj = lane - lrow * (int)rw;
+  auto shift = [&](uint32_t c) { return BITS * (c & (PER - 1u)); };  // of entry c within its dword c / PER
+  // Written by every lane: a lane-masked store here would meet the search
+  // loop's end in one block, and the compiler would then keep the loop's
+  // uniform values (f, t, the lists' lengths) in vector registers.
+  auto give_up = [&]() { late_args()->iters[li] = -2; };
 
-  // 1. start colouring (rejected whole if a colour is outside [0, k)), padded table, class sizes
+  // 1. start colouring (rejected whole if a colour is outside [0, k)), class sizes
   int bad = 0;
-  for (int v = lane; v < n; v += kWave) {
+  for (int v = tid; v < n; v += BLOCK) {
     const int c = gcol[v];
     bad |= (c < 0) | (c >= k);
     cg[v] = (uint16_t)(c & 0xff);
   }
-  if (__ballot(bad)) {
-    if (lane == 0) {
-      *f_best_out = -1;
-      *iters_out = -1;
+  uint32_t* scr = reinterpret_cast<uint32_t*>(smem + L.list);
+  for (int i = tid; i < k; i += BLOCK) reinterpret_cast<uint16_t*>(scr)[i] = 0;
+  for (int i = tid; i < 2 * (int)rw; i += BLOCK) tabw[(uint32_t)n * rw + (uint32_t)i] = 0xffffffffu;
+  if (tid == 0) {
+    cg[n] = 0;
+    cg[n + 1] = 0x80ffu;  // "listed": never appended
+    *full = 0u;
+    *mailn = 0u;
+  }
+  team_sync<NW>();
+  if (__ballot(bad) && lane == 0) *full = 1u;
+  team_sync<NW>();
+  if (rfl(*full)) {
+    if (tid == 0) {
+      a.f_best[li] = -1;
+      a.iters[li] = -1;
     }
     return;
   }
-  for (int i = lane; i < (int)(kp >> 1); i += kWave) csw[i] = 0u;
-  {
-    const int words = (n + 1) * (int)kq;
-    for (int i = lane; i < words; i += kWave) {
-      const int v = i / (int)kq, q = i - v * (int)kq;
-      uint32_t w = 0u;
-#pragma unroll
-      for (int b = 0; b < 4; ++b)
-        if (v == n || 4 * q + b >= k) w |= 0xffu << (8 * b);
-      tabw[i] = w;
-    }
-  }
-  if (lane == 0) cg[n] = 0;
-  wave_sync();
-  for (int v = lane; v < n; v += kWave) {
+  for (int v = tid; v < n; v += BLOCK) {
     const uint32_t c = cg[v];
-    atomicAdd(&csw[c >> 1], 1u << (16u * (c & 1u)));
+    atomicAdd(&scr[c >> 1], 1u << (16u * (c & 1u)));
   }
-  wave_sync();
+  team_sync<NW>();
+  constexpr int NR = ((int)PER * RW + kWave - 1) / kWave;
+  uint32_t cz[NR];  // size of class lane + 64 r
   {
-    int big = 0;
-    for (int c = lane; c < k; c += kWave) big |= csize((uint32_t)c) > kW8ClassMax;
-    if (__ballot(big)) {
+    uint32_t big = 0u;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int c = lane + kWave * r;
+      cz[r] = c < k ? (uint32_t)reinterpret_cast<uint16_t*>(scr)[c] : 0u;
+      big = max(big, cz[r]);
+    }
+    if (__ballot(big > kW8ClassMax)) {  // every wave looks at every class: uniform
       give_up();
       return;
     }
   }
-  // 2. gamma from the CSR entries
-  const int nnz = row_c[n];
-  for (int e = lane; e < nnz; e += kWave) {
-    const uint32_t u = (uint32_t)col_idx[e], v = (uint32_t)erow[e];
-    const uint32_t c = cg[u];
-    atomicAdd(&tabw[v * kq + (c >> 2)], 1u << (8u * (c & 3u)));
-  }
-  wave_sync();
-  // 3. the current colour's gamma into cg, its flag set; f = sum / 2
+  team_sync<NW>();
+  // 2. the table, a chunk of vertices at a time: gamma in bytes from the CSR
+  // entries into the scratch, then packed; entries that do not fit join the side list
   uint32_t fs = 0;
-  for (int v = lane; v < n; v += kWave) {
-    const uint32_t c = cg[v];
-    const uint32_t g = tab[(uint32_t)v * kp + c];
-    atomicOr(&tabw[(uint32_t)v * kq + (c >> 2)], kW8Flag << (8u * (c & 3u)));
-    cg[v] = (uint16_t)(c | (g << 8));
-    fs += g;
+  {
+    const uint32_t sw = (kp + 3u) >> 2;  // scratch dwords per vertex
+    const int rows = (int)((L.slot - L.list) / (4u * sw));
+    for (int v0 = 0; v0 < n; v0 += rows) {
+      const int v1 = min(n, v0 + rows);
+      for (int i = tid; i < (v1 - v0) * (int)sw; i += BLOCK) scr[i] = 0u;
+      team_sync<NW>();
+      const int e1 = row_c[v1];
+      for (int e = row_c[v0] + tid; e < e1; e += BLOCK) {
+        const uint32_t c = (uint32_t)cg[a.col_idx[e]] & 0xffu;
+        atomicAdd(&scr[(uint32_t)(a.erow[e] - v0) * sw + (c >> 2)], 1u << (8u * (c & 3u)));
+      }
+      team_sync<NW>();
+      for (int i = tid; i < (v1 - v0) * (int)rw; i += BLOCK) {
+        const int r = i / (int)rw, q = i - r * (int)rw;
+        const uint32_t v = (uint32_t)(v0 + r), cv = (uint32_t)cg[v] & 0xffu;
+        uint32_t w = 0u;
+#pragma unroll
+        for (uint32_t b = 0; b < PER; ++b) {
+          const uint32_t c = PER * (uint32_t)q + b;
+          uint32_t g = (scr[(uint32_t)r * sw + (c >> 2)] >> (8u * (c & 3u))) & 0xffu;
+          if (c == cv) {
+            cg[v] = (uint16_t)(cv | (g << 8));
+            fs += g;
+            g = ESC;
+          } else if (c >= (uint32_t)k) {
+            g = ESC;
+          } else if (g >= ESC) {
+            const uint32_t p = atomicAdd(mailn, 1u);
+            if (p < (uint32_t)acap) {
+              act[p] = (v * kp + c) << 15;
+              actg[p] = (uint8_t)(g | kW8Free);
+            }
+            g = ESC;
+          }
+          w |= g << (BITS * b);
+        }
+        tabw[v * rw + (uint32_t)q] = w;
+      }
+      team_sync<NW>();
+    }
   }
-  int f = (int)(wave_sum_u32(fs) >> 1);
-  wave_sync();
-  int len = w8_build_list(cg, list, n, lane);
-  int C = len;  // conflicting vertices, as the last scan counted them
+  int A = (int)rfl(*mailn);  // side-list entries in act (the tail wave's count)
+  if (A > acap) {
+    give_up();
+    return;
+  }
+  // 3. f = half the sum of the own gammas
+  fs = wave_sum_u32(fs);
+  if constexpr (NW > 1) {
+    if (lane == 0) slot[wid].x = fs;
+  }
+  team_sync<NW>();
+  if constexpr (NW > 1) {
+    fs = 0u;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) fs += rfl(slot[w].x);
+  }
+  int f = (int)(fs >> 1);
+  if (tid == 0) *mailn = 0u;
+  int len = w8_build_list<NW>(cg, list, n, wid, lane);
+  // a longer list is compacted: stale entries cost a scan round; so is any
+  // list of several rounds every 64 iterations, since conflicts get fewer
+  int len_max = max(64, (len + 63) & ~63);
+  team_sync<NW>();
 
-  int t = 0, f_best = f, A = 0;
+  int t = 0, f_best = f;
   bool best_cur = true;
-  uint32_t asp = kW8None;  // this lane's best biased delta among aspiring tabu pairs
-  // statistics and fingerprint accumulate in lane 0 (vector registers, by
-  // select rather than branch: the scalar file is the scarce one); moves = t - no-ops
+  // statistics (st_conf per lane) and fingerprint; moves = t - no-ops
   uint64_t st_conf = 0, st_deg = 0, fp = kFnvOffset;
   uint32_t st_noops = 0, st_ties = 0, st_cap = 0;
   const bool l0 = lane == 0;
   uint32_t Lreg = 0;
-  uint16_t* sink16 = reinterpret_cast<uint16_t*>(sink);
+  bool spill = false;  // the tail wave could not take an entry
+  bool mailed = false;  // entries wait in mail (one wave: known without a look)
   const W8RoundKeys rk = w8_round_keys(key);
+  // the tail wave's register part of the side list: vertex, colour, expiry mod
+  // 2^15, gamma | kW8Free; a free lane holds vertex n and a colour that matches nothing
+  constexpr int NB = 2;
+  constexpr uint32_t kNoColour = 0xfffeu;
+  uint32_t sv[NB], sc[NB], sx[NB], sg[NB];
+  uint64_t room[NB];  // free lanes
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    sv[b] = (uint32_t)n;
+    sc[b] = kNoColour;
+    sx[b] = 0u;
+    sg[b] = 0u;
+    room[b] = ~0ull;
+  }
+  auto refill = [&]() {  // from the end of act
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+      const int rank = (int)lane_rank(room[b]);
+      const bool get = ((room[b] >> lane) & 1ull) != 0ull && rank < A;
+      const int i = get ? A - 1 - rank : acap;
+      const uint32_t e = act[i], g = actg[i];
+      const uint32_t v = __umulhi(e >> 15, kp_inv);
+      sv[b] = get ? v : sv[b];
+      sc[b] = get ? (e >> 15) - v * kp : sc[b];
+      sx[b] = get ? e & kW8ExpMask : sx[b];
+      sg[b] = get ? g : sg[b];
+      const uint64_t got = __ballot(get);
+      A -= __popcll(got);
+      room[b] &= ~got;
+    }
+  };
 
   while (t < T && f > 0) {
-    if (((len + 63) >> 6) > ((C + 64) >> 6)) {  // stale entries cost a scan round: compact
+    if ((t & 63) == 0) {
+      if (rfl(*full)) {  // an entry was lost: left to the 16-bit rerun
+        give_up();
+        return;
+      }
+      if (tail_wave) {
+        Lreg = lemire(philox_w0_rk(ind, (uint32_t)(t + lane), 0u, kDomTenure, rk), ten_rand);
+        if (A > 0) refill();
+      }
+    }
+    uint32_t mails = 0u;
+    if (BITS == 4 && NW > 1 && tail_wave) mails = *mailn;
+    if (len > ((t & 63) != 0 ? len_max : 64)) {
       wave_sync();
       len = w8_compact_list(cg, list, len, lane);
+      len_max = max(64, (len + 63) & ~63);
       wave_sync();
     }
-    if ((t & 63) == 0) Lreg = lemire(philox_w0_rk(ind, (uint32_t)(t + lane), 0u, kDomTenure, rk), ten_rand);
 
-    // ---- scan: list entry (r << 6) + lane in round r
+    // ---- scan: list entry (r << 6) + lane in round r.  Biased deltas
+    // (delta + 128) of the first eight rounds stay in dp0 (rounds 0..3) and dp1
     const int rounds = (len + 63) >> 6;
-    uint32_t best = kW8None, dlast = kW8None, vlast = (uint32_t)n, glast = 0u;
-    C = 0;
+    uint32_t best = kW8None, dp0 = 0u, dp1 = 0u, vlast = (uint32_t)n, xlast = 0u, dlast = kW8None;
+    uint32_t conf = 0u;
     for (int r = 0; r < rounds; ++r) {
       const int i = (r << 6) + lane;
-      const uint32_t v = i < len ? (uint32_t)list[i] : (uint32_t)n;
-      const uint32_t g = ((uint32_t)cg[v] >> 8) & 0x7fu;
-      C += __popcll(__ballot(g != 0u));
-      const uint32_t* row = tabw + __umul24(v, kq);
-      uint32_t w[KQ];
+      const uint32_t v0 = list[min(i, len - 1)];
+      const uint32_t v = i < len ? v0 : (uint32_t)n;
+      const uint32_t x = cg[v], g = (x >> 8) & 0x7fu;
+      const uint32_t* row = tabw + __umul24(v, rw);
+      uint32_t w[RW];
 #pragma unroll
-      for (int q = 0; q < KQ; ++q) w[q] = row[q];
-      // bytes 0, 2 of each dword as the high bytes of the 16-bit halves of
-      // w << 8, bytes 1, 3 as those of w itself: the packed minima's high
-      // bytes are the smallest bytes
-      uint32_t ml = 0xffffffffu, mh = 0xffffffffu;
+      for (int q = 0; q < RW; ++q) w[q] = row[q];
+      conf += g != 0u ? 1u : 0u;
+      // the entries at the top of each 16-bit half of w, w << BITS, ...: the
+      // packed minima's top bits are the smallest entries
+      uint32_t mn[16 / BITS];
 #pragma unroll
-      for (int q = 0; q < KQ; ++q) {
-        const uint32_t x = (q >= KQ_LO && q >= (int)kq) ? 0xffffffffu : w[q];
-        ml = pk_min_u16(ml, x << 8);
-        mh = pk_min_u16(mh, x);
+      for (int j = 0; j < 16 / BITS; ++j) mn[j] = 0xffffffffu;
+#pragma unroll
+      for (int q = 0; q < RW; ++q) {
+        if (q >= RLO && q >= (int)rw) w[q] = 0xffffffffu;
+#pragma unroll
+        for (int j = 0; j < 16 / BITS; ++j) mn[j] = pk_min_u16(mn[j], w[q] << (BITS * j));
       }
-      const uint32_t m = min(min(ml & 0xffffu, ml >> 16), min(mh & 0xffffu, mh >> 16)) >> 8;
-      const uint32_t d = (g != 0u && m < kW8Flag) ? m + 128u - g : kW8None;
-      if (rounds > 1) *(i < len ? rowkey + i : reinterpret_cast<uint8_t*>(sink)) = (uint8_t)d;
+#pragma unroll
+      for (int j = 1; j < 16 / BITS; ++j) mn[0] = pk_min_u16(mn[0], mn[j]);
+      const uint32_t m = min(mn[0] & 0xffffu, mn[0] >> 16) >> (16 - BITS);
+      const uint32_t d = (g != 0u && m != ESC) ? m + 128u - g : kW8None;
+      if (r < rounds - 1) {
+        const uint32_t sh = 8u * (uint32_t)(r & 3);
+        dp0 |= r < 4 ? d << sh : 0u;
+        dp1 |= r >= 4 && r < 8 ? d << sh : 0u;
+      }
       best = min(best, d);
-      dlast = d;
       vlast = v;
-      glast = g;
+      xlast = x;
+      dlast = d;
     }
-    const uint32_t dstar = wave_min_u32(min(best, asp));
-    uint32_t key_star = kW8NoKey;  // the tabu pair a move onto a tabu colour consumes
-
-    if (dstar == kW8None) {  // nothing admissible: no-op iteration
-      st_noops += l0 ? 1u : 0u;
-      st_conf += l0 ? (uint64_t)C : 0ull;
-      fp = l0 ? fnv_step(fp, 0xffffu, 0xffffu, f) : fp;
-      if (trace && t < trace_cap && lane == 0) {
-        gptr<int32_t> tr = trace + ((size_t)li * trace_cap + t) * 2;
-        tr[0] = -1;
-        tr[1] = f;
-      }
-    } else {
-      // ---- every admissible move at dstar, hashed where it is found
-      // The rows at dstar are gathered into slots ((v << 8) | the byte value
-      // their best move has) and read again LPR lanes per row, two dwords
-      // per lane; tabu pairs at dstar come from the list.  Each lane hashes
-      // its own tied moves (Philox of (ind, t, v, c)) and keeps the smallest
-      // (hash, v, c).
-      uint64_t hk = ~0ull;
-      uint32_t seen = 0;  // tied moves met so far, counted up to 2
-      // mask: bit 8 b + 7 set for a tie at colour c0 + b
-      auto hash_in = [&](uint64_t mask, uint32_t v, uint32_t c0) {
-        const uint64_t any = __ballot(mask != 0ull);
-        seen += (uint32_t)__popcll(any) + (__ballot(__popcll(mask) > 1) != 0ull ? 1u : 0u);
-        if (any == 0ull) return;
-        while (__ballot(mask != 0ull)) {
-          if (mask) {
-            const uint32_t c = c0 + ((uint32_t)__builtin_ctzll(mask) >> 3);
-            mask &= mask - 1ull;
-            hk = umin64(hk, ((uint64_t)philox_w0_rk(ind, (uint32_t)t, v, c, rk) << 32) | (v << 16) | c);
-          }
+    st_conf += conf;
+    // the side list's admissible pairs: not tabu, or aspiring (f + delta < f_best)
+    const int aspd = f_best - f - 1;
+    auto pair_delta = [&](uint32_t x, uint32_t ga) -> uint32_t {  // 255 or more: not admissible
+      const int g = (int)((x >> 8) & 0x7fu), dd = (int)(ga & 0x7fu) - g;
+      return g != 0 && (ga >= kW8Free || dd <= aspd) ? (uint32_t)(dd + 128) : kW8None;
+    };
+    auto act_delta = [&](int i0, uint32_t& v, uint32_t& c, uint32_t& x) -> uint32_t {
+      const int i = i0 + lane < A ? i0 + lane : acap;
+      const uint32_t kk = act[i] >> 15, ga = actg[i];
+      v = i < acap ? __umulhi(kk, kp_inv) : (uint32_t)n;
+      c = kk - v * kp;
+      x = cg[v];
+      return pair_delta(x, ga);
+    };
+    uint32_t side[NB], sxg[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) side[b] = kW8None, sxg[b] = 0u;
+    if (tail_wave) {
+      if (BITS == 4 && (NW > 1 ? rfl(mails) != 0u : mailed)) {  // entries that the last move made escape
+        const int got = (int)rfl(*mailn), cnt = min(got, min(kW8Mail, acap - A));
+        spill |= cnt < got;
+        if (lane < cnt) {
+          act[A + lane] = mail[lane] << 15;
+          actg[A + lane] = (uint8_t)(ESC | kW8Free);
         }
+        lanes_joined();
+        A += cnt;
+        if (l0) *mailn = 0u;
+        lanes_joined();
+        mailed = false;
+        wave_sync();
+      }
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        if (b == 0 || room[b] != ~0ull) {
+          sxg[b] = cg[sv[b]];
+          side[b] = pair_delta(sxg[b], sg[b]);
+          best = min(best, side[b]);
+        }
+      for (int i0 = 0; i0 < A; i0 += kWave) {
+        uint32_t v, c, x;
+        best = min(best, act_delta(i0, v, c, x));
+      }
+    }
+    const uint32_t cur = wave_min_u32(best);
+
+    // ---- the wave's best move: every admissible move at cur, hashed where it is found
+    uint32_t vc = 0u, h = 0u, xs = 0u;
+    int seen = 0;
+    if (cur != kW8None) {
+      uint64_t hk = ~0ull;  // hash << 32 | v << 8 | c of this lane's smallest
+      uint32_t hx = 0u;     // the cg word of its vertex
+      auto hash_move = [&](bool has, uint32_t v, uint32_t c, uint32_t x) {
+        const uint64_t y = ((uint64_t)philox_w0_rk(ind, (uint32_t)t, v, c, rk) << 32) | (v << 8) | c;
+        const bool lt = has && y < hk;
+        hx = lt ? x : hx;
+        hk = lt ? y : hk;
       };
-      auto scan_slots = [&](int cnt) {
+      auto scan_rows = [&](int cnt) {
         for (int p0 = 0; p0 < cnt; p0 += rpp) {
           const int ri = p0 + lrow;
           const bool ok = lrow < rpp && ri < cnt;
-          const uint32_t e0 = stage[ri];  // past cnt: harmless, replaced below
-          const uint32_t e = ok ? e0 : ((uint32_t)n << 8);  // row n: all padding, matches nothing
-          const uint32_t v = e >> 8, tv = (e & 0xffu) * 0x01010101u;
-          const uint32_t* rw = tabw + v * kq + 2u * (uint32_t)lj;
-          const uint32_t x0 = rw[0];
-          const uint32_t x1 = 2 * lj + 1 < (int)kq ? rw[1] : 0xffffffffu;
-          // bit 7 of byte b set iff byte b equals the target (a target is
-          // below 128, so flagged and padding bytes never match)
-          const uint32_t y0 = x0 ^ tv, y1 = x1 ^ tv;
-          const uint32_t z0 = ~(((y0 & 0x7f7f7f7fu) + 0x7f7f7f7fu) | y0) & 0x80808080u;
-          const uint32_t z1 = ~(((y1 & 0x7f7f7f7fu) + 0x7f7f7f7fu) | y1) & 0x80808080u;
-          hash_in((uint64_t)z0 | ((uint64_t)z1 << 32), v, 8u * (uint32_t)lj);
+          const uint32_t e = stage[ok ? ri : 0];
+          const uint32_t v = e >> 8;
+          const uint32_t y = tabw[__umul24(v, rw) + (uint32_t)lj] ^ (e & 0xffu) * ONES;
+          const uint32_t x = cg[v];
+          // top bit of an entry set iff it equals the target (below ESC, so escaped entries never match)
+          uint32_t z = ok ? ~(((y & LOW) + LOW) | y) & TOP : 0u;
+          for (uint64_t b = __ballot(z != 0u); b; b = __ballot(z != 0u)) {
+            const uint32_t c = PER * (uint32_t)lj + (((uint32_t)__ffs((int)z) - 1u) / BITS);
+            hash_move(z != 0u, v, c, x);
+            seen += __popcll(b);
+            z &= z - 1u;
+          }
         }
       };
-      {
-        int nrows = 0;
-        for (int r = 0; r < rounds; ++r) {
-          const bool lastr = r == rounds - 1;
-          const int i = (r << 6) + lane;
-          uint32_t vr = vlast, gr = glast, dr = dlast;
-          if (!lastr) {
-            dr = i < len ? (uint32_t)rowkey[i] : kW8None;
-            vr = i < len ? (uint32_t)list[i] : (uint32_t)n;
-            gr = ((uint32_t)cg[vr] >> 8) & 0x7fu;
-          }
-          const bool tied = dr == dstar;
-          const uint64_t M = __ballot(tied);
-          *(tied ? stage + nrows + (int)lane_rank(M) : sink) = (vr << 8) | (dstar + gr - 128u);
-          nrows += __popcll(M);
-          if (nrows > kW8Stage - kWave || lastr) {
-            wave_sync();
-            scan_slots(nrows);
-            nrows = 0;
-            wave_sync();
-          }
+      int cnt = 0;
+      for (int r = 0; r < rounds; ++r) {
+        uint32_t v = vlast, x = xlast, d = dlast;
+        if (r != rounds - 1) {
+          v = list[(r << 6) + lane];  // full rounds
+          x = cg[v];
+          const uint32_t dp = (r < 4 ? dp0 : dp1) >> (8 * (r & 3));
+          // beyond the rounds kept: any row may be at cur, the comparison below tells
+          d = r < 8 ? dp & 0xffu : (((x >> 8) & 0x7fu) != 0u ? cur : kW8None);
+        }
+        const uint32_t tgt = cur + ((x >> 8) & 0x7fu) - 128u;
+        const bool tied = d == cur && tgt < ESC;
+        const uint64_t M = __ballot(tied);
+        stage[tied ? cnt + (int)lane_rank(M) : kW8Stage] = (v << 8) | tgt;
+        cnt += __popcll(M);
+        if (cnt > kW8Stage - kWave || r == rounds - 1) {
+          wave_sync();
+          scan_rows(cnt);
+          cnt = 0;
+          wave_sync();
         }
       }
-      if (__ballot(asp == dstar)) {
-        // tabu pairs at dstar: all of them aspire (the test depends on delta only)
+      if (tail_wave) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          if (const uint64_t m = __ballot(side[b] == cur)) {
+            hash_move(side[b] == cur, sv[b], sc[b], sxg[b]);
+            seen += __popcll(m);
+          }
         for (int i0 = 0; i0 < A; i0 += kWave) {
-          const int i = i0 + lane;
-          const uint32_t kk = i < A ? act[i] >> 15 : 0u;
-          const uint32_t v = __umulhi(kk, kp_inv), c = kk - v * kp;
-          const uint32_t g = ((uint32_t)cg[v] >> 8) & 0x7fu;
-          const bool hit = i < A && g != 0u && (uint32_t)(tab[kk] & 0x7fu) + 128u - g == dstar;
-          hash_in(hit ? 0x80ull : 0ull, v, c);
+          uint32_t v, c, x;
+          const uint32_t d = act_delta(i0, v, c, x);
+          if (const uint64_t m = __ballot(d == cur)) {
+            hash_move(d == cur, v, c, x);
+            seen += __popcll(m);
+          }
         }
       }
-      const uint32_t win = (uint32_t)wave_min_u64(hk);
+      h = wave_min_u32((uint32_t)(hk >> 32));
+      uint64_t at = __ballot((uint32_t)(hk >> 32) == h);
+      if (at & (at - 1ull)) {  // equal hashes: the smallest (v, c)
+        const uint32_t lo = wave_min_u32((uint32_t)(hk >> 32) == h ? (uint32_t)hk : 0xffffffffu);
+        at = __ballot(hk == (((uint64_t)h << 32) | lo));
+      }
+      const int wl = __builtin_ctzll(at);
+      vc = readlane((uint32_t)hk, wl);
+      xs = readlane(hx, wl);
+    }
+    uint32_t dstar = cur;
+    bool shared = seen > 1;  // two or more admissible moves at the best delta
+    if constexpr (NW > 1) {
+      // delta 8 bits, hash 32, v << 8 | c 23 bits, the "more than one" bit
+      const uint32_t khi = cur != kW8None ? (cur << 24) | (h >> 8) : 0xffffffffu;
+      const uint32_t klo = cur != kW8None ? (h << 24) | (vc << 1) | (seen > 1 ? 1u : 0u) : 0xffffffffu;
+      if (l0) slot[wid] = make_uint4(klo, khi, xs, 0u);
+      lanes_joined();
+      __syncthreads();
+      const uint4 e = slot[lane & (NW - 1)];
+      const uint64_t kx = ((uint64_t)e.y << 32) | e.x;
+      uint64_t km = umin64(kx, ((uint64_t)dpp_mov<dpp::kXor1>(e.y) << 32) | dpp_mov<dpp::kXor1>(e.x));
+      if constexpr (NW > 2)
+        km = umin64(km, ((uint64_t)dpp_mov<dpp::kXor2>((uint32_t)(km >> 32)) << 32) | dpp_mov<dpp::kXor2>((uint32_t)km));
+      xs = readlane(e.z, __builtin_ctzll(__ballot(kx == km)));
+      dstar = rfl((uint32_t)(km >> 56));
+      const uint32_t lo = rfl((uint32_t)km);
+      vc = (lo >> 1) & 0x7fffffu;
+      const uint64_t level = __ballot((e.y >> 24) == dstar) & ((1ull << NW) - 1ull);  // waves at the best delta
+      shared = (lo & 1u) != 0u || (level & (level - 1ull)) != 0ull;
+    }
 
-      // ---- apply (v*, c*)
-      const uint32_t vs = win >> 16, cs = win & 0xffffu;
-      const uint32_t xv = rfl((uint32_t)cg[vs]);
-      const uint32_t bnew = rfl((uint32_t)tab[vs * kp + cs]);
-      const uint32_t csz = rfl(csize(cs));
-      const uint32_t old = xv & 0xffu;
-      const int fnew = f + (int)dstar - 128;
-      if (csz >= kW8ClassMax) {  // left to the 16-bit rerun
-        give_up();
-        return;
+    uint32_t vs = (uint32_t)n, cs = 0xffffu, old = 0xffffu;  // no move: they match nothing
+    int fnew = f, deg = 0;
+    bool snap = false;
+    if (dstar != kW8None) {
+      vs = vc >> 8;
+      cs = vc & 0xffu;
+      old = xs & 0xffu;
+      fnew = f + (int)dstar - 128;
+    }
+    // ---- apply.  Neighbour u of v*: gamma[u][old] - 1, gamma[u][c*] + 1; if
+    // u has colour old or c*, its own gamma and list membership follow.
+    // Groups of 16 consecutive neighbours go to the waves in turn, so that
+    // short rows and every wave's list stay balanced.  A row ends in entries
+    // n + 1, where nothing changes.
+    const uint32_t nrow = 2u * vs * stride, arow = 4u * vs * aw;  // bytes
+    auto adj_word = [&](uint32_t v) { return *(gptr<const uint32_t>)((gptr<const char>)adj + (arow + 4u * (v >> 5))); };
+    const uint32_t e0 = (uint32_t)(((lane & ~15) * NW) + (wid << 4) + (lane & 15));
+    const uint32_t wo = (old & 0xffu) / PER, wn = (cs & 0xffu) / PER, so = shift(old), sn = shift(cs);
+    uint32_t sa[NB];  // adjacency of the side list's vertices to v*
+    auto neighbours = [&](auto rounds_c, uint32_t eb, bool with_side) {
+      constexpr int R = decltype(rounds_c)::value;
+      uint32_t nb[R], ra[R], rb[R], xn[R], grew = 0u;
+      uint64_t mi[R];
+      bool ins[R];
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const uint32_t at = nrow + 2u * min(eb + e0 + r * BLOCK, stride - 1u);
+        nb[r] = (uint32_t)*(gptr<const uint16_t>)((gptr<const char>)ell + at);
       }
-      const bool snap = best_cur && fnew >= f_best;  // leaving the best state: keep a copy
-      if (snap)
-        for (int v = lane; v < n; v += kWave) gcol[v] = (int16_t)(cg[v] & 0xffu);
-      const int rs = row_c[vs], re = row_c[vs + 1];
-      const uint32_t dec = 0u - (1u << (8u * (old & 3u))), inc = 1u << (8u * (cs & 3u));
-      const uint32_t wo = old >> 2, wn = cs >> 2;
-      // neighbour u: gamma[u][old] - 1, gamma[u][c*] + 1; if u has colour old
-      // or c*, its own gamma and list membership follow.  Up to 256
-      // neighbours at a time: every CSR load issued before any is used, then
-      // every table add and cg read, then the cg updates; lanes past the row
-      // aim at the sink.
-      constexpr int kPre = 4;
-      for (int e0 = rs; e0 < re; e0 += kPre * kWave) {
-        uint32_t nb[kPre], xs[kPre];
+      if (with_side && tail_wave) {
 #pragma unroll
-        for (int r = 0; r < kPre; ++r)  // past the row: a copy of its last entry (valid, redirected below)
-          nb[r] = (uint32_t)col_idx[min(e0 + lane + r * kWave, re - 1)];
-#pragma unroll
-        for (int r = 0; r < kPre; ++r) {
-          const bool live = e0 + lane + r * kWave < re;
-          uint32_t* ru = tabw + __umul24(nb[r], kq);
-          atomicAdd(live ? ru + wo : sink, dec);
-          atomicAdd(live ? ru + wn : sink, inc);
-          xs[r] = cg[nb[r]];
-        }
-#pragma unroll
-        for (int r = 0; r < kPre; ++r) {
-          if (e0 + r * kWave >= re) break;  // uniform: ballots see the whole wave
-          const bool live = e0 + lane + r * kWave < re;
-          const uint32_t x = xs[r], cu = x & 0xffu;
-          const bool lo = cu == old, hi = cu == cs;
-          // a neighbour that starts to conflict and is not listed yet is appended
-          const bool ins = live && hi && (x & 0xff00u) == 0u;
-          const uint32_t nx = x + (hi ? 0x100u : 0u) - (lo ? 0x100u : 0u) + (ins ? 0x8000u : 0u);
-          *(live ? &cg[nb[r]] : sink16) = (uint16_t)nx;
-          const uint64_t mi = __ballot(ins);
-          *(ins ? &list[len + (int)lane_rank(mi)] : sink16) = (uint16_t)nb[r];
-          len += __popcll(mi);
-        }
+        for (int b = 0; b < NB; ++b) sa[b] = adj_word(sv[b]);
       }
-      // v*: its new colour flagged, its state, class sizes, the new tabu pair
-      const uint32_t gnew = bnew & 0x7fu;
-      if (bnew & kW8Flag) key_star = vs * kp + cs;  // a move onto a tabu colour: that pair is consumed
-      // tenure term floor(num * f / den), capped (as in the block kernel)
-      const uint64_t prod = (uint64_t)ten_num * (uint32_t)fnew;
-      uint32_t ttf;
-      if (prod <= 0xffffffffull) {
-        const uint32_t x = (uint32_t)prod;
-        ttf = __umulhi(x, den_inv);
-        uint32_t rem = x - ttf * ten_den;
-        if (rem >= ten_den) {
-          rem -= ten_den;
-          ++ttf;
-        }
-        if (rem >= ten_den) ++ttf;
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const uint32_t* ru = tabw + __umul24(nb[r], rw);
+        ra[r] = ru[wo];
+        rb[r] = ru[wn];
+        xn[r] = cg[nb[r]];
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        uint32_t* ru = tabw + __umul24(nb[r], rw);
+        const uint32_t ea = (ra[r] >> so) & ESC, ec = (rb[r] >> sn) & ESC;
+        atomicAdd(ru + wo, ea != ESC ? 0u - (1u << so) : 0u);
+        atomicAdd(ru + wn, ec != ESC ? 1u << sn : 0u);
+        const uint32_t x = xn[r], cu = x & 0xffu;
+        // 256 colours leave none that the rows' ends could hold
+        const bool hi = cu == cs && (PER * RW < 256u || nb[r] < (uint32_t)n);
+        // a neighbour that starts to conflict and is not listed yet is appended
+        ins[r] = hi && (x & 0xff00u) == 0u;
+        cg[nb[r]] = (uint16_t)(x + (hi ? 0x100u : 0u) - (cu == old && (PER * RW < 256u || nb[r] < (uint32_t)n) ? 0x100u : 0u) + (ins[r] ? 0x8000u : 0u));
+        grew |= ec == ESC - 1u ? 1u << r : 0u;
+        mi[r] = __ballot(ins[r]);
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        list[ins[r] ? len + (int)lane_rank(mi[r]) : n] = (uint16_t)nb[r];
+        len += __popcll(mi[r]);
+      }
+      if (BITS == 4 && __ballot(grew != 0u)) {  // gamma[u][c*] no longer fits
+        mailed = true;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          if ((grew >> r) & 1u) {
+            const uint32_t p = atomicAdd(mailn, 1u);
+            if (p < (uint32_t)kW8Mail)
+              mail[p] = nb[r] * kp + cs;
+            else
+              *full = 1u;
+          }
+        lanes_joined();
+      }
+    };
+    if (dstar != kW8None) {
+      deg = row_c[vs + 1] - row_c[vs];
+      constexpr int R = NW == 1 ? 4 : 2;  // rounds whose loads are issued before any is used
+      if (stride <= (uint32_t)BLOCK) {
+        neighbours(std::integral_constant<int, 1>{}, 0u, true);
+      } else if (NW == 1 && stride <= 2u * BLOCK) {
+        neighbours(std::integral_constant<int, 2>{}, 0u, true);
       } else {
-        ttf = (uint32_t)std::min<uint64_t>(prod / ten_den, kTenureCap + 1);
+        neighbours(std::integral_constant<int, R>{}, 0u, true);
+        for (uint32_t eb = R * BLOCK; eb < (uint32_t)deg; eb += BLOCK)
+          neighbours(std::integral_constant<int, 1>{}, eb, false);
       }
-      const bool capped = ttf > (uint32_t)kTenureCap;
-      if (capped) ttf = kTenureCap;
-      const uint32_t expiry = (uint32_t)t + readlane(Lreg, t & 63) + ttf;
-      const bool tabu_next = expiry > (uint32_t)t + 1u;  // tabu from iteration t + 1 on
-      if (tabu_next && A >= acap) {
+      snap = best_cur && fnew >= f_best;  // leaving the best state: keep a copy
+      if (snap)
+        for (int v = tid; v < n; v += BLOCK)
+          gcol[v] = (int16_t)((uint32_t)v == vs ? old : (uint32_t)cg[v] & 0xffu);
+      lanes_joined();
+      // class sizes; a class that would pass its limit leaves the individual to the 16-bit rerun
+      uint32_t csz = 0u;
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const uint32_t c = (uint32_t)(lane + kWave * r);
+        if (NR == 1 || (int)(cs >> 6) == r) csz = readlane(cz[r], cs & 63);
+        cz[r] += (c == cs ? 1u : 0u) - (c == old ? 1u : 0u);
+      }
+      if (csz >= kW8ClassMax) {  // the same in every wave
         give_up();
         return;
       }
-      if (lane == 0) {
-        atomicOr(&tabw[vs * kq + wn], kW8Flag << (8u * (cs & 3u)));
-        cg[vs] = (uint16_t)(cs | (gnew << 8) | 0x8000u);
-        atomicAdd(&csw[old >> 1], 0u - (1u << (16u * (old & 1u))));
-        atomicAdd(&csw[cs >> 1], 1u << (16u * (cs & 1u)));
-        if (tabu_next)
-          act[A] = ((vs * kp + old) << 15) | (expiry & kW8ExpMask);
-        else  // a tenure of 0 or 1 never forbids anything
-          atomicAnd(&tabw[vs * kq + wo], ~(kW8Flag << (8u * (old & 3u))));
-      }
-      if (tabu_next) ++A;
-      if (trace && t < trace_cap && lane == 0) {
-        gptr<int32_t> tr = trace + ((size_t)li * trace_cap + t) * 2;
-        tr[0] = (int32_t)(vs | (cs << 16));
-        tr[1] = fnew;
-      }
-      st_conf += l0 ? (uint64_t)C : 0ull;
-      st_deg += l0 ? (uint64_t)(re - rs) : 0ull;
-      st_ties += l0 && seen > 1u ? 1u : 0u;
-      st_cap += l0 && capped ? 1u : 0u;
-      fp = l0 ? fnv_step(fp, vs, cs, fnew) : fp;
-      f = fnew;
-      if (f < f_best) {
-        f_best = f;
-        best_cur = true;
-      } else if (snap) {
-        best_cur = false;
-      }
+    } else {
+#pragma unroll
+      for (int b = 0; b < NB; ++b) sa[b] = 0u;
     }
     ++t;
-
-    // ---- tabu pairs for iteration t: expiries, the consumed pair, aspiration
-    wave_sync();
-    {
-      const int aspd = f_best - f - 1;  // admissible by aspiration iff delta <= aspd
-      asp = kW8None;
-      int base = 0;
-      for (int i0 = 0; i0 < A; i0 += kWave) {
-        const int i = i0 + lane;
-        const bool alive = i < A;
-        const uint32_t e = act[alive ? i : 0];
-        const uint32_t kk = e >> 15;
-        const bool expired = alive && (e & kW8ExpMask) == ((uint32_t)t & kW8ExpMask);
-        const bool drop = alive && kk == key_star;
-        atomicAnd(expired && !drop ? &tabw[kk >> 2] : sink, ~(kW8Flag << (8u * (kk & 3u))));
-        const bool keep = alive && !expired && !drop;
-        const uint32_t v = __umulhi(kk, kp_inv);
-        const int g = (int)(((uint32_t)cg[v] >> 8) & 0x7fu);
-        const int d = (int)(tab[kk] & 0x7fu) - g;
-        if (keep && g != 0 && d <= aspd) asp = min(asp, (uint32_t)(d + 128));
-        const uint64_t mk = __ballot(keep);
-        *(keep ? &act[base + (int)lane_rank(mk)] : sink) = e;
-        base += __popcll(mk);
+    if (tail_wave) {
+      // ---- side list for iteration t: gammas, expiries, the pair v* moved
+      // onto, entries that return to the table.  One that this move touches
+      // waits: a neighbour's lane may be looking at its table entry.
+      const uint32_t texp = (uint32_t)t & kW8ExpMask;
+      auto walk = [&](uint32_t v, uint32_t c, uint32_t ex, uint32_t& ga, bool nbr, bool& gone) {
+        const bool up = nbr && c == cs, down = nbr && c == old;
+        const uint32_t g = (ga & 0x7fu) + (up ? 1u : 0u) - (down ? 1u : 0u);
+        const bool open = ga >= kW8Free || ex == texp;
+        gone = v == vs && c == cs;
+        const bool back = !gone && open && g < ESC && !up && !down && v != (uint32_t)n;
+        if (back) atomicAdd(&tabw[__umul24(v, rw) + c / PER], 0u - ((ESC - g) << shift(c)));
+        lanes_joined();
+        ga = g | (open ? kW8Free : 0u);
+        gone |= back;
+      };
+#pragma unroll
+      for (int b = 0; b < NB; ++b)
+        if (b == 0 || room[b] != ~0ull) {
+          bool gone;
+          walk(sv[b], sc[b], sx[b], sg[b], ((sa[b] >> (sv[b] & 31u)) & 1u) != 0u, gone);
+          sv[b] = gone ? (uint32_t)n : sv[b];
+          sc[b] = gone ? kNoColour : sc[b];
+          room[b] |= __ballot(gone);
+        }
+      if (A > 0) {
+        int base = 0;
+        for (int i0 = 0; i0 < A; i0 += kWave) {
+          const bool alive = i0 + lane < A;
+          const int i = alive ? i0 + lane : acap;
+          const uint32_t e = act[i], v = alive ? __umulhi(e >> 15, kp_inv) : (uint32_t)n;
+          const uint32_t c = alive ? (e >> 15) - v * kp : kNoColour;
+          uint32_t ga = actg[i];
+          const uint32_t ad = dstar != kW8None ? adj_word(v) >> (v & 31u) : 0u;
+          bool gone;
+          walk(v, c, e & kW8ExpMask, ga, (ad & 1u) != 0u, gone);
+          const bool keep = alive && !gone;
+          const uint64_t mk = __ballot(keep);
+          const int p = keep ? base + (int)lane_rank(mk) : acap;
+          act[p] = e;
+          actg[p] = (uint8_t)ga;
+          base += __popcll(mk);
+        }
+        A = base;
       }
-      A = base;
+      if (dstar != kW8None) {
+        // v*: its new colour escaped, its state, the pair it left
+        const uint32_t gown = (xs >> 8) & 0x7fu, gnew = gown + dstar - 128u;
+        // tenure term floor(num * f / den), capped (as in the block kernel)
+        const uint64_t prod = (uint64_t)ten_num * (uint32_t)fnew;
+        uint32_t ttf;
+        if (prod <= 0xffffffffull) {
+          const uint32_t x = (uint32_t)prod;
+          ttf = __umulhi(x, den_inv);
+          uint32_t rem = x - ttf * ten_den;
+          if (rem >= ten_den) {
+            rem -= ten_den;
+            ++ttf;
+          }
+          if (rem >= ten_den) ++ttf;
+        } else {
+          ttf = (uint32_t)std::min<uint64_t>(prod / ten_den, kTenureCap + 1);
+        }
+        const bool capped = ttf > (uint32_t)kTenureCap;
+        if (capped) ttf = kTenureCap;
+        st_cap += capped ? 1u : 0u;
+        const uint32_t expiry = (uint32_t)t - 1u + readlane(Lreg, (t - 1) & 63) + ttf;
+        // a tenure of 0 or 1 never forbids anything
+        const uint32_t gl = gown | (expiry > (uint32_t)t ? 0u : kW8Free);
+        bool put = false;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          if (!put && room[b] != 0ull) {
+            const int at = __builtin_ctzll(room[b]);
+            const bool me = lane == at;
+            sv[b] = me ? vs : sv[b];
+            sc[b] = me ? old : sc[b];
+            sx[b] = me ? expiry & kW8ExpMask : sx[b];
+            sg[b] = me ? gl : sg[b];
+            room[b] &= room[b] - 1ull;
+            put = true;
+          }
+        if (!put) {
+          if (l0 && A < acap) {
+            act[A] = ((vs * kp + old) << 15) | (expiry & kW8ExpMask);
+            actg[A] = (uint8_t)gl;
+          }
+          lanes_joined();
+          spill |= A >= acap;
+          A = min(A + 1, acap);
+        }
+        if (l0) {
+          atomicOr(&tabw[vs * rw + wn], ESC << sn);
+          cg[vs] = (uint16_t)(cs | (gnew << 8) | 0x8000u);
+        }
+        lanes_joined();
+      }
+      if (spill) {
+        if (NW == 1) {
+          give_up();
+          return;
+        }
+        if (l0) *full = 1u;
+        lanes_joined();
+      }
     }
-    wave_sync();
+    if (wid == 0) {
+      const uint32_t vrec = dstar != kW8None ? vs : 0xffffu;
+      if (t <= trace_cap) {  // every lane writes the same record
+        int32_t* tr = late_args()->trace + ((size_t)li * trace_cap + (t - 1)) * 2;
+        tr[0] = (int32_t)(vrec | (cs << 16));
+        tr[1] = fnew;
+      }
+      st_deg += (uint64_t)deg;
+      st_noops += dstar == kW8None ? 1u : 0u;
+      st_ties += dstar != kW8None && shared ? 1u : 0u;
+      fp = fnv_step(fp, vrec, cs, fnew);
+    }
+    f = fnew;
+    if (f < f_best) {
+      f_best = f;
+      best_cur = true;
+    } else if (snap) {
+      best_cur = false;
+    }
+    team_sync<NW>();
   }
 
+  if (rfl(*full)) {  // an entry was lost in the last iteration: the result may be off
+    give_up();
+    return;
+  }
   if (best_cur)
-    for (int v = lane; v < n; v += kWave) gcol[v] = (int16_t)(cg[v] & 0xffu);
-  if (lane == 0) {
-    *f_best_out = f_best;
-    *iters_out = t;
-    if (stats_out) {
-      gptr<int64_t> s = stats_out;
+    for (int v = tid; v < n; v += BLOCK) gcol[v] = (int16_t)(cg[v] & 0xffu);
+  // the lanes' conflict counts (up to 2^41 each) in two halves
+  {
+    const uint64_t lo = (uint64_t)wave_sum_u32((uint32_t)st_conf & 0xffffffu) + ((uint64_t)wave_sum_u32((uint32_t)(st_conf >> 24)) << 24);
+    st_conf = lo;
+  }
+  if constexpr (NW > 1) {
+    if (l0) slot[wid] = make_uint4((uint32_t)st_conf, (uint32_t)(st_conf >> 32), st_cap, 0u);
+    __syncthreads();
+    if (tid == 0) {
+      st_conf = 0ull;
+      st_cap = 0u;
+#pragma unroll
+      for (int w = 0; w < NW; ++w) {
+        const uint4 e = slot[w];
+        st_conf += ((uint64_t)e.y << 32) | e.x;
+        st_cap += e.z;
+      }
+    }
+  }
+  if (tid == 0) {
+    const TabuArgs* o = late_args();
+    o->f_best[li] = f_best;
+    o->iters[li] = t;
+    if (o->stats) {
+      int64_t* s = o->stats + (size_t)li * DLM_NSTATS;
       s[0] = (int64_t)(t - (int)st_noops);
       s[1] = (int64_t)st_noops;
       s[2] = (int64_t)st_conf;
@@ -608,7 +935,7 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
       s[6] = 0;
       s[7] = 0;
     }
-    if (hash_out) *hash_out = fp;
+    if (o->hash) o->hash[li] = fp;
   }
 }
 

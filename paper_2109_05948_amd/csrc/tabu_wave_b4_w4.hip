@@ -1,0 +1,10 @@
+// WAVE8: 4-bit entries, 4 waves per individual.
+#include "tabu_wave_kernel.h"
+
+namespace dlm {
+
+int launch_w4_4(const TabuArgs& a, int pop, int acap, size_t lds, hipStream_t s) {
+  return launch_w8_waves<4, 4>(a, pop, acap, lds, s);
+}
+
+}  // namespace dlm

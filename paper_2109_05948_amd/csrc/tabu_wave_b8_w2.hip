@@ -1,0 +1,10 @@
+// WAVE8: 8-bit entries, 2 waves per individual.
+#include "tabu_wave_kernel.h"
+
+namespace dlm {
+
+int launch_w8_2(const TabuArgs& a, int pop, int acap, size_t lds, hipStream_t s) {
+  return launch_w8_waves<8, 2>(a, pop, acap, lds, s);
+}
+
+}  // namespace dlm

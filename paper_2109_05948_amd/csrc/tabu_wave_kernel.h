@@ -1,0 +1,40 @@
+// The WAVE8 kernel and its dispatch over row widths, for one entry width and
+// number of waves.
+#pragma once
+
+#include "tabu_wave.h"
+#include "tabu_wave_launch.h"
+
+namespace dlm {
+
+template <int BITS, int NW, int RW>
+__global__ __launch_bounds__(64 * NW) void tabucol_w8_kernel(TabuArgs a, int32_t acap) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  tabu_w8_individual<BITS, NW, RW>(a, blockIdx.x, acap, smem);
+}
+
+template <int BITS, int NW, int RW>
+static int launch_w8_rows(const TabuArgs& a, int pop, int acap, size_t lds, hipStream_t s) {
+  auto kern = tabucol_w8_kernel<BITS, NW, RW>;
+  DLM_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  hipLaunchKernelGGL(kern, dim3(pop), dim3(64 * NW), lds, s, a, acap);
+  DLM_HIP(hipGetLastError());
+  return DLM_OK;
+}
+
+template <int BITS, int NW>
+static int launch_w8_waves(const TabuArgs& a, int pop, int acap, size_t lds, hipStream_t s) {
+  switch (w8_bucket(a.k, BITS)) {
+#define DLM_W8(RW) \
+  case RW:         \
+    return launch_w8_rows<BITS, NW, RW>(a, pop, acap, lds, s);
+    DLM_W8(1) DLM_W8(2) DLM_W8(3) DLM_W8(4) DLM_W8(5) DLM_W8(6) DLM_W8(7) DLM_W8(8)
+    DLM_W8(9) DLM_W8(10) DLM_W8(11) DLM_W8(12) DLM_W8(16) DLM_W8(24) DLM_W8(32)
+    case 64:
+      if constexpr (BITS == 8) return launch_w8_rows<BITS, NW, 64>(a, pop, acap, lds, s);
+#undef DLM_W8
+  }
+  return set_error(DLM_E_UNSUPPORTED, "dlm_tabu_batch: k=%d too large for the wave table", a.k);
+}
+
+}  // namespace dlm

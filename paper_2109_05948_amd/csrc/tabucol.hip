@@ -28,10 +28,13 @@
 // The byte-gamma tier gives up on an individual whose colour classes would
 // pass 255 vertices; a rerun kernel repeats those from their start colouring
 // with the 16-bit device table, so every tier returns the same result.
+#include <math.h>
+
 #include <mutex>
 
 #include "tabu_body.h"
 #include "tabu_wave.h"
+#include "tabu_wave_launch.h"
 
 namespace dlm {
 
@@ -64,56 +67,22 @@ __global__ __launch_bounds__(BLOCK) void tabucol_rerun_kernel(TabuArgs a, const 
   }
 }
 
-// WAVE8: one wavefront per individual (tabu_wave.h)
-template <int KQ>
-__global__ __launch_bounds__(64) void tabucol_w8_kernel(TabuArgs a, int32_t acap) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  tabu_w8_individual<KQ>(a, blockIdx.x, acap, smem);
-}
-
-template <int KQ>
-static int launch_w8_kq(const TabuArgs& a, int pop, int acap, size_t lds, hipStream_t s) {
-  auto kern = tabucol_w8_kernel<KQ>;
-  DLM_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-  hipLaunchKernelGGL(kern, dim3(pop), dim3(64), lds, s, a, acap);
-  DLM_HIP(hipGetLastError());
-  return DLM_OK;
-}
-
-static int launch_w8(const TabuArgs& a, int pop, int acap, size_t lds, hipStream_t s) {
-  switch (w8_bucket(a.k)) {
-    case 8: return launch_w8_kq<8>(a, pop, acap, lds, s);
-    case 16:  // rows of 9 to 15 and 17 to 23 dwords get a kernel of their exact width
-      switch (tab_stride(a.k) >> 2) {
-        case 9: return launch_w8_kq<9>(a, pop, acap, lds, s);
-        case 10: return launch_w8_kq<10>(a, pop, acap, lds, s);
-        case 11: return launch_w8_kq<11>(a, pop, acap, lds, s);
-        case 12: return launch_w8_kq<12>(a, pop, acap, lds, s);
-        case 13: return launch_w8_kq<13>(a, pop, acap, lds, s);
-        case 14: return launch_w8_kq<14>(a, pop, acap, lds, s);
-        case 15: return launch_w8_kq<15>(a, pop, acap, lds, s);
-        default: return launch_w8_kq<16>(a, pop, acap, lds, s);
-      }
-    case 24:
-      switch (tab_stride(a.k) >> 2) {
-        case 17: return launch_w8_kq<17>(a, pop, acap, lds, s);
-        case 18: return launch_w8_kq<18>(a, pop, acap, lds, s);
-        case 19: return launch_w8_kq<19>(a, pop, acap, lds, s);
-        case 20: return launch_w8_kq<20>(a, pop, acap, lds, s);
-        case 21: return launch_w8_kq<21>(a, pop, acap, lds, s);
-        case 22: return launch_w8_kq<22>(a, pop, acap, lds, s);
-        case 23: return launch_w8_kq<23>(a, pop, acap, lds, s);
-        default: return launch_w8_kq<24>(a, pop, acap, lds, s);
-      }
-    case 32: return launch_w8_kq<32>(a, pop, acap, lds, s);
-    case 64: return launch_w8_kq<64>(a, pop, acap, lds, s);
-  }
-  return set_error(DLM_E_UNSUPPORTED, "dlm_tabu_batch: k=%d too large for the wave table", a.k);
-}
-
 __global__ void copy_i16_kernel(const int16_t* __restrict__ src, int16_t* __restrict__ dst, int64_t count) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < count) dst[i] = src[i];
+}
+
+static int launch_w8(const TabuArgs& a, int pop, int bits, int nw, int acap, size_t lds, hipStream_t s) {
+  if (bits == 4) switch (nw) {
+      case 1: return launch_w4_1(a, pop, acap, lds, s);
+      case 2: return launch_w4_2(a, pop, acap, lds, s);
+      default: return launch_w4_4(a, pop, acap, lds, s);
+    }
+  switch (nw) {
+    case 1: return launch_w8_1(a, pop, acap, lds, s);
+    case 2: return launch_w8_2(a, pop, acap, lds, s);
+    default: return launch_w8_4(a, pop, acap, lds, s);
+  }
 }
 
 struct Rerun {
@@ -186,9 +155,76 @@ struct TabuPlan {
   uint64_t start_bytes = 0;   // SPLIT8: copy of the start colourings
   uint64_t slot_bytes = 0;    // SPLIT8: one rerun slot (packed 16-bit table)
   int64_t slots = 0;          // SPLIT8: rerun slots
-  int32_t acap = 0;           // WAVE8: tabu pairs each individual's LDS holds
+  int32_t acap = 0;           // WAVE8: side-list entries each individual's LDS holds
+  int bits = 8;               // WAVE8: bits per table entry
   uint64_t ws_bytes = 0;      // total, each part on a 256-byte boundary
 };
+
+// LDS bytes that bound what the wave table serves: a byte per (v, c), 8 bytes
+// per vertex and colour pair state, 64 tabu pairs.  The kernels need less; the
+// bound stays where it is so that the shapes the tier serves do not move.
+static uint64_t w8_least_bytes(int n, int k) {
+  const uint32_t kp = (uint32_t)tab_stride(k);
+  return (uint64_t)align16((uint32_t)(n + 1) * kp) + align16(2u * (uint32_t)(n + 1)) + align16(2u * (uint32_t)n) +
+         align16((uint32_t)n) + 4u * 320u + align16(2u * kp) + 16u + 4u * kWave;
+}
+
+// Table entries of a colouring of k random classes that reach 15: the number
+// of neighbours of v in a class is close to Poisson of mean deg(v) / k.
+static double w8_escapes(const dlm_graph* g, int k) {
+  double total = 0.0;
+  for (const auto& d : g->degrees) {
+    const double mu = (double)d.first / k;
+    double term = exp(-mu), below = 0.0;
+    for (int i = 0; i < 15; ++i) {
+      below += term;
+      term *= mu / (i + 1);
+    }
+    total += (double)d.second * k * std::max(0.0, 1.0 - below);
+  }
+  return total;
+}
+
+// Entry width, waves per individual and side-list entries of a call.
+//
+// 4-bit entries hold twice the individuals per CU, so they are taken where few
+// entries escape by size: each costs the side list's walk a lane, and its
+// registers hold 128.  Waves: the chain of one iteration is shortened most by
+// a second wave (G(500, 0.5), k = 49, 64 individuals: 16.7 -> 15.1 ms), but
+// where the LDS limits the individuals per CU its lists cost residents, and
+// short rows leave it nothing to do (n = 100: 10.3 -> 10.9 ms).  So: one wave
+// below 256 vertices or where more waves would hold fewer individuals, four
+// where at most two individuals fit a CU (G(1000, 0.5), k = 85, 2,048
+// individuals: 170, 121 and 100 ms with one, two and four), else two.
+static void w8_shape(const dlm_graph* g, const dlm_tabu_params* p, int pop, TabuPlan& P) {
+  const int n = g->n, k = p->k;
+  const int64_t lds_max = device_lds_limit(), lds_cu = device_lds_per_cu(), cus = device_cu_count();
+  // tabu pairs to hold: a random start has f = m / k, and while f falls from
+  // there the live pairs peak at little more than half the first tenure
+  const int64_t f0 = g->nnz / 2 / k;
+  int64_t want = 6 * p->ten_num * f0 / (10 * (int64_t)p->ten_den) + p->ten_rand + 32;
+  P.bits = 8;
+  const double esc = w8_escapes(g, k);
+  if (esc <= 192.0 && (uint64_t)n * 8u * (uint64_t)w8_row_dwords(k, 4) <= (1ull << 17)) {
+    P.bits = 4;
+    want += (int64_t)(2.0 * esc) + 32;
+  }
+  want = std::min<int64_t>(16384, (want + 63) & ~63ll);
+  // individuals a CU holds with w waves each (0: not one)
+  auto resident = [&](int w) -> int64_t {
+    if ((int64_t)w8_layout(n, k, P.bits, w, kWave).bytes > lds_max) return 0;
+    const int64_t fit = lds_cu / (int64_t)w8_layout(n, k, P.bits, w, (int)want).bytes;
+    return std::max<int64_t>(1, std::min<int64_t>({fit, 32 / w, ((int64_t)pop + cus - 1) / cus}));
+  };
+  int nw = 1;
+  if (n >= 256 && resident(2) >= resident(1)) nw = resident(4) >= resident(1) && resident(1) <= 2 && n > 512 ? 4 : 2;
+  // as many individuals per CU as the table allows; the rest of their
+  // share of the CU's LDS holds side-list entries
+  const int64_t budget = std::min<int64_t>(lds_max, lds_cu / std::max<int64_t>(1, resident(nw))) & ~15ll;
+  P.acap = (int32_t)std::min<int64_t>(16384, ((budget - (int64_t)w8_layout(n, k, P.bits, nw, 0).bytes) / 5) & ~63ll);
+  P.block = nw * kWave;
+  P.lds = w8_layout(n, k, P.bits, nw, P.acap).bytes;
+}
 
 static uint64_t align256(uint64_t x) { return (x + 255u) & ~255ull; }
 
@@ -215,28 +251,20 @@ static int tabu_plan(const char* fn, const dlm_graph* g, const dlm_tabu_params* 
   // automatic table with an automatic (or 64-thread) block: the wave table
   // whenever it holds the individual (it beat the block kernels at every
   // measured shape, one individual per CU included)
-  const bool wave_auto = p->table == DLM_TABLE_AUTO && (p->block == 0 || p->block == 64) && w8_bucket(k) != 0 &&
+  const bool wave_auto = p->table == DLM_TABLE_AUTO && (p->block == 0 || p->block == 64) && w8_bucket(k, 8) != 0 &&
                          (uint64_t)n * (uint64_t)tab_stride(k) <= (1ull << 17) &&
-                         w8_layout(n, k, 0).bytes + 4u * kWave <= (uint64_t)lds_max;
+                         w8_least_bytes(n, k) <= (uint64_t)lds_max;
   if (p->table == DLM_TABLE_WAVE8 || wave_auto) {
     if (p->block != 0 && p->block != 64)
       return set_error(DLM_E_INVAL, "%s: the wave table runs 64 threads per individual (block=%d)", fn, p->block);
     const uint64_t kp = (uint64_t)tab_stride(k);
-    if (w8_bucket(k) == 0 || (uint64_t)n * kp > (1ull << 17))
+    if (w8_bucket(k, 8) == 0 || (uint64_t)n * kp > (1ull << 17))
       return set_error(DLM_E_UNSUPPORTED, "%s: n=%d, k=%d outside the wave table (k <= 256, n*kp <= 2^17)", fn, n, k);
-    const uint64_t base = w8_layout(n, k, 0).bytes;
-    const int64_t lds_cu = device_lds_per_cu();
-    if (base + 4u * kWave > (uint64_t)lds_max)
+    if (w8_least_bytes(n, k) > (uint64_t)lds_max)
       return set_error(DLM_E_UNSUPPORTED, "%s: %llu bytes of LDS needed, %lld available", fn,
-                       (unsigned long long)(base + 4u * kWave), (long long)lds_max);
-    // as many individuals per CU as the table allows; the rest of their
-    // share of the CU's LDS holds tabu pairs
-    const int64_t res = std::max<int64_t>(1, std::min<int64_t>(32, lds_cu / (int64_t)(base + 4u * kWave)));
-    const int64_t budget = std::min<int64_t>(lds_max, lds_cu / res) & ~15ll;
-    P.acap = (int32_t)std::min<int64_t>(16384, ((budget - (int64_t)base) / 4) & ~63ll);
+                       (unsigned long long)w8_least_bytes(n, k), (long long)lds_max);
+    w8_shape(g, p, pop, P);
     P.table = DLM_TABLE_WAVE8;
-    P.block = 64;
-    P.lds = w8_layout(n, k, P.acap).bytes;
     if (pop > 0) {
       P.slot_bytes = tab_entries(n, k) * TabGlobal16::kGlobalBytes;
       int64_t slots = std::min<int64_t>(pop, 2 * (int64_t)device_cu_count());
@@ -317,7 +345,7 @@ static int tabu_run(const char* fn, const dlm_graph* g, const dlm_tabu_params* p
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   TabuArgs a{g->row_ptr, g->col_idx, g->erow, colors, f_best, iters, stats, hash, trace, nullptr,
              make_key(p->seed), n, k, p->max_iters, p->ten_num, p->ten_den, p->ten_rand,
-             p->ind_base, p->trace_cap};
+             p->ind_base, p->trace_cap, g->ell, g->adj, g->ell_stride};
   if (P.gtab_bytes > 0) a.gtab = ws;
   switch (P.table) {
     case DLM_TABLE_WAVE8: {
@@ -327,7 +355,7 @@ static int tabu_run(const char* fn, const dlm_graph* g, const dlm_tabu_params* p
       hipLaunchKernelGGL(copy_i16_kernel, dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, s, colors, start,
                          cells);
       DLM_HIP(hipGetLastError());
-      if ((rc = launch_w8(a, pop, P.acap, P.lds, s)) != DLM_OK) return rc;
+      if ((rc = launch_w8(a, pop, P.bits, P.block / kWave, P.acap, P.lds, s)) != DLM_OK) return rc;
       const Rerun rr{start, slot_mem, (int32_t)P.slots};
       return launch_tab<TabGlobal16>(a, pop, 256, P.lds_rr, s, &rr);
     }

@@ -255,3 +255,57 @@ def test_wave_static_entry_point(dlm, dev):
     gpu = {kk: v.cpu().numpy() for kk, v in r.items()}
     gpu["hash"] = gpu["hash"].view(np.uint64)
     compare(gpu, ref, range(pop), "wave8 static")
+
+
+WIDTHS = [  # (n, p, k, T, pop, sampled rows): entry width, waves per individual, row dwords
+    (100, 0.5, 9, 2000, 4, None),            # 4 bits, one wave
+    (300, 0.5, 22, 2000, 5, None),           # 4 bits, two waves, entries that outgrow 4 bits
+    (600, 0.5, 44, 1500, 3, None),           # the same with four waves and more escapes than a register bank
+    (400, 0.97, 256, 400, 3, None),          # 4 bits, 32 dwords, every 8-bit colour in use
+    (1100, 0.6, 110, 300, 2, None),          # 4 bits, the 16-dword bucket, rows past 512 neighbours
+    (1000, 0.95, 100, 400, 2, None),         # 8 bits, four waves, 25 dwords
+    (520, 0.95, 250, 300, 3, None),          # 8 bits, 63 dwords: 4-bit rows would pass 2^17 entries
+    (300, 0.3, 14, 200, 6000, (0, 2999, 5999)),   # one wave above 256 vertices: the CU is full of individuals
+    (600, 0.1, 12, 150, 2000, (0, 777, 1999)),    # two waves above 512 vertices
+]
+
+
+@pytest.mark.parametrize("shape", WIDTHS, ids=lambda s: "n%d_p%g_k%d" % s[:3])
+def test_wave_entry_widths_and_waves(dlm, dev, shape):
+    n, p, k, T, pop, rows = shape
+    g = gnp(n, p, seed=n + k)
+    starts = oracle.init_random(n, k, pop, seed=5, ind_base=3)
+    at = np.arange(pop) if rows is None else np.array(rows)
+    ref = oracle.tabucol_batch(g, starts[at], at + 3, k, T, seed=23)
+    say(f"wave8 widths n={n} p={p} k={k} T={T} pop={pop}")
+    gpu = gpu_run(dlm, g, starts, k, T, 23, ind_base=3)
+    compare({x: gpu[x][at] for x in ("f_best", "iters", "stats", "hash", "colors")}, ref, at, f"widths n{n} k{k}")
+
+
+def test_wave_reruns_when_many_entries_outgrow_four_bits_at_once(dlm, dev):
+    """K(100, 100) with colours 0..6 on both sides, k = 20: the neighbours of a
+    vertex share their rows, so a class of one side growing from 14 to 15
+    makes 100 entries escape in one move, more than the 64 a move may hand
+    over; the individual gives up and its rerun equals the oracle."""
+    n, k, T, pop = 200, 20, 400, 4
+    g = from_edges(n, np.array([(i, 100 + j) for i in range(100) for j in range(100)], np.int64), "K(100,100)")
+    starts = oracle.init_random(n, 7, pop, seed=6)
+    assert all(np.bincount(s[:100], minlength=7).max() >= 14 for s in starts)
+    ref = oracle.tabucol_batch(g, starts, np.arange(pop), k, T, seed=7)
+    say("wave8 mass escape K(100,100) k=20")
+    gpu = gpu_run(dlm, g, starts, k, T, 7)
+    compare(gpu, ref, range(pop), "mass escape")
+
+
+def test_wave_reruns_when_the_side_list_overflows(dlm, dev):
+    """All vertices in one class: f starts at every edge, far above a random
+    start's, so tenures far exceed what the LDS share of one of 8192
+    individuals was sized for."""
+    n, k, T, pop = 120, 12, 500, 8192
+    g = gnp(n, 0.5, seed=4)
+    starts = np.zeros((pop, n), np.int16)
+    at = np.array([0, 1, 4095, 8191])
+    ref = oracle.tabucol_batch(g, starts[at], at, k, T, seed=3)
+    say("wave8 side-list overflow n=120 k=12")
+    gpu = gpu_run(dlm, g, starts, k, T, 3)
+    compare({x: gpu[x][at] for x in ("f_best", "iters", "stats", "hash", "colors")}, ref, at, "side list")
