@@ -133,6 +133,13 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
   return max(max(readlane(x, 0), readlane(x, 16)), max(readlane(x, 32), readlane(x, 48)));
 }
 
+// Ends the block after a lane-masked one.  Without it the two paths of a
+// lane-masked block at the end of a uniform one meet where the uniform paths
+// do, and the compiler then takes every value that differs between the uniform
+// paths for lane-dependent: vector registers, masked loops and branches
+// (14,000 instead of 8,000 cycles an iteration at G(500, 0.5)).
+__device__ __forceinline__ void lanes_joined() { asm volatile(""); }
+
 __host__ __device__ constexpr uint32_t align16(uint32_t x) { return (x + 15u) & ~15u; }
 
 // FNV-1a over 64-bit move records
@@ -176,7 +183,7 @@ struct dlm_graph {
   // device uint16[n][ell_stride], the neighbours of v, then n + 1 (at least once).
   // Rows start on 128-byte lines, so a row's address needs no row_ptr and a row
   // of 250 neighbours is 4 lines instead of 9;
-  // device uint32[n][n / 32 + 1], the adjacency bits of v (bit n is 0).
+  // device uint32[n][2 (n / 64 + 1)], the adjacency bits of v, then zeros.
   uint16_t* ell = nullptr;
   uint32_t* adj = nullptr;
   int32_t ell_stride = 0;

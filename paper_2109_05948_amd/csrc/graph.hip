@@ -116,7 +116,7 @@ __global__ __launch_bounds__(256) void evaluate_kernel(const int32_t* __restrict
 __global__ __launch_bounds__(64) void adjacency_kernel(const int32_t* __restrict__ row_ptr,
                                                        const int32_t* __restrict__ col_idx, int32_t n, int32_t stride,
                                                        uint16_t* __restrict__ ell, uint32_t* __restrict__ adj) {
-  const int v = blockIdx.x, rs = row_ptr[v], deg = row_ptr[v + 1] - rs, aw = (n >> 5) + 1;
+  const int v = blockIdx.x, rs = row_ptr[v], deg = row_ptr[v + 1] - rs, aw = 2 * ((n >> 6) + 1);
   for (int e = threadIdx.x; e < stride; e += 64)
     ell[(int64_t)v * stride + e] = e < deg ? (uint16_t)col_idx[rs + e] : (uint16_t)(n + 1);
   for (int w = threadIdx.x; w < aw; w += 64) {
@@ -255,7 +255,7 @@ int dlm_graph_create(int32_t n, const int32_t* row_ptr, const int32_t* col_idx,
   if (n <= kEllMaxVertices) {
     g->ell_stride = (max_deg + 64) & ~63;
     if ((e = hipMalloc(&g->ell, sizeof(uint16_t) * (size_t)n * (size_t)g->ell_stride)) != hipSuccess ||
-        (e = hipMalloc(&g->adj, sizeof(uint32_t) * (size_t)n * (size_t)(n / 32 + 1))) != hipSuccess)
+        (e = hipMalloc(&g->adj, sizeof(uint32_t) * (size_t)n * (size_t)(2 * (n / 64 + 1)))) != hipSuccess)
       return fail(e, "graph upload (adjacency)");
     hipLaunchKernelGGL(adjacency_kernel, dim3((unsigned)n), dim3(64), 0, s, g->row_ptr, g->col_idx, n, g->ell_stride,
                        g->ell, g->adj);

@@ -51,6 +51,7 @@
 #include <type_traits>
 
 #include "tabu_body.h"
+#include "wave_util.h"
 
 namespace dlm {
 
@@ -109,87 +110,6 @@ typedef unsigned short w8_u16x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t pk_min_u16(uint32_t a, uint32_t b) {
   const w8_u16x2 x = __builtin_bit_cast(w8_u16x2, a), y = __builtin_bit_cast(w8_u16x2, b);
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(x, y));
-}
-
-// Orders the wave's LDS accesses around it in the compiler's view; the LDS
-// itself serves one wave's instructions in issue order.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// a uniform 32-bit value in a scalar register of its own (see own_sgpr)
-__device__ __forceinline__ uint32_t own_u32(uint32_t x) {
-  asm volatile("" : "+s"(x));
-  return x;
-}
-
-// The twenty Philox4x32-10 round keys (the seed's two words bumped by the
-// Weyl constants), computed once and held in vector registers: in scalar
-// registers, the scarce file here, they would spill, and recomputing them
-// per call costs twenty scalar adds.
-struct W8RoundKeys {
-  uint32_t k[20];
-};
-
-__device__ __forceinline__ uint32_t to_vgpr(uint32_t x) {
-  uint32_t y;
-  asm volatile("v_mov_b32 %0, %1" : "=v"(y) : "s"(x));
-  return y;
-}
-
-__device__ __forceinline__ W8RoundKeys w8_round_keys(Key key) {
-  W8RoundKeys rk;
-  uint32_t k0 = key.k0, k1 = key.k1;
-#pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    rk.k[2 * r] = to_vgpr(k0);
-    rk.k[2 * r + 1] = to_vgpr(k1);
-    k0 += 0x9E3779B9u;
-    k1 += 0xBB67AE85u;
-  }
-  return rk;
-}
-
-// one v_bitop3_b32
-__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
-  return (uint32_t)__builtin_amdgcn_bitop3_b32((int)a, (int)b, (int)c, 0x96);
-}
-
-// Ends the block after a lane-masked one.  Without it the two paths of a
-// lane-masked block at the end of a uniform one meet where the uniform paths
-// do, and the compiler then takes every value that differs between the uniform
-// paths for lane-dependent: vector registers, masked loops and branches
-// (14,000 instead of 8,000 cycles an iteration at G(500, 0.5)).
-__device__ __forceinline__ void lanes_joined() { asm volatile(""); }
-
-// Philox4x32-10 word 0 (the same function as philox_w0) from precomputed round keys
-__device__ __forceinline__ uint32_t philox_w0_rk(uint32_t x0, uint32_t x1, uint32_t x2, uint32_t x3,
-                                                 const W8RoundKeys& rk) {
-#pragma unroll
-  for (int r = 0; r < 10; ++r) {
-    const uint64_t p0 = (uint64_t)0xD2511F53u * x0, p1 = (uint64_t)0xCD9E8D57u * x2;
-    const uint32_t y0 = xor3((uint32_t)(p1 >> 32), x1, rk.k[2 * r]), y2 = xor3((uint32_t)(p0 >> 32), x3, rk.k[2 * r + 1]);
-    x1 = (uint32_t)p1;
-    x3 = (uint32_t)p0;
-    x0 = y0;
-    x2 = y2;
-  }
-  return x0;
-}
-
-__device__ __forceinline__ uint32_t rfl(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
-}
-
-// The kernel's arguments, read again where they are needed late and rarely:
-// output pointers would otherwise hold (and spill) scalar registers all along.
-// The kernel's first argument is the TabuArgs block.
-__device__ __forceinline__ const TabuArgs* late_args() {
-  uint64_t p = (uint64_t)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(p));
-  return (const TabuArgs*)p;
 }
 
 // Barrier of the waves that share an individual.
@@ -261,7 +181,7 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
   const uint32_t rw = (uint32_t)w8_row_dwords(k, BITS), kp = rw * PER;
   const gptr<const uint16_t> ell = own_sgpr(a.ell);
   const gptr<const uint32_t> adj = own_sgpr(a.adj);
-  const uint32_t stride = own_u32((uint32_t)a.ell_stride), aw = ((uint32_t)n >> 5) + 1u;
+  const uint32_t stride = own_u32((uint32_t)a.ell_stride), aw = 2u * (((uint32_t)n >> 6) + 1u);
   const int trace_cap = (int)own_u32((uint32_t)(a.trace ? a.trace_cap : 0)), T = (int)own_u32((uint32_t)a.T);
   const Key key{own_u32(a.key.k0), own_u32(a.key.k1)};
   const uint32_t ten_num = own_u32((uint32_t)a.ten_num), ten_den = own_u32((uint32_t)a.ten_den);
@@ -292,7 +212,7 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
   // Written by every lane: a lane-masked store here would meet the search
   // loop's end in one block, and the compiler would then keep the loop's
   // uniform values (f, t, the lists' lengths) in vector registers.
-  auto give_up = [&]() { late_args()->iters[li] = -2; };
+  auto give_up = [&]() { late_args<TabuArgs>()->iters[li] = -2; };
 
   // 1. start colouring (rejected whole if a colour is outside [0, k)), class sizes
   int bad = 0;
@@ -419,7 +339,7 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
   uint32_t Lreg = 0;
   bool spill = false;  // the tail wave could not take an entry
   bool mailed = false;  // entries wait in mail (one wave: known without a look)
-  const W8RoundKeys rk = w8_round_keys(key);
+  const RoundKeys rk = round_keys(key);
   // the tail wave's register part of the side list: vertex, colour, expiry mod
   // 2^15, gamma | kW8Free; a free lane holds vertex n and a colour that matches nothing
   constexpr int NB = 2;
@@ -876,7 +796,7 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
     if (wid == 0) {
       const uint32_t vrec = dstar != kW8None ? vs : 0xffffu;
       if (t <= trace_cap) {  // every lane writes the same record
-        int32_t* tr = late_args()->trace + ((size_t)li * trace_cap + (t - 1)) * 2;
+        int32_t* tr = late_args<TabuArgs>()->trace + ((size_t)li * trace_cap + (t - 1)) * 2;
         tr[0] = (int32_t)(vrec | (cs << 16));
         tr[1] = fnew;
       }
@@ -921,7 +841,7 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
     }
   }
   if (tid == 0) {
-    const TabuArgs* o = late_args();
+    const TabuArgs* o = late_args<TabuArgs>();
     o->f_best[li] = f_best;
     o->iters[li] = t;
     if (o->stats) {

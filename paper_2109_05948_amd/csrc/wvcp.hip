@@ -24,25 +24,16 @@
 // vertex {colour | gamma of own colour, weight, frozen-until}, per class
 // (largest weight, its multiplicity, second largest weight), the best-g
 // colouring.
+#include <algorithm>
+
 #include "dlm_common.h"
+#include "wvcp.h"
+#include "wvcp_wave.h"
 
 namespace dlm {
 
 constexpr uint64_t kGBias = 1ull << 62;
 constexpr int kWStage = 128;  // tied moves a wave hashes in one staged pass
-
-struct WvcpArgs {
-  const int32_t* row_ptr;
-  const int32_t* col_idx;
-  const int32_t* erow;
-  const int32_t* weights;
-  int16_t* colors;
-  int32_t* best_legal;
-  int64_t* stats;
-  uint64_t* hash;
-  Key key;
-  int32_t n, k, T, R, ten_rand, frz, shift, ind_base, max_w, max_deg;
-};
 
 // gamma rows are padded to kp = k rounded up to 4 colours (one 8-byte read
 // per quad of candidates); per vertex {colour | gamma(own colour) << 16,
@@ -543,8 +534,23 @@ extern "C" int dlm_wvcp_batch(const dlm_graph* g, const dlm_wvcp_params* p, int3
     return set_error(DLM_E_UNSUPPORTED, "dlm_wvcp_batch: %zu bytes of LDS needed", lds);
   WvcpArgs a{g->row_ptr, g->col_idx, g->erow, g->weights, colors, best_legal, stats, hash,
              make_key(p->seed), g->n, p->k, p->iters_per_round, p->rounds, p->ten_rand,
-             (int32_t)((int64_t)p->frz_num * g->n / p->frz_den), p->shift, p->ind_base, g->max_w, g->max_deg};
+             (int32_t)((int64_t)p->frz_num * g->n / p->frz_den), p->shift, p->ind_base, g->max_w, g->max_deg, g->adj};
   hipStream_t s = (hipStream_t)stream;
+  if (p->block == 0) {
+    // the wave search, where it holds the individual and no round can need
+    // wider keys: phi at most doubles from round to round, and the last round
+    // takes 2 max_w.  Otherwise (or with an explicit block) the block search.
+    const int64_t phi0 = ((int64_t)p->k * g->max_w << p->shift) / (2 * (int64_t)g->n);
+    int64_t phi = phi0;
+    for (int r = 1; r < p->rounds && phi < (1ll << 30); ++r) phi *= 2;
+    phi = std::max(std::min<int64_t>(phi, 1ll << 30), (int64_t)(2 * g->max_w) << p->shift);
+    phi = std::max(phi, phi0);
+    const bool narrow = ((int64_t)g->max_w << p->shift) + phi * (int64_t)std::max(g->max_deg, 1) < (int64_t)INT32_MAX - 1;
+    const int bytes = g->max_deg <= 255 ? 1 : 2;
+    if (narrow && g->adj && g->n <= kWvMaxN && p->k <= kWvMaxK &&
+        (int64_t)wv_layout((g->n + 63) / 64, p->k, bytes).bytes <= device_lds_limit())
+      return bytes == 1 ? launch_wvcp_wave8(a, pop, s) : launch_wvcp_wave16(a, pop, s);
+  }
   switch (block) {
     case 64: return launch_wvcp<64>(a, pop, lds, s);
     case 128: return launch_wvcp<128>(a, pop, lds, s);

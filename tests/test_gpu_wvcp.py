@@ -116,3 +116,54 @@ def test_wvcp_wide_keys(dlm, dev):
     assert (r["stats"].cpu().numpy()[:, :6] == ref["stats"][:, :6]).all()
     assert (r["hash"].cpu().numpy().view(np.uint64) == ref["hash"]).all()
     assert (r["colors"].cpu().numpy() == ref["colors"]).all()
+
+
+# one wave per individual: every number of 64-vertex slots and each row split
+# (8, 16, 32 lanes), 8- and 16-bit gammas, slots that end exactly and one past
+WAVE = [  # (n, p, extra colours, wmax, T, R)
+    (3, 0.7, 1, 5, 60, 3),
+    (64, 0.5, 0, 100, 300, 4),
+    (65, 0.5, 20, 3, 300, 4),          # few weights: many equal class maxima
+    (150, 0.9, 10, 100, 300, 3),       # 70 colours or so: 32 lanes per row
+    (200, 0.3, 2, 1, 300, 3),          # unit weights
+    (257, 0.2, 0, 100, 300, 3),
+    (330, 0.1, 25, 100, 250, 3),
+    (420, 0.7, 0, 100, 200, 2),        # degrees past 255: 16-bit gammas
+    (512, 0.55, 3, 50, 150, 2),
+]
+
+
+@pytest.mark.parametrize("n,p,more,wmax,T,R", WAVE)
+def test_wvcp_wave_shapes(dlm, dev, n, p, more, wmax, T, R):
+    g = gnp(n, p, seed=n).with_weights(uniform_weights(n, 1, wmax, seed=n + 1))
+    pop = 3
+    starts = [oracle.greedy_init(g, seed=2, ind=i) for i in range(pop)]
+    k = max(u for _, u in starts) + more
+    starts = np.stack([c for c, _ in starts])
+    starts[1] = oracle.init_random(n, k, 1, seed=8)[0]  # an illegal start: phi rises
+    ref = oracle.wvcp_batch(g, starts, np.arange(pop), k, T, R, seed=6)
+    G = dlm.Graph.from_csr(g)
+    say(f"wvcp wave n={n} k={k} degree {g.max_deg} T={T} R={R}")
+    r = dlm.wvcp_batch(G, torch.from_numpy(starts).cuda(), k, T, R, seed=6)
+    torch.cuda.synchronize()
+    assert (r["best_legal"].cpu().numpy() == ref["best_legal"]).all()
+    assert (r["stats"].cpu().numpy()[:, :6] == ref["stats"][:, :6]).all()
+    assert (r["hash"].cpu().numpy().view(np.uint64) == ref["hash"]).all()
+    assert (r["colors"].cpu().numpy() == ref["colors"]).all()
+
+
+def test_wvcp_wave_and_block_agree(dlm, dev):
+    """The automatic block (one wave) against the 256-thread search, with a
+    start outside the colours and a run of no iterations."""
+    g = gnp(180, 0.4, seed=3).with_weights(uniform_weights(180, 1, 100, seed=4))
+    G = dlm.Graph.from_csr(g)
+    start, used = dlm.init_population(G, 0, 200, seed=9, mode="greedy")
+    k = int(used.max().item())
+    start[7, 5] = k
+    for T, R in ((400, 4), (0, 3), (50, 0)):
+        say(f"wvcp wave against block T={T} R={R}")
+        a, b = (dlm.wvcp_batch(G, start.clone(), k, T, R, seed=5, block=x) for x in (0, 256))
+        ok = torch.arange(200, device="cuda") != 7
+        assert a["best_legal"][7].item() == b["best_legal"][7].item() == -1
+        for x in ("best_legal", "colors", "stats", "hash"):
+            assert (a[x][ok] == b[x][ok]).all(), x
