@@ -131,7 +131,8 @@ int dlm_init_population(const dlm_graph* g, int32_t k, int32_t pop, uint64_t see
 #define DLM_TABLE_WAVE8 6      /* one to four wavefronts per individual (the library's choice, block 0 or 64), all
                                   in LDS: 4 or 8 bits per (v,c) holding gamma, or an escape for the current colour,
                                   tabu pairs and gammas that do not fit, and a side list of the escaped pairs;
-                                  needs k <= 256 and n * kp <= 2^17.  An individual whose colour classes would pass
+                                  needs k <= 256 and n * kp <= 2^17 when asked for (AUTO also takes it for
+                                  larger tables that fit in 4 bits).  An individual whose colour classes would pass
                                   127 vertices, or whose side list would overflow, is rerun from its start with
                                   GLOBAL16 (same results) */
 

@@ -15,8 +15,9 @@
 //               v*'s adjacency bits, expired pairs lose their tabu state, and a
 //               pair that is neither tabu nor too large returns to the table.
 //               128 entries live in registers of the last wave, one or two per
-//               lane; the rest in act[] = (v*kp + c) << 15 | expiry mod 2^15 and
-//               actg[] = gamma | 0x80 on a pair that is not tabu
+//               lane; the rest in act[] = v << 17 | c << 9 | low 9 bits of the
+//               expiry mod 2^15 and actg[] = its high 6 bits << 8 | gamma | 0x80
+//               on a pair that is not tabu
 //   cg[v]       colour (bits 0..7) | gamma[v][col v] (bits 8..14) |
 //               "listed" (bit 15)
 //   list[w]     per wave, the listed vertices it scans: every conflicting
@@ -59,7 +60,7 @@ constexpr uint32_t kW8ClassMax = 127u;
 constexpr uint32_t kW8None = 255u;        // biased delta (delta + 128) of "no admissible move"
 constexpr uint32_t kW8ExpMask = 0x7fffu;  // expiries are kept modulo 2^15
 constexpr uint32_t kW8NoKey = 0xffffffffu;
-constexpr uint32_t kW8Free = 0x80u;  // actg: not tabu
+constexpr uint32_t kW8Free = 0x80u;  // gamma of a side-list pair: not tabu
 constexpr int kW8Stage = 128;        // tied rows a wave stages: up to 64 waiting and 64 more
 constexpr int kW8Mail = 64;          // entries that can escape by growth in one move
 
@@ -68,6 +69,12 @@ struct W8Layout {
 };
 
 __host__ __device__ constexpr int w8_row_dwords(int k, int bits) { return (k * bits + 31) >> 5; }
+
+// Vertices one wave's list holds: all of them for one wave.  Several waves share
+// them evenly but for chance (about sqrt(n)); half of them and 64 is room enough
+// in earnest, and a list that is full all the same leaves the individual to the
+// 16-bit rerun.
+__host__ __device__ constexpr int w8_list_cap(int n, int nw) { return nw == 1 || n / 2 + 64 > n ? n : n / 2 + 64; }
 
 // LDS of one individual searched by nw waves, with room for acap side-list
 // entries (a multiple of 64).  A row read covers up to RW dwords; reads past
@@ -82,8 +89,8 @@ __host__ __device__ inline W8Layout w8_layout(int n, int k, int bits, int nw, in
   o += align16(4u * (uint32_t)(n + 2) * (uint32_t)w8_row_dwords(k, bits));
   L.cg = o;
   o += align16(2u * (uint32_t)(n + 2));
-  L.list = o;
-  o += (uint32_t)nw * align16(2u * (uint32_t)(n + 1));
+  L.list = o;  // one entry more than a list holds: where lanes without a vertex to append write
+  o += (uint32_t)nw * align16(2u * (uint32_t)(w8_list_cap(n, nw) + 1));
   L.stage = o;  // one entry more than kW8Stage: where lanes without a tied row write
   o += (uint32_t)nw * 4u * (kW8Stage + 4);
   L.slot = o;  // 16 bytes per wave, then "give up" and the mail count
@@ -93,7 +100,7 @@ __host__ __device__ inline W8Layout w8_layout(int n, int k, int bits, int nw, in
   L.act = o;  // one entry more than acap: where lanes without an entry write
   o += 4u * (uint32_t)acap + 4u;
   L.actg = o;
-  o += (uint32_t)acap + 12u;
+  o += 2u * (uint32_t)acap + 12u;
   L.bytes = o;
   return L;
 }
@@ -187,12 +194,11 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
   const uint32_t ten_num = own_u32((uint32_t)a.ten_num), ten_den = own_u32((uint32_t)a.ten_den);
   const uint32_t ten_rand = own_u32((uint32_t)a.ten_rand);
   const uint32_t den_inv = 0xffffffffu / ten_den;
-  // ceil(2^32 / kp): v = umulhi(v*kp + c, kp_inv) is exact for v*kp + c < 2^17
-  const uint32_t kp_inv = (uint32_t)((0x100000000ull + kp - 1u) / kp);
   const W8Layout L = w8_layout(n, k, BITS, NW, acap);
   uint32_t* tabw = reinterpret_cast<uint32_t*>(smem + L.tab);
   uint16_t* cg = reinterpret_cast<uint16_t*>(smem + L.cg);
-  uint16_t* list = reinterpret_cast<uint16_t*>(smem + L.list + (uint32_t)wid * align16(2u * (uint32_t)(n + 1)));
+  uint16_t* list = reinterpret_cast<uint16_t*>(smem + L.list + (uint32_t)wid * align16(2u * (uint32_t)(w8_list_cap(n, NW) + 1)));
+  const int lcap = w8_list_cap(n, NW);
   uint32_t* stage = reinterpret_cast<uint32_t*>(smem + L.stage + (uint32_t)wid * 4u * (kW8Stage + 4));
   uint4* slot = reinterpret_cast<uint4*>(smem + L.slot);
   // "give up" is written between the fold's barrier and the iteration's last
@@ -201,7 +207,7 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
   uint32_t* mailn = full + 1;
   uint32_t* mail = reinterpret_cast<uint32_t*>(smem + L.mail);
   uint32_t* act = reinterpret_cast<uint32_t*>(smem + L.act);
-  uint8_t* actg = smem + L.actg;
+  uint16_t* actg = reinterpret_cast<uint16_t*>(smem + L.actg);
   const gptr<int16_t> gcol = own_sgpr(a.colors + (size_t)li * n);
   const __attribute__((address_space(4))) int32_t* row_c =
       (const __attribute__((address_space(4))) int32_t*)(const int32_t*)own_sgpr(a.row_ptr);
@@ -294,8 +300,8 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
           } else if (g >= ESC) {
             const uint32_t p = atomicAdd(mailn, 1u);
             if (p < (uint32_t)acap) {
-              act[p] = (v * kp + c) << 15;
-              actg[p] = (uint8_t)(g | kW8Free);
+              act[p] = (v << 17) | (c << 9);
+              actg[p] = (uint16_t)(g | kW8Free);
             }
             g = ESC;
           }
@@ -361,11 +367,10 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
       const bool get = ((room[b] >> lane) & 1ull) != 0ull && rank < A;
       const int i = get ? A - 1 - rank : acap;
       const uint32_t e = act[i], g = actg[i];
-      const uint32_t v = __umulhi(e >> 15, kp_inv);
-      sv[b] = get ? v : sv[b];
-      sc[b] = get ? (e >> 15) - v * kp : sc[b];
-      sx[b] = get ? e & kW8ExpMask : sx[b];
-      sg[b] = get ? g : sg[b];
+      sv[b] = get ? e >> 17 : sv[b];
+      sc[b] = get ? (e >> 9) & 0xffu : sc[b];
+      sx[b] = get ? (e & 0x1ffu) | ((g >> 8) << 9) : sx[b];
+      sg[b] = get ? g & 0xffu : sg[b];
       const uint64_t got = __ballot(get);
       A -= __popcll(got);
       room[b] &= ~got;
@@ -441,9 +446,9 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
     };
     auto act_delta = [&](int i0, uint32_t& v, uint32_t& c, uint32_t& x) -> uint32_t {
       const int i = i0 + lane < A ? i0 + lane : acap;
-      const uint32_t kk = act[i] >> 15, ga = actg[i];
-      v = i < acap ? __umulhi(kk, kp_inv) : (uint32_t)n;
-      c = kk - v * kp;
+      const uint32_t e = act[i], ga = actg[i] & 0xffu;
+      v = i < acap ? e >> 17 : (uint32_t)n;
+      c = (e >> 9) & 0xffu;
       x = cg[v];
       return pair_delta(x, ga);
     };
@@ -455,8 +460,8 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
         const int got = (int)rfl(*mailn), cnt = min(got, min(kW8Mail, acap - A));
         spill |= cnt < got;
         if (lane < cnt) {
-          act[A + lane] = mail[lane] << 15;
-          actg[A + lane] = (uint8_t)(ESC | kW8Free);
+          act[A + lane] = mail[lane] << 9;
+          actg[A + lane] = (uint16_t)(ESC | kW8Free);
         }
         lanes_joined();
         A += cnt;
@@ -634,9 +639,19 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
         grew |= ec == ESC - 1u ? 1u << r : 0u;
         mi[r] = __ballot(ins[r]);
       }
+      if constexpr (NW > 1) {
+        int more = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) more += __popcll(mi[r]);
+        if (len + more > lcap) {  // this wave's list is full: nothing is appended, and the run is left to the rerun
+#pragma unroll
+          for (int r = 0; r < R; ++r) mi[r] = 0ull, ins[r] = false;
+          *full = 1u;
+        }
+      }
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        list[ins[r] ? len + (int)lane_rank(mi[r]) : n] = (uint16_t)nb[r];
+        list[ins[r] ? len + (int)lane_rank(mi[r]) : lcap] = (uint16_t)nb[r];
         len += __popcll(mi[r]);
       }
       if (BITS == 4 && __ballot(grew != 0u)) {  // gamma[u][c*] no longer fits
@@ -646,7 +661,7 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
           if ((grew >> r) & 1u) {
             const uint32_t p = atomicAdd(mailn, 1u);
             if (p < (uint32_t)kW8Mail)
-              mail[p] = nb[r] * kp + cs;
+              mail[p] = (nb[r] << 8) | cs;
             else
               *full = 1u;
           }
@@ -717,17 +732,17 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
         for (int i0 = 0; i0 < A; i0 += kWave) {
           const bool alive = i0 + lane < A;
           const int i = alive ? i0 + lane : acap;
-          const uint32_t e = act[i], v = alive ? __umulhi(e >> 15, kp_inv) : (uint32_t)n;
-          const uint32_t c = alive ? (e >> 15) - v * kp : kNoColour;
-          uint32_t ga = actg[i];
+          const uint32_t e = act[i], eg = actg[i], v = alive ? e >> 17 : (uint32_t)n;
+          const uint32_t c = alive ? (e >> 9) & 0xffu : kNoColour;
+          uint32_t ga = eg & 0xffu;
           const uint32_t ad = dstar != kW8None ? adj_word(v) >> (v & 31u) : 0u;
           bool gone;
-          walk(v, c, e & kW8ExpMask, ga, (ad & 1u) != 0u, gone);
+          walk(v, c, (e & 0x1ffu) | ((eg >> 8) << 9), ga, (ad & 1u) != 0u, gone);
           const bool keep = alive && !gone;
           const uint64_t mk = __ballot(keep);
           const int p = keep ? base + (int)lane_rank(mk) : acap;
           act[p] = e;
-          actg[p] = (uint8_t)ga;
+          actg[p] = (uint16_t)((eg & 0xff00u) | ga);
           base += __popcll(mk);
         }
         A = base;
@@ -771,8 +786,8 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
           }
         if (!put) {
           if (l0 && A < acap) {
-            act[A] = ((vs * kp + old) << 15) | (expiry & kW8ExpMask);
-            actg[A] = (uint8_t)gl;
+            act[A] = (vs << 17) | (old << 9) | (expiry & 0x1ffu);
+            actg[A] = (uint16_t)((((expiry & kW8ExpMask) >> 9) << 8) | gl);
           }
           lanes_joined();
           spill |= A >= acap;

@@ -185,6 +185,27 @@ static double w8_escapes(const dlm_graph* g, int k) {
   return total;
 }
 
+constexpr double kW4Escapes = 192.0;  // above it entries are 8 bits
+
+// Side-list entries a random start needs: it has f = m / k, and while f falls
+// from there the live tabu pairs peak at little more than half the first tenure.
+static int64_t w8_side(const dlm_graph* g, const dlm_tabu_params* p, double esc) {
+  const int64_t f0 = g->nnz / 2 / p->k;
+  int64_t want = 6 * p->ten_num * f0 / (10 * (int64_t)p->ten_den) + p->ten_rand + 32;
+  if (esc <= kW4Escapes) want += (int64_t)(2.0 * esc) + 32;
+  return std::min<int64_t>(16384, (want + 63) & ~63ll);
+}
+
+// Tables of more than 2^17 bytes fit the LDS with 4-bit entries only: the
+// automatic table takes the wave tier there too when few entries escape
+// (G(1000, 0.9) with k = 220: 112 KB; its byte table would be in device memory).
+static bool w8_large(const dlm_graph* g, const dlm_tabu_params* p) {
+  if (!g->ell || w8_bucket(p->k, 4) == 0) return false;
+  const double esc = w8_escapes(g, p->k);
+  return esc <= kW4Escapes &&
+         (int64_t)w8_layout(g->n, p->k, 4, 1, (int)w8_side(g, p, esc)).bytes <= (int64_t)device_lds_limit();
+}
+
 // Entry width, waves per individual and side-list entries of a call.
 //
 // 4-bit entries hold twice the individuals per CU, so they are taken where few
@@ -199,17 +220,9 @@ static double w8_escapes(const dlm_graph* g, int k) {
 static void w8_shape(const dlm_graph* g, const dlm_tabu_params* p, int pop, TabuPlan& P) {
   const int n = g->n, k = p->k;
   const int64_t lds_max = device_lds_limit(), lds_cu = device_lds_per_cu(), cus = device_cu_count();
-  // tabu pairs to hold: a random start has f = m / k, and while f falls from
-  // there the live pairs peak at little more than half the first tenure
-  const int64_t f0 = g->nnz / 2 / k;
-  int64_t want = 6 * p->ten_num * f0 / (10 * (int64_t)p->ten_den) + p->ten_rand + 32;
-  P.bits = 8;
   const double esc = w8_escapes(g, k);
-  if (esc <= 192.0 && (uint64_t)n * 8u * (uint64_t)w8_row_dwords(k, 4) <= (1ull << 17)) {
-    P.bits = 4;
-    want += (int64_t)(2.0 * esc) + 32;
-  }
-  want = std::min<int64_t>(16384, (want + 63) & ~63ll);
+  P.bits = esc <= kW4Escapes ? 4 : 8;
+  const int64_t want = w8_side(g, p, esc);
   // individuals a CU holds with w waves each (0: not one)
   auto resident = [&](int w) -> int64_t {
     if ((int64_t)w8_layout(n, k, P.bits, w, kWave).bytes > lds_max) return 0;
@@ -221,7 +234,7 @@ static void w8_shape(const dlm_graph* g, const dlm_tabu_params* p, int pop, Tabu
   // as many individuals per CU as the table allows; the rest of their
   // share of the CU's LDS holds side-list entries
   const int64_t budget = std::min<int64_t>(lds_max, lds_cu / std::max<int64_t>(1, resident(nw))) & ~15ll;
-  P.acap = (int32_t)std::min<int64_t>(16384, ((budget - (int64_t)w8_layout(n, k, P.bits, nw, 0).bytes) / 5) & ~63ll);
+  P.acap = (int32_t)std::min<int64_t>(16384, ((budget - (int64_t)w8_layout(n, k, P.bits, nw, 0).bytes) / 6) & ~63ll);
   P.block = nw * kWave;
   P.lds = w8_layout(n, k, P.bits, nw, P.acap).bytes;
 }
@@ -251,16 +264,17 @@ static int tabu_plan(const char* fn, const dlm_graph* g, const dlm_tabu_params* 
   // automatic table with an automatic (or 64-thread) block: the wave table
   // whenever it holds the individual (it beat the block kernels at every
   // measured shape, one individual per CU included)
-  const bool wave_auto = p->table == DLM_TABLE_AUTO && (p->block == 0 || p->block == 64) && w8_bucket(k, 8) != 0 &&
-                         (uint64_t)n * (uint64_t)tab_stride(k) <= (1ull << 17) &&
+  const bool wave_fits = w8_bucket(k, 8) != 0 && (uint64_t)n * (uint64_t)tab_stride(k) <= (1ull << 17) &&
                          w8_least_bytes(n, k) <= (uint64_t)lds_max;
+  const bool wave_auto =
+      p->table == DLM_TABLE_AUTO && (p->block == 0 || p->block == 64) && (wave_fits || w8_large(g, p));
   if (p->table == DLM_TABLE_WAVE8 || wave_auto) {
     if (p->block != 0 && p->block != 64)
       return set_error(DLM_E_INVAL, "%s: the wave table runs 64 threads per individual (block=%d)", fn, p->block);
     const uint64_t kp = (uint64_t)tab_stride(k);
-    if (w8_bucket(k, 8) == 0 || (uint64_t)n * kp > (1ull << 17))
+    if (!wave_auto && (w8_bucket(k, 8) == 0 || (uint64_t)n * kp > (1ull << 17)))
       return set_error(DLM_E_UNSUPPORTED, "%s: n=%d, k=%d outside the wave table (k <= 256, n*kp <= 2^17)", fn, n, k);
-    if (w8_least_bytes(n, k) > (uint64_t)lds_max)
+    if (!wave_auto && w8_least_bytes(n, k) > (uint64_t)lds_max)
       return set_error(DLM_E_UNSUPPORTED, "%s: %llu bytes of LDS needed, %lld available", fn,
                        (unsigned long long)w8_least_bytes(n, k), (long long)lds_max);
     w8_shape(g, p, pop, P);

@@ -264,7 +264,8 @@ WIDTHS = [  # (n, p, k, T, pop, sampled rows): entry width, waves per individual
     (400, 0.97, 256, 400, 3, None),          # 4 bits, 32 dwords, every 8-bit colour in use
     (1100, 0.6, 110, 300, 2, None),          # 4 bits, the 16-dword bucket, rows past 512 neighbours
     (1000, 0.95, 100, 400, 2, None),         # 8 bits, four waves, 25 dwords
-    (520, 0.95, 250, 300, 3, None),          # 8 bits, 63 dwords: 4-bit rows would pass 2^17 entries
+    (520, 0.95, 250, 300, 3, None),          # 4 bits, 32 dwords
+    (990, 0.99, 130, 200, 2, None),          # 8 bits, 33 dwords in the bucket of 64
     (300, 0.3, 14, 200, 6000, (0, 2999, 5999)),   # one wave above 256 vertices: the CU is full of individuals
     (600, 0.1, 12, 150, 2000, (0, 777, 1999)),    # two waves above 512 vertices
 ]
@@ -309,3 +310,21 @@ def test_wave_reruns_when_the_side_list_overflows(dlm, dev):
     say("wave8 side-list overflow n=120 k=12")
     gpu = gpu_run(dlm, g, starts, k, T, 3)
     compare({x: gpu[x][at] for x in ("f_best", "iters", "stats", "hash", "colors")}, ref, at, "side list")
+
+
+def test_wave_table_beyond_two_to_the_seventeen(dlm, dev):
+    """G(800, 0.9), k = 185: 148,800 entries, in 4 bits; the automatic table
+    takes the wave tier, an explicit wave8 stays refused."""
+    n, k, T, pop = 800, 185, 250, 2
+    g = gnp(n, 0.9, seed=8)
+    starts = oracle.init_random(n, k, pop, seed=2)
+    ref = oracle.tabucol_batch(g, starts, np.arange(pop), k, T, seed=4)
+    say("auto table n=800 k=185")
+    G = dlm.Graph.from_csr(g)
+    with pytest.raises(dlm.DlmError):
+        dlm.tabu_batch(G, torch.from_numpy(starts).cuda(), k, T, 4, table="wave8")
+    r = dlm.tabu_batch(G, torch.from_numpy(starts).cuda(), k, T, 4)
+    torch.cuda.synchronize()
+    gpu = {x: v.cpu().numpy() for x, v in r.items() if isinstance(v, torch.Tensor)}
+    gpu["hash"] = gpu["hash"].view(np.uint64)
+    compare(gpu, ref, range(pop), "large table")
