@@ -167,16 +167,15 @@ __device__ __forceinline__ int w8_compact_list(uint16_t* cg, uint16_t* list, int
 }
 
 // One individual (row li of a.colors) searched by the NW waves of the calling
-// workgroup.  RW: dwords read per row (exact up to 12, else the bucket of
-// w8_bucket); acap: side-list entries the LDS holds.
-template <int BITS, int NW, int RW>
-__device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, int acap, unsigned char* smem) {
+// workgroup.  RW: dwords read per row, of which the first RLO lie in every row
+// the kernel serves; acap: side-list entries the LDS holds; late(): the
+// argument block again, read where its fields are needed late and rarely.
+template <int BITS, int NW, int RW, int RLO, class Late>
+__device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, int acap, unsigned char* smem, Late late) {
   constexpr int BLOCK = NW * kWave;
   constexpr uint32_t PER = 32u / BITS, ESC = (1u << BITS) - 1u;  // entries per dword, the escaped entry
   constexpr uint32_t ONES = BITS == 4 ? 0x11111111u : 0x01010101u;
   constexpr uint32_t LOW = ONES * (ESC >> 1), TOP = ~LOW;  // the lower bits and the top bit of every entry
-  // dwords q < RLO of a row always lie in it
-  constexpr int RLO = RW <= 12 ? RW : RW == 16 ? 12 : RW == 24 ? 16 : RW == 32 ? 24 : 32;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wid = NW == 1 ? 0 : (int)rfl((uint32_t)tid / kWave);
   const bool tail_wave = wid == NW - 1;  // keeps v*'s state and the side list
@@ -218,7 +217,7 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
   // Written by every lane: a lane-masked store here would meet the search
   // loop's end in one block, and the compiler would then keep the loop's
   // uniform values (f, t, the lists' lengths) in vector registers.
-  auto give_up = [&]() { late_args<TabuArgs>()->iters[li] = -2; };
+  auto give_up = [&]() { late()->iters[li] = -2; };
 
   // 1. start colouring (rejected whole if a colour is outside [0, k)), class sizes
   int bad = 0;
@@ -811,7 +810,7 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
     if (wid == 0) {
       const uint32_t vrec = dstar != kW8None ? vs : 0xffffu;
       if (t <= trace_cap) {  // every lane writes the same record
-        int32_t* tr = late_args<TabuArgs>()->trace + ((size_t)li * trace_cap + (t - 1)) * 2;
+        int32_t* tr = late()->trace + ((size_t)li * trace_cap + (t - 1)) * 2;
         tr[0] = (int32_t)(vrec | (cs << 16));
         tr[1] = fnew;
       }
@@ -856,7 +855,7 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
     }
   }
   if (tid == 0) {
-    const TabuArgs* o = late_args<TabuArgs>();
+    const TabuArgs* o = late();
     o->f_best[li] = f_best;
     o->iters[li] = t;
     if (o->stats) {

@@ -10,7 +10,9 @@ namespace dlm {
 template <int BITS, int NW, int RW>
 __global__ __launch_bounds__(64 * NW) void tabucol_w8_kernel(TabuArgs a, int32_t acap) {
   extern __shared__ __align__(16) unsigned char smem[];
-  tabu_w8_individual<BITS, NW, RW>(a, blockIdx.x, acap, smem);
+  // dwords of a row that lie in it for every k of the bucket
+  constexpr int RLO = RW <= 12 ? RW : RW == 16 ? 12 : RW == 24 ? 16 : RW == 32 ? 24 : 32;
+  tabu_w8_individual<BITS, NW, RW, RLO>(a, blockIdx.x, acap, smem, [] { return late_args<TabuArgs>(); });
 }
 
 template <int BITS, int NW, int RW>

@@ -14,4 +14,28 @@ int launch_w8_1(const TabuArgs& a, int pop, int acap, size_t lds, hipStream_t s)
 int launch_w8_2(const TabuArgs& a, int pop, int acap, size_t lds, hipStream_t s);
 int launch_w8_4(const TabuArgs& a, int pop, int acap, size_t lds, hipStream_t s);
 
+// One graph's share of an uneven batch on the WAVE8 search: items
+// [first_item, first_item + pop) of the batch are its individuals.
+struct WaveDesc {
+  TabuArgs a;
+  int16_t* start;  // pop * n: the start colourings, for a rerun
+  int32_t first_item, pop, acap, instance;
+};
+
+// items [base, base + items) of descs[0 .. ndesc)
+int launch_multi_w8_1(const WaveDesc* descs, int ndesc, int base, int items, size_t lds, hipStream_t s);
+int launch_multi_w8_2(const WaveDesc* descs, int ndesc, int base, int items, size_t lds, hipStream_t s);
+int launch_multi_w8_4(const WaveDesc* descs, int ndesc, int base, int items, size_t lds, hipStream_t s);
+
+// How a graph's individuals are searched: entry width, waves per individual
+// and the side-list entries a random start needs.
+struct W8Pick {
+  int bits, waves;
+  int64_t side;
+};
+
+// whether the automatic table is the wave table
+bool w8_auto(const dlm_graph* g, const dlm_tabu_params* p);
+W8Pick w8_pick(const dlm_graph* g, const dlm_tabu_params* p, int64_t pop);
+
 }  // namespace dlm

@@ -206,37 +206,78 @@ static bool w8_large(const dlm_graph* g, const dlm_tabu_params* p) {
          (int64_t)w8_layout(g->n, p->k, 4, 1, (int)w8_side(g, p, esc)).bytes <= (int64_t)device_lds_limit();
 }
 
-// Entry width, waves per individual and side-list entries of a call.
+// The automatic table is the wave table whenever it holds the individual (it
+// beat the block kernels at every measured shape, one individual per CU
+// included).
+bool w8_auto(const dlm_graph* g, const dlm_tabu_params* p) {
+  const int n = g->n, k = p->k;
+  const bool fits = w8_bucket(k, 8) != 0 && (uint64_t)n * (uint64_t)tab_stride(k) <= (1ull << 17) &&
+                    w8_least_bytes(n, k) <= (uint64_t)device_lds_limit();
+  return fits || w8_large(g, p);
+}
+
+// A CU hands out its LDS in granules: workgroups of 53,760 bytes fit three to
+// a CU, workgroups of 53,776 two (timed with a kernel of fixed length; the
+// occupancy query of the runtime does not know the granule).
+constexpr int64_t kLdsGranule = 1280;
+
+// individuals a CU holds with w waves each (0: not one), of those pop leaves it
+static int64_t w8_resident(const dlm_graph* g, int k, int64_t pop, int bits, int64_t side, int w) {
+  const int64_t lds_max = device_lds_limit(), granules = device_lds_per_cu() / kLdsGranule, cus = device_cu_count();
+  if ((int64_t)w8_layout(g->n, k, bits, w, kWave).bytes > lds_max) return 0;
+  const int64_t need = ((int64_t)w8_layout(g->n, k, bits, w, (int)side).bytes + kLdsGranule - 1) / kLdsGranule;
+  return std::max<int64_t>(1, std::min<int64_t>({granules / need, 32 / w, (pop + cus - 1) / cus}));
+}
+
+// Entry width and waves per individual of a call.
 //
 // 4-bit entries hold twice the individuals per CU, so they are taken where few
 // entries escape by size: each costs the side list's walk a lane, and its
-// registers hold 128.  Waves: the chain of one iteration is shortened most by
-// a second wave (G(500, 0.5), k = 49, 64 individuals: 16.7 -> 15.1 ms), but
-// where the LDS limits the individuals per CU its lists cost residents, and
-// short rows leave it nothing to do (n = 100: 10.3 -> 10.9 ms).  So: one wave
-// below 256 vertices or where more waves would hold fewer individuals, four
-// where at most two individuals fit a CU (G(1000, 0.5), k = 85, 2,048
-// individuals: 170, 121 and 100 ms with one, two and four), else two.
+// registers hold 128.
+//
+// Waves: more of them shorten the chain of one iteration, the more so the
+// longer the rows, but individuals that share a CU hide one another's latency
+// as well, and the lists of more waves take LDS.  1,500 iterations with one,
+// two and four waves, in ms:
+//   one individual per CU    G(160, 0.5) 3.50 3.39 3.56   G(250, 0.5) 4.62 4.13 3.78
+//   two                      G(200, 0.5) 3.90 3.69 4.18   G(400, 0.5) 6.53 5.69 5.14
+//   four                     G(320, 0.5) 5.65 5.41 5.77   G(700, 0.15) 12.2 9.55 9.08
+//   eight                    G(250, 0.5) 6.49 6.97 11.0   G(400, 0.5) 9.00 7.99 12.1
+// So the more individuals a CU holds, the later the second and the fourth wave
+// come (the fourth by long rows as well: G(200, 0.8), one per CU, 4.14 3.92
+// 3.73; G(520, 0.8), four, 14.8 11.6 10.3).  Where the LDS of their lists costs residents they still pay as long
+// as the population passes through the CUs in about as many turns (G(700, 0.5),
+// 2,048 individuals, five, four and four resident: 34.2 26.1 25.1).
+W8Pick w8_pick(const dlm_graph* g, const dlm_tabu_params* p, int64_t pop) {
+  const int n = g->n, k = p->k;
+  W8Pick r;
+  const double esc = w8_escapes(g, k);
+  r.bits = esc <= kW4Escapes ? 4 : 8;
+  r.side = w8_side(g, p, esc);
+  const int64_t cus = device_cu_count(), share = (std::max<int64_t>(pop, 1) + cus - 1) / cus;
+  auto resident = [&](int w) { return w8_resident(g, k, pop, r.bits, r.side, w); };
+  auto turns = [&](int64_t held) { return (share + held - 1) / held; };
+  const int64_t t1 = turns(std::max<int64_t>(1, resident(1))), r2 = resident(2), r4 = resident(4);
+  const int64_t deg = g->nnz / std::max(n, 1);
+  r.waves = 1;
+  if (r4 > 0 && (r4 == 1 ? n >= 240 || deg >= 110 : r4 == 2 ? n >= 400 : r4 <= 4 && (n >= 640 || deg >= 400)) && 4 * turns(r4) <= 5 * t1)
+    r.waves = 4;
+  else if (r2 > 0 && n >= (r2 == 1 ? 160 : r2 == 2 ? 200 : 256) && 9 * turns(r2) <= 10 * t1)
+    r.waves = 2;
+  return r;
+}
+
+// ... and its LDS: as many individuals per CU as the table allows; the rest
+// of their share of the CU's LDS holds side-list entries.
 static void w8_shape(const dlm_graph* g, const dlm_tabu_params* p, int pop, TabuPlan& P) {
   const int n = g->n, k = p->k;
-  const int64_t lds_max = device_lds_limit(), lds_cu = device_lds_per_cu(), cus = device_cu_count();
-  const double esc = w8_escapes(g, k);
-  P.bits = esc <= kW4Escapes ? 4 : 8;
-  const int64_t want = w8_side(g, p, esc);
-  // individuals a CU holds with w waves each (0: not one)
-  auto resident = [&](int w) -> int64_t {
-    if ((int64_t)w8_layout(n, k, P.bits, w, kWave).bytes > lds_max) return 0;
-    const int64_t fit = lds_cu / (int64_t)w8_layout(n, k, P.bits, w, (int)want).bytes;
-    return std::max<int64_t>(1, std::min<int64_t>({fit, 32 / w, ((int64_t)pop + cus - 1) / cus}));
-  };
-  int nw = 1;
-  if (n >= 256 && resident(2) >= resident(1)) nw = resident(4) >= resident(1) && resident(1) <= 2 && n > 512 ? 4 : 2;
-  // as many individuals per CU as the table allows; the rest of their
-  // share of the CU's LDS holds side-list entries
-  const int64_t budget = std::min<int64_t>(lds_max, lds_cu / std::max<int64_t>(1, resident(nw))) & ~15ll;
-  P.acap = (int32_t)std::min<int64_t>(16384, ((budget - (int64_t)w8_layout(n, k, P.bits, nw, 0).bytes) / 6) & ~63ll);
-  P.block = nw * kWave;
-  P.lds = w8_layout(n, k, P.bits, nw, P.acap).bytes;
+  const W8Pick w = w8_pick(g, p, pop);
+  const int64_t per_cu = std::max<int64_t>(1, w8_resident(g, k, pop, w.bits, w.side, w.waves));
+  const int64_t budget = std::min<int64_t>(device_lds_limit(), device_lds_per_cu() / kLdsGranule / per_cu * kLdsGranule);
+  P.bits = w.bits;
+  P.acap = (int32_t)std::min<int64_t>(16384, ((budget - (int64_t)w8_layout(n, k, w.bits, w.waves, 0).bytes) / 6) & ~63ll);
+  P.block = w.waves * kWave;
+  P.lds = w8_layout(n, k, w.bits, w.waves, P.acap).bytes;
 }
 
 static uint64_t align256(uint64_t x) { return (x + 255u) & ~255ull; }
@@ -261,13 +302,7 @@ static int tabu_check(const char* fn, const dlm_graph* g, const dlm_tabu_params*
 static int tabu_plan(const char* fn, const dlm_graph* g, const dlm_tabu_params* p, int32_t pop, TabuPlan& P) {
   const int n = g->n, k = p->k;
   const int64_t lds_max = device_lds_limit();
-  // automatic table with an automatic (or 64-thread) block: the wave table
-  // whenever it holds the individual (it beat the block kernels at every
-  // measured shape, one individual per CU included)
-  const bool wave_fits = w8_bucket(k, 8) != 0 && (uint64_t)n * (uint64_t)tab_stride(k) <= (1ull << 17) &&
-                         w8_least_bytes(n, k) <= (uint64_t)lds_max;
-  const bool wave_auto =
-      p->table == DLM_TABLE_AUTO && (p->block == 0 || p->block == 64) && (wave_fits || w8_large(g, p));
+  const bool wave_auto = p->table == DLM_TABLE_AUTO && (p->block == 0 || p->block == 64) && w8_auto(g, p);
   if (p->table == DLM_TABLE_WAVE8 || wave_auto) {
     if (p->block != 0 && p->block != 64)
       return set_error(DLM_E_INVAL, "%s: the wave table runs 64 threads per individual (block=%d)", fn, p->block);
@@ -285,6 +320,12 @@ static int tabu_plan(const char* fn, const dlm_graph* g, const dlm_tabu_params* 
       P.slots = std::max<int64_t>(1, std::min<int64_t>(slots, (int64_t)((1ull << 30) / std::max<uint64_t>(P.slot_bytes, 1))));
       P.lds_rr = tabu_layout(n, k, 256 / kWave, TabGlobal16::kLdsBytes).bytes;
       P.start_bytes = sizeof(int16_t) * (uint64_t)pop * (uint64_t)n;
+      // beyond 2^17 entries never more than the device-memory tables of the whole population
+      if ((uint64_t)n * kp > (1ull << 17)) {
+        const uint64_t whole = P.slot_bytes * (uint64_t)pop, start = align256(P.start_bytes) + 255u;
+        const int64_t left = whole > start ? (int64_t)((whole - start) / P.slot_bytes) : 0;
+        P.slots = std::max<int64_t>(1, std::min(P.slots, left));
+      }
     }
     P.ws_bytes = align256(P.start_bytes) + align256(P.slot_bytes * (uint64_t)P.slots);
     return DLM_OK;

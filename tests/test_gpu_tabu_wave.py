@@ -259,7 +259,9 @@ def test_wave_static_entry_point(dlm, dev):
 
 WIDTHS = [  # (n, p, k, T, pop, sampled rows): entry width, waves per individual, row dwords
     (100, 0.5, 9, 2000, 4, None),            # 4 bits, one wave
-    (300, 0.5, 22, 2000, 5, None),           # 4 bits, two waves, entries that outgrow 4 bits
+    (300, 0.5, 22, 2000, 5, None),           # 4 bits, four waves, entries that outgrow 4 bits
+    (180, 0.5, 18, 2000, 4, None),           # 4 bits, two waves
+    (220, 0.5, 22, 300, 700, (0, 255, 699)),      # three individuals per CU, one wave each
     (600, 0.5, 44, 1500, 3, None),           # the same with four waves and more escapes than a register bank
     (400, 0.97, 256, 400, 3, None),          # 4 bits, 32 dwords, every 8-bit colour in use
     (1100, 0.6, 110, 300, 2, None),          # 4 bits, the 16-dword bucket, rows past 512 neighbours
@@ -328,3 +330,12 @@ def test_wave_table_beyond_two_to_the_seventeen(dlm, dev):
     gpu = {x: v.cpu().numpy() for x, v in r.items() if isinstance(v, torch.Tensor)}
     gpu["hash"] = gpu["hash"].view(np.uint64)
     compare(gpu, ref, range(pop), "large table")
+
+
+@pytest.mark.parametrize("pop", [2, 3, 300, 600, 2000])
+def test_wave_table_beyond_two_to_the_seventeen_asks_for_no_more_workspace(dlm, dev, pop):
+    """Tables of that size went to device memory before: the start colourings
+    and rerun slots of the wave table must not need more than that did."""
+    n, k = 1000, 223
+    G = dlm.Graph.from_csr(gnp(n, 0.9, seed=4))
+    assert dlm.tabu_workspace_bytes(G, pop, k, 100) <= dlm.tabu_workspace_bytes(G, pop, k, 100, table="global16")
