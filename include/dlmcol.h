@@ -247,7 +247,8 @@ typedef struct dlm_multi_item {
 } dlm_multi_item;
 
 typedef struct dlm_multi_config {
-  int32_t block;       /* threads per workgroup: 0 = 256, else 64, 128, 256 or 512 */
+  int32_t block;       /* threads per workgroup of the graphs that the wave table does not hold
+                          within the budget: 0 = 256, else 64, 128, 256 or 512 */
   int32_t lds_budget;  /* LDS bytes a graph's table may use (0 = device maximum) */
 } dlm_multi_config;
 
@@ -256,8 +257,8 @@ typedef struct dlm_multi_plan dlm_multi_plan;
 int dlm_multi_plan_create(const dlm_multi_item* items, int32_t count, const dlm_multi_config* cfg,
                           void* stream, dlm_multi_plan** out);
 int dlm_multi_plan_launch(dlm_multi_plan* plan, void* stream);
-/* grid size, dynamic LDS bytes, graphs using device memory for (part of)
- * their table, items */
+/* workgroups, largest dynamic LDS bytes, graphs whose 16-bit table exceeds the
+ * LDS budget, items */
 int dlm_multi_plan_info(const dlm_multi_plan* plan, int32_t* grid, int32_t* lds_bytes,
                         int32_t* n_global, int32_t* total_items);
 int dlm_multi_plan_destroy(dlm_multi_plan* plan);

@@ -1,9 +1,17 @@
 // Uneven batches: populations of many graphs (different n, k, budgets) in one
-// persistent launch, captured once into a hipGraph and replayed.
+// hipGraph, captured once and replayed.
 //
 // Work items are (graph, individual) pairs ordered longest-first (graphs by
-// n * k * iterations, descending).  The grid holds as many workgroups as the
-// device keeps resident at the launch's LDS size; each workgroup pops items
+// n * k * iterations, descending).  Graphs that the wave table holds within
+// the launch's LDS budget run the WAVE8 search, one workgroup per item, with
+// one, two or four waves each; the launches of the three are branches of the
+// graph beside the block search of the others, and one more node reruns what
+// the wave table gave up on.  A batch lasts as long as its longest chain: 12
+// graphs of 100 to 1,000 vertices with 64 individuals each (the longest: 854
+// vertices, k = 174) took 170 ms on the block search alone.
+//
+// The others share one persistent launch: as many workgroups as the device
+// keeps resident at its LDS size; each workgroup pops items
 // from an atomic counter until the queue is empty, so every workgroup exits.
 // A graph whose table fits the launch's LDS budget runs the LDS16 table, one
 // whose byte gamma alone fits runs the SPLIT8 table (expiries in device
@@ -19,7 +27,9 @@
 #include <numeric>
 #include <vector>
 
-#include "tabu_body.h"
+#include "tabu_wave.h"
+#include "tabu_wave_launch.h"
+#include "tabu_wave_multi.h"
 
 namespace dlm {
 
@@ -77,17 +87,49 @@ __global__ __launch_bounds__(BLOCK) void tabu_multi_kernel(const MultiDesc* __re
   }
 }
 
+// What the wave table gave up on (iters = -2), from its saved start with the
+// packed 16-bit table in device memory, one slot per workgroup.
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void tabu_multi_rerun_kernel(const WaveDesc* __restrict__ descs, int32_t ndesc,
+                                                                 int32_t total, unsigned char* __restrict__ slots,
+                                                                 int64_t slot_bytes) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  unsigned char* gtab = slots + (size_t)blockIdx.x * (size_t)slot_bytes;
+  int g = 0;
+  for (int32_t item = blockIdx.x; item < total; item += gridDim.x) {
+    while (g + 1 < ndesc && descs[g + 1].first_item <= item) ++g;
+    const WaveDesc& d = descs[g];
+    const int li = item - d.first_item;
+    if (d.a.iters[li] != -2) continue;
+    const size_t row = (size_t)li * (size_t)d.a.n;
+    for (int v = threadIdx.x; v < d.a.n; v += BLOCK) d.a.colors[row + v] = d.start[row + v];
+    __syncthreads();
+    tabu_individual<BLOCK, TabGlobal16>(d.a, li, gtab, smem);
+    __syncthreads();
+  }
+}
+
 }  // namespace dlm
 
 using namespace dlm;
 
 struct dlm_multi_plan {
-  int32_t block = 256, lds_budget = 0, grid = 0, total = 0, ndesc = 0, n_global = 0;
-  size_t lds = 0;
+  int32_t block = 256, lds_budget = 0, grid = 0, total = 0, block_items = 0, ndesc = 0, n_global = 0;
+  size_t lds = 0, info_lds = 0;
   int64_t slot_words = 0;
   MultiDesc* d_descs = nullptr;
   uint32_t* d_queue = nullptr;
   uint32_t* d_slots = nullptr;
+  // the wave table's share: its descriptors by number of waves, descending
+  int32_t wdesc[4] = {0, 0, 0, 0};  // descriptors before class i (4, 2, 1 waves; the end)
+  int32_t witem[4] = {0, 0, 0, 0};  // items before class i
+  size_t wlds[3] = {0, 0, 0};
+  int32_t rr_grid = 0;
+  size_t rr_lds = 0;
+  int64_t rr_slot_bytes = 0;
+  WaveDesc* d_wdescs = nullptr;
+  int16_t* d_start = nullptr;
+  unsigned char* d_rr_slots = nullptr;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
 };
@@ -125,7 +167,7 @@ int launch_persistent(const dlm_multi_plan* p, hipStream_t s) {
 #define DLM_CASE(B)                                                                                       \
   case B:                                                                                                 \
     hipLaunchKernelGGL(tabu_multi_kernel<B>, dim3(p->grid), dim3(B), p->lds, s, p->d_descs, p->ndesc,     \
-                       p->total, p->d_queue, p->d_slots, p->slot_words);                                  \
+                       p->block_items, p->d_queue, p->d_slots, p->slot_words);                                  \
     break;
     DLM_CASE(64)
     DLM_CASE(128)
@@ -146,7 +188,103 @@ void free_plan(dlm_multi_plan* p) {
   (void)hipFree(p->d_descs);
   (void)hipFree(p->d_queue);
   (void)hipFree(p->d_slots);
+  (void)hipFree(p->d_wdescs);
+  (void)hipFree(p->d_start);
+  (void)hipFree(p->d_rr_slots);
   delete p;
+}
+
+constexpr int kRerunBlock = 256;
+constexpr uint64_t kRerunSlotBytes = 256ull << 20;  // of all rerun slots together
+
+// One graph of the batch on the wave table.
+struct WaveItem {
+  int oi;  // index into items
+  W8Pick pick;
+  int instance;
+  int64_t least;  // LDS with the side list a random start needs
+};
+
+dlm_tabu_params item_params(const dlm_multi_item& it) {
+  dlm_tabu_params q{};
+  q.k = it.k;
+  q.max_iters = it.max_iters;
+  q.ten_num = it.ten_num;
+  q.ten_den = it.ten_den;
+  q.ten_rand = it.ten_rand;
+  q.ind_base = it.ind_base;
+  q.seed = it.seed;
+  return q;
+}
+
+// Whether a graph of the batch runs the wave table, and how.  Classes of more
+// than half the limit in the mean are left to the block search: a rerun here
+// begins when everything else has ended.  pop: the individuals that the
+// number of waves is picked for.
+bool wave_item(const dlm_multi_item& it, int64_t pop, int64_t budget, WaveItem& w) {
+  const dlm_tabu_params q = item_params(it);
+  if (!it.g->ell || !w8_auto(it.g, &q) || it.g->n > (int)(kW8ClassMax / 2) * it.k) return false;
+  w.pick = w8_pick(it.g, &q, pop);
+  w.instance = w8_multi_instance(it.k, w.pick.bits);
+  w.least = (int64_t)w8_layout(it.g->n, it.k, w.pick.bits, w.pick.waves, (int)w.pick.side).bytes;
+  const int64_t rr = (int64_t)tabu_layout(it.g->n, it.k, kRerunBlock / kWave, 0).bytes;
+  return w.instance >= 0 && w.least <= budget && rr <= device_lds_limit();
+}
+
+// The wave table's graphs, longest first.  A batch that the card holds whole
+// is as long as its longest individual: each graph gets the waves it would get
+// alone.  Otherwise the individuals share the CUs and the whole batch counts.
+std::vector<WaveItem> wave_items(const dlm_multi_item* items, const std::vector<int>& order, int64_t budget) {
+  std::vector<WaveItem> r;
+  int64_t total = 0, lds = 0, waves = 0;
+  for (int oi : order) total += items[oi].pop;
+  for (int oi : order) {
+    WaveItem w{};
+    w.oi = oi;
+    if (items[oi].pop == 0 || !wave_item(items[oi], items[oi].pop, budget, w)) continue;
+    lds += items[oi].pop * w.least;
+    waves += (int64_t)items[oi].pop * w.pick.waves;
+    r.push_back(w);
+  }
+  const int64_t cus = device_cu_count();
+  if (lds * 4 > cus * device_lds_per_cu() * 3 || waves > 16 * cus) {
+    size_t kept = 0;
+    for (WaveItem& w : r)
+      if (wave_item(items[w.oi], total, budget, w)) r[kept++] = w;
+    r.resize(kept);
+  }
+  return r;
+}
+
+// The plan's nodes onto cs[3] (capturing): class c of the wave table on the
+// branch of cs[c], the persistent kernel on cs[3] itself.
+int capture_plan(const dlm_multi_plan* p, const hipStream_t* cs, const hipEvent_t* ev) {
+  hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, cs[3], p->d_queue, 1, 0u);
+  DLM_HIP(hipGetLastError());
+  DLM_HIP(hipEventRecord(ev[3], cs[3]));
+  auto items = [&](int c) { return p->witem[c + 1] - p->witem[c]; };
+  for (int c = 0; c < 3; ++c) {
+    if (items(c) == 0) continue;
+    DLM_HIP(hipStreamWaitEvent(cs[c], ev[3], 0));
+    const auto launch = c == 0 ? launch_multi_w8_4 : c == 1 ? launch_multi_w8_2 : launch_multi_w8_1;
+    const int rc = launch(p->d_wdescs + p->wdesc[c], p->wdesc[c + 1] - p->wdesc[c], p->witem[c], items(c), p->wlds[c], cs[c]);
+    if (rc != DLM_OK) return rc;
+    DLM_HIP(hipEventRecord(ev[c], cs[c]));
+  }
+  if (p->block_items > 0) {
+    const int rc = launch_persistent(p, cs[3]);
+    if (rc != DLM_OK) return rc;
+  }
+  for (int c = 0; c < 3; ++c)
+    if (items(c) > 0) DLM_HIP(hipStreamWaitEvent(cs[3], ev[c], 0));
+  if (p->rr_grid > 0) {
+    auto kern = tabu_multi_rerun_kernel<kRerunBlock>;
+    DLM_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p->rr_lds));
+    hipLaunchKernelGGL(kern, dim3(p->rr_grid), dim3(kRerunBlock), p->rr_lds, cs[3], p->d_wdescs, p->wdesc[3],
+                       p->witem[3], p->d_rr_slots, p->rr_slot_bytes);
+    DLM_HIP(hipGetLastError());
+  }
+  return DLM_OK;
 }
 
 }  // namespace
@@ -177,6 +315,9 @@ int dlm_multi_plan_create(const dlm_multi_item* items, int32_t count, const dlm_
   p->block = block;
   p->lds_budget = (int32_t)budget;
   std::vector<MultiDesc> descs;
+  const std::vector<WaveItem> wave = wave_items(items, order, budget);
+  std::vector<char> on_wave(count, 0);
+  for (const WaveItem& w : wave) on_wave[w.oi] = 1;
   int32_t first = 0;
   size_t lds = tabu_layout(1, 1, nw, 0).bytes;
   for (int oi : order) {
@@ -189,6 +330,10 @@ int dlm_multi_plan_create(const dlm_multi_item* items, int32_t count, const dlm_
                    it.ten_num, it.ten_den, it.ten_rand, it.ind_base, 0};
     const uint64_t lds16 = tabu_layout(n, it.k, nw, TabLds16::kLdsBytes).bytes;
     const uint64_t lds8 = tabu_layout(n, it.k, nw, TabSplit8::kLdsBytes).bytes;
+    if (on_wave[oi]) {
+      if ((int64_t)lds16 > budget) ++p->n_global;
+      continue;
+    }
     if ((int64_t)lds16 <= budget) {
       d.tier = 0;
       lds = std::max<size_t>(lds, lds16);
@@ -210,9 +355,50 @@ int dlm_multi_plan_create(const dlm_multi_item* items, int32_t count, const dlm_
     descs.push_back(d);
   }
   p->slot_words = (p->slot_words + 3) & ~int64_t(3);  // 16-byte aligned slots
-  p->total = first;
+  p->block_items = first;
+  // the wave table's descriptors; an LDS of the class leaves the smaller
+  // individuals of the class more side-list entries
+  std::vector<WaveDesc> wdescs;
+  std::vector<size_t> start_at;
+  size_t start_cells = 0;
+  int32_t witems = 0;
+  for (int c = 0; c < 3; ++c) {
+    const int nwv = 4 >> c;
+    p->wdesc[c] = (int32_t)wdescs.size();
+    p->witem[c] = witems;
+    for (const WaveItem& w : wave)
+      if (w.pick.waves == nwv) p->wlds[c] = std::max(p->wlds[c], (size_t)w.least);
+    for (const WaveItem& w : wave) {
+      if (w.pick.waves != nwv) continue;
+      const dlm_multi_item& it = items[w.oi];
+      const int n = it.g->n;
+      WaveDesc d{};
+      d.a = TabuArgs{it.g->row_ptr, it.g->col_idx, it.g->erow, it.colors_dev, it.f_best_dev, it.iters_dev,
+                     it.stats_dev, it.hash_dev, nullptr, nullptr, make_key(it.seed), n, it.k, it.max_iters,
+                     it.ten_num, it.ten_den, it.ten_rand, it.ind_base, 0, it.g->ell, it.g->adj, it.g->ell_stride};
+      const int64_t room = (int64_t)p->wlds[c] - (int64_t)w8_layout(n, it.k, w.pick.bits, nwv, 0).bytes;
+      d.acap = (int32_t)std::max<int64_t>(w.pick.side, std::min<int64_t>(16384, (room / 6) & ~63ll));
+      d.instance = w.instance;
+      d.first_item = witems;
+      d.pop = it.pop;
+      witems += it.pop;
+      start_at.push_back(start_cells);
+      start_cells += (size_t)it.pop * n;
+      wdescs.push_back(d);
+      p->rr_slot_bytes = std::max<int64_t>(p->rr_slot_bytes, (int64_t)((tab_entries(n, it.k) * TabGlobal16::kGlobalBytes + 15) & ~15ull));
+      p->rr_lds = std::max(p->rr_lds, (size_t)tabu_layout(n, it.k, kRerunBlock / kWave, 0).bytes);
+    }
+    p->info_lds = std::max(p->info_lds, p->wlds[c]);
+  }
+  p->wdesc[3] = (int32_t)wdescs.size();
+  p->witem[3] = witems;
+  if (witems > 0)
+    p->rr_grid = (int32_t)std::max<int64_t>(
+        1, std::min<int64_t>({(int64_t)witems, 2 * (int64_t)device_cu_count(), (int64_t)(kRerunSlotBytes / (uint64_t)p->rr_slot_bytes)}));
+  p->total = first + witems;
   p->ndesc = (int32_t)descs.size();
   p->lds = lds;
+  if (first > 0) p->info_lds = std::max(p->info_lds, lds);
   if ((int64_t)lds > lds_max) {
     free_plan(p);
     return set_error(DLM_E_UNSUPPORTED, "dlm_multi_plan_create: %zu bytes of LDS needed", lds);
@@ -228,7 +414,7 @@ int dlm_multi_plan_create(const dlm_multi_item* items, int32_t count, const dlm_
     free_plan(p);
     return rc;
   }
-  p->grid = std::max(1, std::min(per_cu * device_cu_count(), std::max(p->total, 1)));
+  p->grid = std::max(1, std::min(per_cu * device_cu_count(), std::max(p->block_items, 1)));
   hipStream_t s = (hipStream_t)stream;
   auto fail = [&](hipError_t e, const char* what) {
     free_plan(p);
@@ -245,17 +431,39 @@ int dlm_multi_plan_create(const dlm_multi_item* items, int32_t count, const dlm_
       (e = hipMemcpy(p->d_descs, descs.data(), sizeof(MultiDesc) * descs.size(), hipMemcpyHostToDevice)) !=
           hipSuccess)
     return fail(e, "hipMemcpy");
-  // capture: queue reset (a fill kernel, no memset node) + the persistent kernel
-  hipStream_t cs;
-  if ((e = hipStreamCreateWithFlags(&cs, hipStreamNonBlocking)) != hipSuccess) return fail(e, "hipStreamCreate");
-  if ((e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal)) != hipSuccess) {
-    (void)hipStreamDestroy(cs);
+  if (!wdescs.empty()) {
+    if ((e = hipMalloc(&p->d_wdescs, sizeof(WaveDesc) * wdescs.size())) != hipSuccess) return fail(e, "hipMalloc");
+    if ((e = hipMalloc(&p->d_start, sizeof(int16_t) * start_cells)) != hipSuccess) return fail(e, "hipMalloc");
+    if ((e = hipMalloc(&p->d_rr_slots, (size_t)p->rr_slot_bytes * p->rr_grid)) != hipSuccess)
+      return fail(e, "hipMalloc");
+    for (size_t i = 0; i < wdescs.size(); ++i) wdescs[i].start = p->d_start + start_at[i];
+    if ((e = hipMemcpy(p->d_wdescs, wdescs.data(), sizeof(WaveDesc) * wdescs.size(), hipMemcpyHostToDevice)) !=
+        hipSuccess)
+      return fail(e, "hipMemcpy");
+  }
+  // capture: queue reset (a fill kernel, no memset node), the wave launches and
+  // the persistent kernel side by side, the reruns
+  hipStream_t cs[4] = {};
+  hipEvent_t ev[4] = {};
+  auto release = [&]() {
+    for (int i = 0; i < 4; ++i) {
+      if (ev[i]) (void)hipEventDestroy(ev[i]);
+      if (cs[i]) (void)hipStreamDestroy(cs[i]);
+    }
+  };
+  for (int i = 0; i < 4; ++i)
+    if ((e = hipStreamCreateWithFlags(&cs[i], hipStreamNonBlocking)) != hipSuccess ||
+        (e = hipEventCreateWithFlags(&ev[i], hipEventDisableTiming)) != hipSuccess) {
+      release();
+      return fail(e, "hipStreamCreate");
+    }
+  if ((e = hipStreamBeginCapture(cs[3], hipStreamCaptureModeThreadLocal)) != hipSuccess) {
+    release();
     return fail(e, "hipStreamBeginCapture");
   }
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, cs, p->d_queue, 1, 0u);
-  rc = p->total > 0 ? launch_persistent(p, cs) : DLM_OK;
-  e = hipStreamEndCapture(cs, &p->graph);
-  (void)hipStreamDestroy(cs);
+  rc = capture_plan(p, cs, ev);
+  e = hipStreamEndCapture(cs[3], &p->graph);
+  release();
   if (rc != DLM_OK) {
     free_plan(p);
     return rc;
@@ -277,8 +485,8 @@ int dlm_multi_plan_launch(dlm_multi_plan* p, void* stream) {
 int dlm_multi_plan_info(const dlm_multi_plan* p, int32_t* grid, int32_t* lds_bytes, int32_t* n_global,
                         int32_t* total_items) {
   if (!p) return set_error(DLM_E_INVAL, "dlm_multi_plan_info: plan is NULL");
-  if (grid) *grid = p->grid;
-  if (lds_bytes) *lds_bytes = (int32_t)p->lds;
+  if (grid) *grid = (p->block_items > 0 ? p->grid : 0) + p->witem[3];
+  if (lds_bytes) *lds_bytes = (int32_t)p->info_lds;
   if (n_global) *n_global = p->n_global;
   if (total_items) *total_items = p->total;
   return DLM_OK;

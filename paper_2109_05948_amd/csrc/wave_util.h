@@ -19,6 +19,11 @@ __device__ __forceinline__ uint32_t own_u32(uint32_t x) {
   return x;
 }
 
+__device__ __forceinline__ uint64_t own_u64(uint64_t x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
+
 // The twenty Philox4x32-10 round keys (the seed's two words bumped by the
 // Weyl constants), computed once and held in vector registers: in scalar
 // registers, the scarce file here, they would spill, and recomputing them

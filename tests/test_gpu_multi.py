@@ -120,3 +120,32 @@ def test_uneven64_full_plan_sampled(dlm, dev):
             assert (stats[i][:6] == ref["stats"][r][:6]).all(), msg
         conf, _ = dlm.evaluate(j["graph"], j["colors"], j["k"])
         assert (conf.cpu().numpy() == fb).all(), f"graph {gi}: f_best differs from the recount"
+
+
+WAVE_SPECS = [  # every entry width and number of waves, narrow to wide rows; colour 0 everywhere where start is False
+    (90, 0.5, 3, 5, 300, True), (70, 0.5, 12, 4, 400, True), (130, 0.6, 33, 3, 400, True),      # one wave
+    (200, 0.5, 50, 3, 400, True), (190, 0.9, 77, 2, 300, True), (180, 0.9, 14, 2, 300, True),   # two
+    (300, 0.9, 100, 2, 300, True), (420, 0.8, 130, 2, 250, True), (500, 0.95, 200, 2, 200, True),
+    (600, 0.95, 45, 2, 150, True), (700, 0.95, 60, 2, 120, True), (1000, 0.95, 100, 1, 100, True),   # four
+    (200, 0.5, 12, 3, 400, False), (650, 0.6, 40, 2, 200, False)]   # a class past 127: given up and rerun
+
+
+def test_multi_wave_widths_and_reruns(dlm, dev):
+    jobs, starts = make_jobs(dlm, [("gnp", n, p, k, pop, T) for n, p, k, pop, T, _ in WAVE_SPECS])
+    for j, st, spec in zip(jobs, starts, WAVE_SPECS):
+        if not spec[5]:
+            st[:] = 0
+    say("multi wave widths")
+    mb = dlm.MultiBatch(jobs)
+    refs = [oracle.tabucol_batch(j["g"], st, j["ind_base"] + np.arange(len(st)), j["k"], j["iters"], seed=j["seed"])
+            for j, st in zip(jobs, starts)]
+    for rep in range(2):
+        for j, st in zip(jobs, starts):
+            j["colors"].copy_(torch.from_numpy(st))
+        mb.launch()
+        torch.cuda.synchronize()
+        for gi, (j, ref) in enumerate(zip(jobs, refs)):
+            assert (j["f_best"].cpu().numpy() == ref["f_best"]).all(), (rep, gi)
+            assert (j["iters_out"].cpu().numpy() == ref["iters"]).all(), (rep, gi)
+            assert (j["hash"].cpu().numpy().view(np.uint64) == ref["hash"]).all(), (rep, gi)
+            assert (j["colors"].cpu().numpy() == ref["colors"]).all(), (rep, gi)
