@@ -55,7 +55,8 @@ KERNEL_SOURCES = ("paper_2109_05948_amd/csrc/tabu_body.h", "paper_2109_05948_amd
 # HBM bytes of the two distance launches of one diversity step (old x new
 # block + new x new triangle), from the same counter runs
 DIVERSITY_TRAFFIC = {"sources_sha256": "9f79de36c3bbbdb83d6884a3ccb01ff45ffbb8d43bbc23bc6ed9041fc722adea", "bytes": 1629448352}  # profiles/distance_diversity_gnp500.md
-DIVERSITY_SOURCES = ("paper_2109_05948_amd/csrc/diversity.hip", "paper_2109_05948_amd/csrc/dlm_common.h")
+DIVERSITY_SOURCES = ("paper_2109_05948_amd/csrc/diversity.hip", "paper_2109_05948_amd/csrc/wave_util.h",
+                     "paper_2109_05948_amd/csrc/dlm_common.h")
 
 
 def kernel_sources_digest(sources=None) -> str:

@@ -11,13 +11,22 @@
 // D~ is an upper bound of the exact distance (n - a maximum matching), and
 // it is exact on close partitions.
 //
-// One wave per pair: the k x k overlap counts are 16-bit halves of 32-bit
+// Many pairs (distance_lanes_kernel): a wave takes one row x and 64 rows y,
+// one per lane, and walks x's classes in order.  The overlaps of a class with
+// every y's classes are counted in the lane's own LDS counters, so nothing is
+// reduced across lanes and no k x k table is cleared or scanned: an overlap is
+// found by as many counter updates as the class has vertices.  The passes
+// over A and over B are two launches with the sides swapped.
+//
+// Few pairs (distance_kernel), one wave per pair: the k x k overlap counts are 16-bit halves of 32-bit
 // LDS words (k^2 / 2 words per wave), filled by one LDS atomic per vertex.
 // A greedy step is one LDS read per owned column (lane c owns classes c,
 // c + 64, ...) and a DPP wave maximum of (overlap << 16 | 0xffff - class);
 // the two passes run interleaved, as two independent chains.  The class
 // orders are computed once per colouring by a small kernel first.
-#include "dlm_common.h"
+#include <type_traits>
+
+#include "wave_util.h"
 
 namespace dlm {
 
@@ -208,6 +217,251 @@ __global__ __launch_bounds__(256) void distance_kernel(const int16_t* __restrict
       d = n - (int32_t)(sab > sba ? sab : sba);
     }
     if (lane == 0) out[(size_t)i * ld + j] = d;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// One pass of the distance for a row x against 64 rows y, one per lane.
+//
+// LDS: the 64 rows y transposed to bytes, T[v * 64 + lane] (one row more, of
+// colour k, for the padding); the lanes' counters; per wave, x's vertices by
+// class (each class padded to an even number), and k words for that sort.
+// A counter holds count << bits | 2^bits - 1 - d, so that the largest one is
+// the largest overlap, ties by index; the sign bit marks a class of y that is
+// taken, and the padding's colour k.  Counters are raised by returning
+// atomics, the largest raised value is the class's choice, and lowered again.
+// Counter d of lane l lies in bank l: no conflicts.  Where n << bits stays
+// below 2^15 two waves share a counter's dword, a half each: an atomic on one
+// half never carries into the other.
+//
+// Bound by the issue of each wave's instructions (about 6 per vertex), so by
+// the waves that the LDS holds: n = 500, k = 49 has 14 with halves and 8
+// without.  4096 x 4096 pairs of that shape, both passes: 42.3 ms with one
+// wave per pair, 9.4 with whole counters, 7.9 with halves.  Reading the
+// next classes' colours ahead cost more in branches than it hid (16.8 ms), as
+// did stores instead of the lowering atomics in selects (10.0 ms).
+constexpr int kLaneK = 255;                // colours are bytes, and k is one of them
+
+__host__ __device__ inline uint32_t lanes_tile_bytes(int n) { return 64u * (uint32_t)(n + 1); }
+__host__ __device__ inline uint32_t lanes_counter_bytes(int k) { return 256u * (uint32_t)(k + 1); }
+__host__ __device__ inline uint32_t lanes_sort_bytes(int n, int k) {
+  return 4u * (uint32_t)((n + k + 3) & ~3) + 4u * (uint32_t)((k + 3) & ~3);
+}
+__host__ __device__ inline uint32_t lanes_bytes(int n, int k, int waves, bool half) {
+  return lanes_tile_bytes(n) + (uint32_t)(half ? (waves + 1) / 2 : waves) * lanes_counter_bytes(k) +
+         (uint32_t)waves * lanes_sort_bytes(n, k);
+}
+
+// groups [g0, g1) of 64 rows y that have a pair with rows x of a chunk
+template <int DIR>
+__host__ __device__ inline void lanes_tri_groups(int chunk, int rows, int nx, int groups, int& g0, int& g1) {
+  const int x0 = chunk * rows, x1 = x0 + rows < nx ? x0 + rows : nx;
+  g0 = DIR == 0 ? (x0 + 1) / 64 : 0;                       // y > x0 for some y of the group
+  g1 = DIR == 0 ? groups : (x1 - 2 + 64) / 64;             // y < x1 - 1 for some
+  g1 = g1 < groups ? g1 : groups;
+  g0 = g0 < g1 ? g0 : g1;
+}
+
+// DIR 0: x a row of A, y of B, writes n - S_ab.  DIR 1: x a row of B, y of A,
+// lowers what DIR 0 wrote to n - S_ba where that is less.
+// HALF: 16-bit counters of `bits` index bits (else 32 and 8); KW: k <= 64 KW.
+template <int DIR, bool HALF, int KW>
+__global__ __launch_bounds__(1024) void distance_lanes_kernel(const int16_t* __restrict__ X,
+                                                             const int16_t* __restrict__ recX, int32_t nx,
+                                                             const int16_t* __restrict__ Y,
+                                                             const int16_t* __restrict__ recY, int32_t ny, int32_t tri,
+                                                             int32_t n, int32_t k, int32_t bits, int32_t rows,
+                                                             int32_t* __restrict__ out, int64_t ld) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave, waves = blockDim.x / kWave;
+  // The triangle needs i < j only (x = i and y = j, or the other way round):
+  // its workgroups are counted off over the chunks of rows that have any such
+  // pair with a group.  Launched over the full rectangle, its idle workgroups
+  // would fall on the same shader engines every time, and it took as long as
+  // the rectangle.
+  const int groups = (ny + 63) / 64;
+  int chunk = 0, g0 = 0, g1 = groups, left = (int)blockIdx.x;
+  if (!tri) {
+    chunk = left / groups;
+    left -= chunk * groups;
+  } else {
+    for (;; ++chunk) {
+      lanes_tri_groups<DIR>(chunk, rows, nx, groups, g0, g1);
+      if (left < g1 - g0) break;
+      left -= g1 - g0;
+    }
+  }
+  const int y0 = 64 * (g0 + left), x0 = chunk * rows, x1 = min(nx, x0 + rows);
+  uint8_t* T = smem;
+  uint32_t* T32 = reinterpret_cast<uint32_t*>(smem);
+  int32_t* cnt = reinterpret_cast<int32_t*>(smem + lanes_tile_bytes(n) +
+                                            (uint32_t)(HALF ? wid >> 1 : wid) * lanes_counter_bytes(k)) + lane;
+  uint32_t* list = reinterpret_cast<uint32_t*>(
+      smem + lanes_tile_bytes(n) + (uint32_t)(HALF ? (waves + 1) >> 1 : waves) * lanes_counter_bytes(k) +
+      (uint32_t)wid * lanes_sort_bytes(n, k));
+  uint32_t* pos = list + ((n + k + 3) & ~3);
+  const int hi = HALF ? 16 * (wid & 1) : 0;  // this wave's half begins at this bit
+  const int ib = HALF ? bits : 8;
+  const int32_t mask = (1 << ib) - 1, unit = 1 << (ib + hi), taken = (int32_t)((HALF ? 0x8000u : 0x80000000u) << hi);
+  // a counter's value as the upper (or all) bits of a word, and its store
+  auto value = [&](int32_t w) { return HALF ? (int32_t)((uint32_t)w << (16 - hi)) : w; };
+  auto set = [&](int d, int32_t x) {
+    if (HALF)
+      reinterpret_cast<uint16_t*>(cnt + d * 64)[hi >> 4] = (uint16_t)x;
+    else
+      cnt[d * 64] = x;
+  };
+  // four rows y to a dword; rows past the last repeat it, colours outside [0, k) become k - 1
+  for (int g = wid; g < 16; g += waves) {
+    const int16_t* r[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) r[q] = Y + (size_t)min(y0 + 4 * g + q, ny - 1) * n;
+    for (int v = lane; v < n; v += kWave) {
+      uint32_t w = 0u;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) w |= min((uint32_t)(uint16_t)r[q][v], (uint32_t)(k - 1)) << (8 * q);
+      T32[v * 16 + g] = w;
+    }
+  }
+  if (threadIdx.x < 64) T[64 * n + threadIdx.x] = (uint8_t)k;
+  __syncthreads();
+  const int y = y0 + lane;
+  const bool have = y < ny, ybad = recY[(size_t)min(y, ny - 1) * (k + 2) + k] < 0;
+  for (int x = x0 + wid; x < x1; x += waves) {
+    if (tri && (DIR == 0 ? y0 + 63 <= x : y0 >= x)) continue;
+    int32_t* const at = DIR == 0 ? out + (size_t)x * ld + y : out + (size_t)y * ld + x;
+    const bool write = have && (!tri || (DIR == 0 ? y > x : y < x));
+    const int16_t* rec = recX + (size_t)x * (k + 2);
+    const int nonempty = __builtin_amdgcn_readfirstlane(rec[k]);
+    if (nonempty < 0) {
+      if (DIR == 0 && write) *at = -1;
+      continue;
+    }
+    // ---- x's vertices by class, in the order of the classes
+    const int16_t* xr = X + (size_t)x * n;
+    for (int c = lane; c < k; c += kWave) pos[c] = 0u;
+    wave_sync();
+    for (int v = lane; v < n; v += kWave) atomicAdd(&pos[xr[v]], 1u);
+    wave_sync();
+    uint32_t start[KW];  // first list entry of the class of rank lane + 64 r, in twos
+    uint32_t base = 0u;
+#pragma unroll
+    for (int r = 0; r < KW; ++r) {
+      start[r] = 0u;
+      {
+        const int t = r * kWave + lane;
+        const uint32_t c = t < k ? (uint32_t)rec[t] : 0u, size = t < k ? pos[c] : 0u;
+        uint32_t sum = (size + 1u) >> 1;
+        for (int o = 1; o < kWave; o <<= 1) {
+          const uint32_t up = __shfl_up(sum, o);
+          sum += lane >= o ? up : 0u;
+        }
+        start[r] = base + sum - ((size + 1u) >> 1);
+        if (t < k) {
+          pos[c] = 2u * start[r];
+          if (size & 1u) list[2u * start[r] + size] = 64u * (uint32_t)n;
+        }
+        base += readlane(sum, 63);
+      }
+    }
+    wave_sync();
+    for (int v = lane; v < n; v += kWave) list[atomicAdd(&pos[xr[v]], 1u)] = 64u * (uint32_t)v;
+    for (int d = 0; d < k; ++d) set(d, mask - d);
+    set(k, HALF ? 0x8000 : taken);
+    wave_sync();
+    // ---- the classes of x in order
+    const uint2* list2 = reinterpret_cast<const uint2*>(list);
+    int32_t total = 0;
+    auto choose = [&](int32_t best) {  // the largest value found before its own vertex was added
+      const int32_t m = (HALF ? best >> 16 : best) + (1 << ib);
+      const bool ok = m >= 0;
+      total += ok ? m >> ib : 0;
+      atomicOr(cnt + (ok ? mask - (m & mask) : k) * 64, taken);
+    };
+    auto colours = [&](auto twos, uint32_t q, uint32_t* d) {
+#pragma unroll
+      for (int c = 0; c < decltype(twos)::value; ++c) {
+        const uint2 e = list2[q + c];
+        d[2 * c] = T[e.x + lane];
+        d[2 * c + 1] = T[e.y + lane];
+      }
+    };
+    auto raise = [&](auto twos, const uint32_t* d, int32_t& best) {
+      constexpr int V = 2 * decltype(twos)::value;
+      int32_t old[V];
+#pragma unroll
+      for (int c = 0; c < V; ++c) old[c] = atomicAdd(cnt + d[c] * 64u, unit);
+#pragma unroll
+      for (int c = 0; c < V; ++c) best = max(best, value(old[c]));
+    };
+    auto lower = [&](auto twos, const uint32_t* d) {
+#pragma unroll
+      for (int c = 0; c < 2 * decltype(twos)::value; ++c) atomicSub(cnt + d[c] * 64u, unit);
+    };
+    auto some = [&](auto twos, uint32_t q) {
+      uint32_t d[2 * decltype(twos)::value];
+      int32_t best = INT32_MIN;
+      colours(twos, q, d);
+      raise(twos, d, best);
+      lower(twos, d);
+      choose(best);
+    };
+    auto many = [&](uint32_t q, uint32_t end) {  // classes of more than 16, 16 vertices at a time
+      constexpr std::integral_constant<int, 8> eight{};
+      constexpr std::integral_constant<int, 1> one{};
+      int32_t best = INT32_MIN;
+      uint32_t d[16], at = q;
+      for (; at + 8 <= end; at += 8) {
+        colours(eight, at, d);
+        raise(eight, d, best);
+      }
+      for (; at < end; ++at) {
+        colours(one, at, d);
+        raise(one, d, best);
+      }
+      if (end - q > (uint32_t)k) {  // fewer counters than vertices
+#pragma unroll 4
+        for (int c = 0; c < k; ++c) set(c, value(cnt[c * 64]) < 0 ? (HALF ? 0x8000 | (mask - c) : taken | (mask - c)) : mask - c);
+        set(k, HALF ? 0x8000 : taken);
+      } else {
+        for (at = q; at + 8 <= end; at += 8) {
+          colours(eight, at, d);
+          lower(eight, d);
+        }
+        for (; at < end; ++at) {
+          colours(one, at, d);
+          lower(one, d);
+        }
+      }
+      choose(best);
+    };
+    auto start_of = [&](int t) -> uint32_t {
+      uint32_t s = base;
+#pragma unroll
+      for (int r = 0; r < KW; ++r)
+        if (t < k && (KW == 1 || t / kWave == r)) s = readlane(start[r], t & (kWave - 1));
+      return s;
+    };
+    uint32_t q = 0u;
+    for (int t = 0; t < nonempty; ++t) {
+      const uint32_t end = start_of(t + 1);
+      switch (end - q) {
+#define DLM_CASE(N) \
+  case N: some(std::integral_constant<int, N>{}, q); break;
+        DLM_CASE(1) DLM_CASE(2) DLM_CASE(3) DLM_CASE(4) DLM_CASE(5) DLM_CASE(6) DLM_CASE(7) DLM_CASE(8)
+#undef DLM_CASE
+        default: many(q, end);
+      }
+      q = end;
+    }
+    if (write) {
+      const int32_t d = n - total;
+      if (DIR == 0)
+        *at = ybad ? -1 : d;
+      else if (!ybad)
+        *at = min(*at, d);
+    }
+    wave_sync();
   }
 }
 
@@ -489,9 +743,70 @@ int dlm_partition_distance(int32_t n, int32_t k, const int16_t* a, int32_t na, c
   return DLM_OK;
 }
 
+// Whether the lanes kernel is the faster one.  However few the pairs, its two
+// launches take one wave through one row each, about 10 + 0.2 n + 0.6 k us;
+// the pair kernel takes about 0.7 + k^2 / 1000 ns a pair (1.8 k^2 beyond one
+// column per lane), two thirds of that in the triangle form.  Pair kernel and
+// lanes kernel, in us, around the line: n = 500, k = 49, 128 x 128 pairs 61
+// and 128, 256 x 256 181 and 129; n = 1000, k = 85, 64 x 64 77 and 151,
+// 256 x 256 879 and 279; n = 100, k = 15, 128 x 128 26 and 30, 256 x 256 68
+// and 31; n = 1000, k = 20, 128 x 128 40 and 200.
+static bool lanes_faster(int32_t na, int32_t nb, int32_t tri, int32_t n, int32_t k) {
+  const double pairs = (double)na * nb * (tri ? 2.0 / 3.0 : 1.0);
+  return pairs * (700.0 + (k <= kWave ? 1.0 : 1.8) * k * k) >= 1e6 * (10.0 + 0.2 * n + 0.6 * k);
+}
+
 static int distance_pairs(const int16_t* a, const int16_t* b, const int16_t* recA, const int16_t* recB, int32_t na,
                           int32_t nb, int32_t tri, int32_t n, int32_t k, int64_t npairs, int32_t* out, int64_t ld,
                           hipStream_t s) {
+  // The lanes kernel, with as many waves as the LDS holds; 16-bit counters
+  // where they take a whole row's count.
+  int bits = 1;
+  while ((1 << bits) < k) ++bits;
+  const bool half = ((int64_t)n << bits) < (1 << 15);
+  int waves = half ? 16 : 8;
+  while (waves > 0 && (int64_t)lanes_bytes(n, k, waves, half) > (int64_t)device_lds_limit()) waves -= half ? 2 : 1;
+  // few jobs: fewer waves to a workgroup, on more CUs
+  while (waves > 4 && waves % 4 == 0 && (int64_t)((nb + 63) / 64) * na < (int64_t)waves * device_cu_count()) waves /= 2;
+  if (k <= kLaneK && waves >= 2 && lanes_faster(na, nb, tri, n, k)) {
+    auto pass = [&](auto kern, int dir, const int16_t* x, const int16_t* rx, int32_t nx, const int16_t* y,
+                    const int16_t* ry, int32_t ny) -> int {
+      // rows per workgroup: at least one per wave, more once every CU has work
+      const int64_t groups = (ny + 63) / 64, jobs = groups * nx;
+      const int64_t per = std::max<int64_t>(1, std::min<int64_t>(8, jobs / ((int64_t)device_cu_count() * waves * 4)));
+      const int64_t rows = per * waves, chunks = (nx + rows - 1) / rows;
+      int64_t blocks = groups * chunks;
+      if (tri) {
+        blocks = 0;
+        for (int64_t c = 0; c < chunks; ++c) {
+          int g0, g1;
+          if (dir == 0)
+            lanes_tri_groups<0>((int)c, (int)rows, nx, (int)groups, g0, g1);
+          else
+            lanes_tri_groups<1>((int)c, (int)rows, nx, (int)groups, g0, g1);
+          blocks += g1 - g0;
+        }
+      }
+      const size_t bytes = lanes_bytes(n, k, waves, half);
+      DLM_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+      hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(kWave * waves), bytes, s, x, rx, nx, y, ry, ny,
+                         (int32_t)(tri != 0), n, k, bits, (int32_t)rows, out, ld);
+      DLM_HIP(hipGetLastError());
+      return DLM_OK;
+    };
+    auto both = [&](auto half_c, auto kw_c) -> int {
+      constexpr bool H = decltype(half_c)::value;
+      constexpr int W = decltype(kw_c)::value;
+      const int rc = pass(distance_lanes_kernel<0, H, W>, 0, a, recA, na, b, recB, nb);
+      return rc != DLM_OK ? rc : pass(distance_lanes_kernel<1, H, W>, 1, b, recB, nb, a, recA, na);
+    };
+    auto wide = [&](auto half_c) -> int {
+      if (k <= 64) return both(half_c, std::integral_constant<int, 1>{});
+      if (k <= 128) return both(half_c, std::integral_constant<int, 2>{});
+      return both(half_c, std::integral_constant<int, 4>{});
+    };
+    return half ? wide(std::true_type{}) : wide(std::false_type{});
+  }
   const uint32_t wave_bytes = 4u * hist_words(k);
   int wpb = (int)(65536u / wave_bytes);  // up to 4 waves and 64 KB of LDS per workgroup
   wpb = wpb < 1 ? 1 : (wpb > 4 ? 4 : wpb);

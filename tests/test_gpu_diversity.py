@@ -240,3 +240,37 @@ def test_gathers(dlm, dev):
             assert (rows[r] == allr[s]).all() and fs[r] == allf[s]
         else:
             assert (rows[r] == -1).all() and fs[r] == -1
+
+
+@pytest.mark.parametrize("k,n,na,nb", [(5, 64, 300, 261), (64, 511, 257, 200), (64, 512, 257, 200), (100, 255, 190, 130),
+                                       (128, 300, 130, 129), (255, 100, 150, 65), (200, 400, 64, 150),
+                                       (3, 1000, 640, 641), (20, 900, 500, 490), (2, 60, 320, 321)])
+def test_distance_many_pairs(dlm, dev, k, n, na, nb):
+    """Enough pairs for the one-lane-per-pair kernel: 16- and 32-bit counters,
+    one to four columns per lane, classes of one to hundreds of vertices, rows
+    with invalid colours; against the same rows in blocks too small for it,
+    which take the one-wave-per-pair kernel, and the oracle on some pairs."""
+    rng = np.random.default_rng(100 * k + n)
+    a = colourings(rng, na, n, k)
+    b = np.concatenate([colourings(rng, nb // 2, n, k), colourings(rng, nb - nb // 2, n, k, close_to=a, moved=n // 20)])
+    b[1] = 0
+    a[2, : n // 2] = k - 1
+    some = [(int(rng.integers(na)), int(rng.integers(nb))) for _ in range(12)] + [(2, 1), (na - 1, nb - 1)]
+    ref = [dv.distance_matrix(a[i:i + 1], b[j:j + 1], k)[0, 0] for i, j in some]
+    a[3, 0], b[0, n - 1] = k, -1
+    ga, gb = cuda(a), cuda(b)
+
+    def small_blocks(x, y):
+        return torch.cat([dlm.partition_distance(x, k, y[j:j + 8]) if x.shape[0] <= 40 else
+                          torch.cat([dlm.partition_distance(x[i:i + 40], k, y[j:j + 8]) for i in range(0, x.shape[0], 40)])
+                          for j in range(0, y.shape[0], 8)], dim=1)
+
+    say(f"distance many pairs k={k} n={n} {na}x{nb}")
+    got = dlm.partition_distance(ga, k, gb).cpu().numpy()
+    assert (got == small_blocks(ga, gb).cpu().numpy()).all()
+    for (i, j), d in zip(some, ref):
+        assert got[i, j] == (-1 if i == 3 or j == 0 else d), (i, j)
+    tri = dlm.partition_distance(ga, k).cpu().numpy()
+    want = small_blocks(ga, ga).cpu().numpy()
+    iu = np.triu_indices(na, 1)
+    assert (tri[iu] == want[iu]).all() and (tri.T == tri).all() and (np.diag(tri) == 0).all()
