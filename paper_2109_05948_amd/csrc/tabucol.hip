@@ -236,18 +236,18 @@ static int64_t w8_resident(const dlm_graph* g, int k, int64_t pop, int bits, int
 // registers hold 128.
 //
 // Waves: more of them shorten the chain of one iteration, the more so the
-// longer the rows, but individuals that share a CU hide one another's latency
-// as well, and the lists of more waves take LDS.  1,500 iterations with one,
-// two and four waves, in ms:
-//   one individual per CU    G(160, 0.5) 3.50 3.39 3.56   G(250, 0.5) 4.62 4.13 3.78
-//   two                      G(200, 0.5) 3.90 3.69 4.18   G(400, 0.5) 6.53 5.69 5.14
-//   four                     G(320, 0.5) 5.65 5.41 5.77   G(700, 0.15) 12.2 9.55 9.08
-//   eight                    G(250, 0.5) 6.49 6.97 11.0   G(400, 0.5) 9.00 7.99 12.1
-// So the more individuals a CU holds, the later the second and the fourth wave
-// come (the fourth by long rows as well: G(200, 0.8), one per CU, 4.14 3.92
-// 3.73; G(520, 0.8), four, 14.8 11.6 10.3).  Where the LDS of their lists costs residents they still pay as long
-// as the population passes through the CUs in about as many turns (G(700, 0.5),
-// 2,048 individuals, five, four and four resident: 34.2 26.1 25.1).
+// larger the graph and while many vertices conflict, but individuals that
+// share a CU hide one another's latency as well, and the lists of more waves
+// take LDS.  10,000 iterations from a random start with one, two and four
+// waves, in ms:
+//   one individual per CU    G(250, 0.5) 24.6 24.8 23.5   G(400, 0.3) 28.0 25.9 24.4   G(700, 0.5) 49.8 42.3 39.5
+//   two                      G(320, 0.5) 27.5 27.7 28.7   G(400, 0.5) 30.5 28.9 29.6   G(700, 0.3) 47.2 41.5 38.9
+//   four                     G(320, 0.5) 29.0 30.9 35.8   G(520, 0.5) 41.0 37.9 52.1   G(900, 0.5) 139 114 99.8
+//   eight                    G(320, 0.5) 39.3 41.9 69.2   G(400, 0.5) 42.5 41.3 71.5   G(520, 0.3) 51.4 50.6 77.5
+// The more individuals a CU holds, the later the second and the fourth wave
+// come.  Where the LDS of their lists costs residents they still pay as long
+// as the population passes through the CUs in about as many turns (G(900,
+// 0.75), 1,024 individuals: 184 157 139).
 W8Pick w8_pick(const dlm_graph* g, const dlm_tabu_params* p, int64_t pop) {
   const int n = g->n, k = p->k;
   W8Pick r;
@@ -258,11 +258,11 @@ W8Pick w8_pick(const dlm_graph* g, const dlm_tabu_params* p, int64_t pop) {
   auto resident = [&](int w) { return w8_resident(g, k, pop, r.bits, r.side, w); };
   auto turns = [&](int64_t held) { return (share + held - 1) / held; };
   const int64_t t1 = turns(std::max<int64_t>(1, resident(1))), r2 = resident(2), r4 = resident(4);
-  const int64_t deg = g->nnz / std::max(n, 1);
+  const int four = r4 == 1 ? 250 : r4 == 2 ? 650 : 800, two = r2 == 1 ? 320 : r2 == 2 ? 360 : 400;
   r.waves = 1;
-  if (r4 > 0 && (r4 == 1 ? n >= 240 || deg >= 110 : r4 == 2 ? n >= 400 : r4 <= 4 && (n >= 640 || deg >= 400)) && 4 * turns(r4) <= 5 * t1)
+  if (r4 > 0 && r4 <= 4 && n >= four && 4 * turns(r4) <= 5 * t1)
     r.waves = 4;
-  else if (r2 > 0 && n >= (r2 == 1 ? 160 : r2 == 2 ? 200 : 256) && 9 * turns(r2) <= 10 * t1)
+  else if (r2 > 0 && n >= two && 9 * turns(r2) <= 10 * t1)
     r.waves = 2;
   return r;
 }

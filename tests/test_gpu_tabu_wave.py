@@ -260,7 +260,8 @@ def test_wave_static_entry_point(dlm, dev):
 WIDTHS = [  # (n, p, k, T, pop, sampled rows): entry width, waves per individual, row dwords
     (100, 0.5, 9, 2000, 4, None),            # 4 bits, one wave
     (300, 0.5, 22, 2000, 5, None),           # 4 bits, four waves, entries that outgrow 4 bits
-    (180, 0.5, 18, 2000, 4, None),           # 4 bits, two waves
+    (340, 0.3, 18, 2000, 600, (0, 255, 599)),     # 4 bits, three individuals per CU
+    (430, 0.5, 40, 500, 600, (0, 300, 599)),      # 4 bits, two waves
     (220, 0.5, 22, 300, 700, (0, 255, 699)),      # three individuals per CU, one wave each
     (600, 0.5, 44, 1500, 3, None),           # the same with four waves and more escapes than a register bank
     (400, 0.97, 256, 400, 3, None),          # 4 bits, 32 dwords, every 8-bit colour in use
