@@ -97,14 +97,23 @@ struct TrainBufs {
   float* p2;      // [B][H2] per-colouring sum over classes of da2
 };
 
+__device__ __forceinline__ int rfl_i(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
 // ---------------------------------------------------------------------------
 // Forward, one workgroup (4 waves) per colouring.
-//   layer 1: wave w takes classes i = w, w+4, ...; it lists the class's
+//   layer 1 (FEW): wave w takes classes i = w, w+4, ...; it lists the class's
 //            vertices in ascending order (ballot) and sums their W1 rows, lane l
 //            owning features 4l..4l+3 (deterministic order)
+//   layer 1 (else): the same sums in the same order; the vertices are sorted
+//            by class, ascending within each (ballots over the bits of the
+//            class rank every 64 of them), and wave w takes the w-th quarter
+//            of the classes.  Bound by W1's rows out of the L2 (n KB a
+//            colouring), so eight rows are always under way:
+//            32,768 colourings of 1,000 vertices, k = 85, took 4.6 ms with a
+//            scan of all vertices per class and a row at a time, 1.9 ms so.
 //   layer 2: wave w computes the output columns 32w..32w+31 for every row tile
 //   pool + head: column sums over the valid rows, then the FP32 head
-template <bool TRAIN>
+template <bool TRAIN, bool FEW>
 __global__ __launch_bounds__(256) void scorer_fwd_kernel(ScorerDev s, const int16_t* __restrict__ colors,
                                                          int32_t count, float* __restrict__ out,
                                                          TrainBufs tb) {
@@ -113,46 +122,182 @@ __global__ __launch_bounds__(256) void scorer_fwd_kernel(ScorerDev s, const int1
   const int n = s.n, k = s.k, kpad = s.kpad;
   const int64_t b = blockIdx.x;
   uint16_t* h1 = reinterpret_cast<uint16_t*>(smem);                       // [kpad][kRowPadH1]
-  int16_t* col = reinterpret_cast<int16_t*>(smem + (size_t)kpad * kRowPadH1 * 2);
-  uint16_t* lists = reinterpret_cast<uint16_t*>(col + ((n + 7) & ~7));   // [4][n]
-  float* zs = reinterpret_cast<float*>(lists + 4 * ((n + 7) & ~7));       // [H2]
-  float* hs = zs + H2;                                                    // [H3]
+  const int np = (n + 7) & ~7;
+  // FEW: the colours and a list per wave, else one list of all vertices
+  uint16_t* lists = reinterpret_cast<uint16_t*>(smem + (size_t)kpad * kRowPadH1 * 2) + (FEW ? np : 0);
+  float* zs = reinterpret_cast<float*>(lists + (FEW ? 4 : 1) * np);  // [H2]
+  float* hs = zs + H2;                                               // [H3]
 
   const int16_t* cb = colors + b * n;
-  for (int v = tid; v < n; v += 256) col[v] = cb[v];
-  // rows k..kpad-1 are zero
-  for (int i = k + wid; i < kpad; i += 4)
-    for (int f = lane; f < H1; f += 64) h1[i * kRowPadH1 + f] = 0;
-  __syncthreads();
+  if constexpr (FEW) {
+    int16_t* col = reinterpret_cast<int16_t*>(lists) - np;
+    for (int v = tid; v < n; v += 256) col[v] = cb[v];
+    // rows k..kpad-1 are zero
+    for (int i = k + wid; i < kpad; i += 4)
+      for (int f = lane; f < H1; f += 64) h1[i * kRowPadH1 + f] = 0;
+    __syncthreads();
+    // ---- layer 1 (gather) + LReLU -> h1 (bf16, LDS)
+    uint16_t* mylist = lists + wid * np;
+    const float* b1 = s.P + s.ob1;
+    for (int i = wid; i < k; i += 4) {
+      int cnt = 0;
+      for (int v0 = 0; v0 < n; v0 += 64) {
+        const int v = v0 + lane;
+        const bool in = v < n && col[v] == i;
+        const uint64_t m = __ballot(in);
+        if (in) mylist[cnt + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)v;
+        cnt += __popcll(m);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      float a0 = b1[4 * lane], a1v = b1[4 * lane + 1], a2v = b1[4 * lane + 2], a3v = b1[4 * lane + 3];
+      const float* W1 = s.P + s.oW1 + 4 * lane;
+      for (int q = 0; q < cnt; ++q) {
+        const float4 wrow = *reinterpret_cast<const float4*>(W1 + (size_t)mylist[q] * H1);
+        a0 += wrow.x;
+        a1v += wrow.y;
+        a2v += wrow.z;
+        a3v += wrow.w;
+      }
+      uint16_t* row = h1 + i * kRowPadH1 + 4 * lane;
+      row[0] = f2bf(lrelu(a0));
+      row[1] = f2bf(lrelu(a1v));
+      row[2] = f2bf(lrelu(a2v));
+      row[3] = f2bf(lrelu(a3v));
+    }
+  } else {
+    const int chunks = (n + 63) >> 6, w = __builtin_amdgcn_readfirstlane(wid);
+    const int i0 = k * w / 4, i_end = k * (w + 1) / 4;      // this wave's classes
+    uint16_t* first = reinterpret_cast<uint16_t*>(zs);      // [k + 1] first list entries, until layer 2 is done
+    // ---- the vertices by class.  cc[chunk][class]: the class's vertices in each
+    // 64 vertices, then where that chunk's part of the class begins (in h1's room)
+    uint16_t* cc = h1;
+    for (int i = tid; i < chunks * k; i += 256) cc[i] = 0;
+    __syncthreads();
+    int bits = 1;
+    while ((1 << bits) < k) ++bits;
+    auto same_class = [&](int c) -> uint64_t {  // lanes of the wave with the same c
+      uint64_t m = __ballot(c >= 0);
+      for (int i = 0; i < bits; ++i) {
+        const uint64_t set = __ballot((c >> i) & 1);
+        m &= (c >> i) & 1 ? set : ~set;
+      }
+      return m;
+    };
+    // the wave's chunks w, w + 4, ...; the first four's colours are read at once and kept
+    auto colour = [&](int ch) -> int {  // -1: no class, such a vertex adds to none
+      const int v = 64 * ch + lane, c = v < n ? (int)cb[v] : -1;
+      return c < k ? c : -1;
+    };
+    int kept[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) kept[q] = colour(w + 4 * q);
+    auto each_chunk = [&](auto f) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (w + 4 * q < chunks) f(w + 4 * q, kept[q]);
+      for (int ch = w + 16; ch < chunks; ch += 4) f(ch, colour(ch));
+    };
+    each_chunk([&](int ch, int c) {
+      const uint64_t m = same_class(c);
+      if (c >= 0 && (m & ((1ull << lane) - 1ull)) == 0ull) cc[ch * k + c] = (uint16_t)__popcll(m);
+    });
+    __syncthreads();
+    // begins[r]: first entry of class lane + 64 r (every wave computes all)
+    constexpr int KR = 4;  // k <= 256
+    int begins[KR], base = 0;
+#pragma unroll
+    for (int r = 0; r < KR; ++r) {
+      begins[r] = base;
+      if (64 * r < k) {
+        const int c = 64 * r + lane;
+        int total = 0;
+        if (c < k)
+          for (int ch = 0; ch < chunks; ++ch) total += cc[ch * k + c];
+        int sum = total;
+        for (int o = 1; o < 64; o <<= 1) {
+          const int up = __shfl_up(sum, o);
+          sum += lane >= o ? up : 0;
+        }
+        begins[r] = base + sum - total;
+        base += __builtin_amdgcn_readlane(sum, 63);
+      }
+    }
+    __syncthreads();  // every wave has read the counts
+    if (wid == 0) {
+      if (lane == 0) first[k] = (uint16_t)base;
+#pragma unroll
+      for (int r = 0; r < KR; ++r) {
+        const int c = 64 * r + lane;
+        int at = begins[r];
+        if (c < k) first[c] = (uint16_t)at;
+        if (c < k)
+          for (int ch = 0; ch < chunks; ++ch) {
+            const int here = cc[ch * k + c];
+            cc[ch * k + c] = (uint16_t)at;
+            at += here;
+          }
+      }
+    }
+    __syncthreads();
+    each_chunk([&](int ch, int c) {
+      const uint64_t m = same_class(c);
+      if (c >= 0) lists[cc[ch * k + c] + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)(64 * ch + lane);
+    });
+    __syncthreads();
+    const int e1 = rfl_i(first[i_end]);
+    // rows k..kpad-1 are zero
+    for (int i = k + wid; i < kpad; i += 4)
+      for (int f = lane; f < H1; f += 64) h1[i * kRowPadH1 + f] = 0;
 
-  // ---- layer 1 (gather) + LReLU -> h1 (bf16, LDS)
-  uint16_t* mylist = lists + wid * ((n + 7) & ~7);
-  const float* b1 = s.P + s.ob1;
-  for (int i = wid; i < k; i += 4) {
-    int cnt = 0;
-    for (int v0 = 0; v0 < n; v0 += 64) {
-      const int v = v0 + lane;
-      const bool in = v < n && col[v] == i;
-      const uint64_t m = __ballot(in);
-      if (in) mylist[cnt + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)v;
-      cnt += __popcll(m);
+    // ---- layer 1 (gather) + LReLU -> h1 (bf16, LDS)
+    {
+      const float4 bias = *reinterpret_cast<const float4*>(s.P + s.ob1 + 4 * lane);
+      const float* W1 = s.P + s.oW1 + 4 * lane;
+      int i = i0;
+      auto first_of = [&](int c) { return c < i_end ? rfl_i(first[c]) : e1; };
+      const int e0 = first_of(i0);
+      int next = first_of(i0 + 1);
+      float4 a = bias;
+      auto finish = [&]() {  // class i is complete
+        uint16_t* row = h1 + i * kRowPadH1 + 4 * lane;
+        row[0] = f2bf(lrelu(a.x));
+        row[1] = f2bf(lrelu(a.y));
+        row[2] = f2bf(lrelu(a.z));
+        row[3] = f2bf(lrelu(a.w));
+        a = bias;
+        ++i;
+        next = first_of(i + 1);
+      };
+      for (int eb = e0; eb < e1; eb += 64) {
+        const int mine = lists[min(eb + lane, e1 - 1)], cnt = min(64, e1 - eb);
+        auto load = [&](float4 (&r)[8], int q) {  // entries past the last repeat it
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            r[j] = *reinterpret_cast<const float4*>(W1 + (size_t)__builtin_amdgcn_readlane(mine, min(q + j, cnt - 1)) * H1);
+        };
+        auto add = [&](const float4 (&r)[8], int q) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            if (q + j < cnt) {
+              while (eb + q + j >= next) finish();
+              a.x += r[j].x;
+              a.y += r[j].y;
+              a.z += r[j].z;
+              a.w += r[j].w;
+            }
+        };
+        float4 w0[8], w1[8];
+        load(w0, 0);
+        for (int q = 0; q < cnt; q += 16) {
+          load(w1, q + 8);
+          add(w0, q);
+          load(w0, q + 16);
+          add(w1, q + 8);
+        }
+      }
+      while (i < i_end) finish();
     }
-    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    float a0 = b1[4 * lane], a1v = b1[4 * lane + 1], a2v = b1[4 * lane + 2], a3v = b1[4 * lane + 3];
-    const float* W1 = s.P + s.oW1 + 4 * lane;
-    for (int q = 0; q < cnt; ++q) {
-      const float4 wrow = *reinterpret_cast<const float4*>(W1 + (size_t)mylist[q] * H1);
-      a0 += wrow.x;
-      a1v += wrow.y;
-      a2v += wrow.z;
-      a3v += wrow.w;
-    }
-    uint16_t* row = h1 + i * kRowPadH1 + 4 * lane;
-    row[0] = f2bf(lrelu(a0));
-    row[1] = f2bf(lrelu(a1v));
-    row[2] = f2bf(lrelu(a2v));
-    row[3] = f2bf(lrelu(a3v));
   }
   __syncthreads();
   if (TRAIN) {  // h1 transposed for the weight-gradient product: h1t[b][f][i]
@@ -163,16 +308,24 @@ __global__ __launch_bounds__(256) void scorer_fwd_kernel(ScorerDev s, const int1
     }
   }
 
-  // ---- layer 2 on MFMA: wave w -> columns n0 = 32 w
+  // ---- layer 2 on MFMA: wave w -> columns n0 = 32 w, its part of W2 in registers
   const int n0 = 32 * wid;
+  bf8 w2[FEW ? 1 : H1 / 16];
+#pragma unroll
+  for (int q = 0; q < (FEW ? 0 : H1 / 16); ++q) w2[q] = ld_b8(s.W2t + (size_t)(n0 + (lane & 31)) * H1 + 8 * (lane >> 5) + 16 * q);
   const float bias2 = s.P[s.ob2 + n0 + (lane & 31)];
   float zc = 0.f;  // this lane's share of z[n0 + lane % 32]
   for (int m0 = 0; m0 < kpad; m0 += 32) {
     f16v acc = {};
     const uint16_t* arow = h1 + (m0 + (lane & 31)) * kRowPadH1 + 8 * (lane >> 5);
-    const uint16_t* brow = s.W2t + (size_t)(n0 + (lane & 31)) * H1 + 8 * (lane >> 5);
+    if constexpr (FEW) {
+      const uint16_t* brow = s.W2t + (size_t)(n0 + (lane & 31)) * H1 + 8 * (lane >> 5);
 #pragma unroll 4
-    for (int k0 = 0; k0 < H1; k0 += 16) acc = mfma(ld_b8(arow + k0), ld_b8(brow + k0), acc);
+      for (int k0 = 0; k0 < H1; k0 += 16) acc = mfma(ld_b8(arow + k0), ld_b8(brow + k0), acc);
+    } else {
+#pragma unroll
+      for (int q = 0; q < H1 / 16; ++q) acc = mfma(ld_b8(arow + 16 * q), w2[q], acc);
+    }
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int i = m0 + 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3);
@@ -309,7 +462,9 @@ __global__ __launch_bounds__(256) void scorer_dw2_kernel(int32_t count, int32_t 
     }
 }
 
-// Small gradients and the dW2 reduction (fixed summation order).
+// Small gradients and the dW2 reduction (fixed summation order).  Each sum is
+// one chain of adds; sixteen of its loads are under way at a time (302 -> 45
+// us at 1,024 colourings).
 __global__ __launch_bounds__(256) void scorer_grad_small_kernel(ScorerDev s, int32_t count,
                                                                 int32_t nchunk, TrainBufs tb,
                                                                 float* __restrict__ g) {
@@ -317,6 +472,7 @@ __global__ __launch_bounds__(256) void scorer_grad_small_kernel(ScorerDev s, int
   int64_t o = e;
   if (o < H1 * H2) {  // dW2
     float a = 0.f;
+#pragma unroll 16
     for (int c = 0; c < nchunk; ++c) a += tb.part[(int64_t)c * H1 * H2 + o];
     g[s.oW2 + o] = a;
     return;
@@ -324,6 +480,7 @@ __global__ __launch_bounds__(256) void scorer_grad_small_kernel(ScorerDev s, int
   o -= H1 * H2;
   if (o < H1) {  // db1
     float a = 0.f;
+#pragma unroll 16
     for (int b = 0; b < count; ++b) a += tb.p1[(int64_t)b * H1 + o];
     g[s.ob1 + o] = a;
     return;
@@ -331,6 +488,7 @@ __global__ __launch_bounds__(256) void scorer_grad_small_kernel(ScorerDev s, int
   o -= H1;
   if (o < H2) {  // db2
     float a = 0.f;
+#pragma unroll 16
     for (int b = 0; b < count; ++b) a += tb.p2[(int64_t)b * H2 + o];
     g[s.ob2 + o] = a;
     return;
@@ -339,6 +497,7 @@ __global__ __launch_bounds__(256) void scorer_grad_small_kernel(ScorerDev s, int
   if (o < H2 * H3) {  // dW3
     const int q = (int)(o / H3), j = (int)(o % H3);
     float a = 0.f;
+#pragma unroll 16
     for (int b = 0; b < count; ++b) a += tb.z[(int64_t)b * H2 + q] * tb.da3[(int64_t)b * H3 + j];
     g[s.oW3 + o] = a;
     return;
@@ -346,6 +505,7 @@ __global__ __launch_bounds__(256) void scorer_grad_small_kernel(ScorerDev s, int
   o -= H2 * H3;
   if (o < H3) {  // db3 and dw4
     float a = 0.f, w = 0.f;
+#pragma unroll 16
     for (int b = 0; b < count; ++b) {
       a += tb.da3[(int64_t)b * H3 + o];
       w += tb.dy[b] * lrelu(tb.a3[(int64_t)b * H3 + o]);
@@ -357,20 +517,31 @@ __global__ __launch_bounds__(256) void scorer_grad_small_kernel(ScorerDev s, int
   o -= H3;
   if (o == 0) {  // db4
     float a = 0.f;
+#pragma unroll 16
     for (int b = 0; b < count; ++b) a += tb.dy[b];
     g[s.ob4] = a;
   }
 }
 
-// dW1[v][f] = sum_b da1[b][col_b v][f]  (fixed order over b)
+// dW1[v][f] = sum_b da1[b][col_b v][f]  (fixed order over b; sixteen colours,
+// then their rows, are under way at a time: 477 -> 310 us at n = 1,000 and
+// 1,024 colourings)
 __global__ __launch_bounds__(256) void scorer_dw1_kernel(ScorerDev s, const int16_t* __restrict__ colors,
                                                          int32_t count, TrainBufs tb, float* __restrict__ g) {
   const int v = blockIdx.x, f = threadIdx.x;
   float a = 0.f;
-  for (int b = 0; b < count; ++b) {
-    const int c = colors[(int64_t)b * s.n + v];
-    a += tb.da1[((int64_t)b * s.kpad + c) * H1 + f];
+  int b = 0;
+  for (; b + 16 <= count; b += 16) {
+    int c[16];
+    float d[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) c[j] = colors[(int64_t)(b + j) * s.n + v];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) d[j] = tb.da1[((int64_t)(b + j) * s.kpad + c[j]) * H1 + f];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) a += d[j];
   }
+  for (; b < count; ++b) a += tb.da1[((int64_t)b * s.kpad + colors[(int64_t)b * s.n + v]) * H1 + f];
   g[s.oW1 + (int64_t)v * H1 + f] = a;
 }
 
@@ -435,9 +606,20 @@ struct dlm_scorer {
 };
 
 namespace {
-size_t fwd_lds(int n, int kpad) {
+// Up to 32 classes (one row tile) a scan of the vertices per class and a row at
+// a time are the faster form: the sort's phases and W2's registers, which cost
+// residents, have too little to save.  Scan and sort, in us: n = 309, k = 12,
+// 310 colourings 16.4 and 19.7; n = 500, k = 25, 4,000: 122 and 134; n = 1000,
+// k = 40, 4,000: 294 and 220; n = 309, k = 40, 310: 28 and 22; k = 60, 348 and 224.
+bool scorer_few(int k) { return k <= 32; }
+size_t fwd_lds(int n, int k, int kpad) {
   const size_t np = (size_t)((n + 7) & ~7);
-  return (size_t)kpad * kRowPadH1 * 2 + np * 2 + 4 * np * 2 + (H2 + H3) * 4;
+  return (size_t)kpad * kRowPadH1 * 2 + np * 2 * (scorer_few(k) ? 5 : 1) + (H2 + H3) * 4;
+}
+// The sizes served are those whose colours and four vertex lists would fit as
+// well: what the sort's counts rely on (they take the place of h1).
+size_t fwd_lds_limit(int n, int kpad) {
+  return (size_t)kpad * kRowPadH1 * 2 + (size_t)((n + 7) & ~7) * 10 + (H2 + H3) * 4;
 }
 size_t bwd_lds(int kpad) { return (size_t)kpad * kRowPadH2 * 2 + (H2 + H3) * 4; }
 
@@ -452,8 +634,9 @@ int cast_weights(dlm_scorer* s, hipStream_t st) {
 int grad_pass(dlm_scorer* s, const int16_t* colors, const float* targets, int32_t count,
               float* loss, hipStream_t st) {
   const ScorerDev d = s->dev();
-  const size_t lf = fwd_lds(s->n, s->kpad), lb = bwd_lds(s->kpad);
-  hipLaunchKernelGGL(scorer_fwd_kernel<true>, dim3(count), dim3(256), lf, st, d, colors, count, s->tb.y, s->tb);
+  const size_t lf = fwd_lds(s->n, s->k, s->kpad), lb = bwd_lds(s->kpad);
+  const auto fwd = scorer_few(s->k) ? scorer_fwd_kernel<true, true> : scorer_fwd_kernel<true, false>;
+  hipLaunchKernelGGL(fwd, dim3(count), dim3(256), lf, st, d, colors, count, s->tb.y, s->tb);
   DLM_HIP(hipGetLastError());
   if (loss) {
     hipLaunchKernelGGL(scorer_loss_kernel, dim3(1), dim3(256), 0, st, s->tb.y, targets, count, loss);
@@ -579,12 +762,13 @@ int dlm_score_offspring(const dlm_scorer* s, const int16_t* colors, int32_t coun
   if (rc != DLM_OK) return rc;
   if (count == 0) return DLM_OK;
   if (!scores) return set_error(DLM_E_INVAL, "dlm_score_offspring: scores is NULL");
-  const size_t lds = fwd_lds(s->n, s->kpad);
-  if ((int64_t)lds > device_lds_limit())
-    return set_error(DLM_E_UNSUPPORTED, "dlm_score_offspring: %zu bytes of LDS needed", lds);
-  DLM_HIP(hipFuncSetAttribute((const void*)scorer_fwd_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+  const size_t lds = fwd_lds(s->n, s->k, s->kpad), need = fwd_lds_limit(s->n, s->kpad);
+  if ((int64_t)need > device_lds_limit())
+    return set_error(DLM_E_UNSUPPORTED, "dlm_score_offspring: %zu bytes of LDS needed", need);
+  const auto fwd = scorer_few(s->k) ? scorer_fwd_kernel<false, true> : scorer_fwd_kernel<false, false>;
+  DLM_HIP(hipFuncSetAttribute((const void*)fwd, hipFuncAttributeMaxDynamicSharedMemorySize,
                               (int)lds));
-  hipLaunchKernelGGL(scorer_fwd_kernel<false>, dim3(count), dim3(256), lds, (hipStream_t)stream, s->dev(), colors,
+  hipLaunchKernelGGL(fwd, dim3(count), dim3(256), lds, (hipStream_t)stream, s->dev(), colors,
                      count, scores, s->tb);
   DLM_HIP(hipGetLastError());
   return DLM_OK;
@@ -598,8 +782,9 @@ int dlm_scorer_grad(dlm_scorer* s, const int16_t* colors, const float* targets, 
     return set_error(DLM_E_INVAL, "dlm_scorer_grad: count=%d outside [1, max_batch=%d]", count, s->max_batch);
   if (!targets) return set_error(DLM_E_INVAL, "dlm_scorer_grad: targets is NULL");
   hipStream_t st = (hipStream_t)stream;
-  DLM_HIP(hipFuncSetAttribute((const void*)scorer_fwd_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)fwd_lds(s->n, s->kpad)));
+  const auto fwd = scorer_few(s->k) ? scorer_fwd_kernel<true, true> : scorer_fwd_kernel<true, false>;
+  DLM_HIP(hipFuncSetAttribute((const void*)fwd, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)fwd_lds_limit(s->n, s->kpad)));
   if ((rc = grad_pass(s, colors, targets, count, loss_dev, st)) != DLM_OK) return rc;
   if (grad_dev)
     DLM_HIP(hipMemcpyAsync(grad_dev, s->g, sizeof(float) * s->L.total, hipMemcpyDeviceToDevice, st));
@@ -616,8 +801,9 @@ int dlm_scorer_train(dlm_scorer* s, const int16_t* colors, const float* targets,
   if (count == 0 || epochs == 0) return DLM_OK;
   if (!targets) return set_error(DLM_E_INVAL, "dlm_scorer_train: targets is NULL");
   hipStream_t st = (hipStream_t)stream;
-  DLM_HIP(hipFuncSetAttribute((const void*)scorer_fwd_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              (int)fwd_lds(s->n, s->kpad)));
+  const auto fwd = scorer_few(s->k) ? scorer_fwd_kernel<true, true> : scorer_fwd_kernel<true, false>;
+  DLM_HIP(hipFuncSetAttribute((const void*)fwd, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)fwd_lds_limit(s->n, s->kpad)));
   const double beta1 = 0.9, beta2 = 0.999;
   int64_t li = 0;
   for (int ep = 0; ep < epochs; ++ep)

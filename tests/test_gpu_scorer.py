@@ -164,3 +164,22 @@ def test_adam_step_and_training(dlm, dev):
                       epochs=30, lr=1e-3).cpu().numpy()
     assert np.isfinite(losses).all()
     assert losses[-4:].mean() < 0.5 * losses[:4].mean()
+
+
+@pytest.mark.parametrize("n,k,count", [(1, 1, 3), (64, 1, 5), (65, 2, 7), (130, 200, 6), (1000, 3, 9), (959, 256, 4)])
+def test_forward_class_lists(dlm, dev, n, k, count):
+    """Classes of none to hundreds of vertices, k past n and at its largest,
+    vertex counts around multiples of 64; vertices whose colour is outside
+    [0, k) add to no class (the oracle gets a zero row of W1 for them)."""
+    W = scorer_weights(n, seed=n)
+    rng = np.random.default_rng(n + k)
+    cols = colorings(rng, count, n, k)
+    out = np.arange(n) % 7 == 3
+    P = {kk: v.astype(np.float64) for kk, v in W.items()}
+    P["W1"] = P["W1"].copy()
+    P["W1"][out] = 0.0
+    yr = ref.forward(P, cols, k)
+    cols[:, out] = np.where(rng.random((count, int(out.sum()))) < 0.5, -1, k)
+    say(f"scorer class lists n={n} k={k}")
+    y = dlm.Scorer(n, k, W, max_batch=8).score(torch.from_numpy(cols).cuda()).cpu().numpy()
+    assert rel_ok(y, yr).all(), np.max(np.abs(y - yr) / np.maximum(np.abs(yr), 1))
