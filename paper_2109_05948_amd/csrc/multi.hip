@@ -247,7 +247,7 @@ std::vector<WaveItem> wave_items(const dlm_multi_item* items, const std::vector<
     r.push_back(w);
   }
   const int64_t cus = device_cu_count();
-  if (lds * 4 > cus * device_lds_per_cu() * 3 || waves > 16 * cus) {
+  if (lds > cus * device_lds_per_cu() || waves > 16 * cus) {
     size_t kept = 0;
     for (WaveItem& w : r)
       if (wave_item(items[w.oi], total, budget, w)) r[kept++] = w;
