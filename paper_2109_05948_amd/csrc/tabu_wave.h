@@ -16,7 +16,7 @@
 //               pair that is neither tabu nor too large returns to the table.
 //               128 entries live in registers of the last wave, one or two per
 //               lane; the rest in act[] = v << 17 | c << 9 | low 9 bits of the
-//               expiry mod 2^15 and actg[] = its high 6 bits << 8 | gamma | 0x80
+//               expiry mod 2^17 and actg[] = its high 8 bits << 8 | gamma | 0x80
 //               on a pair that is not tabu
 //   cg[v]       colour (bits 0..7) | gamma[v][col v] (bits 8..14) |
 //               "listed" (bit 15)
@@ -58,7 +58,7 @@ namespace dlm {
 
 constexpr uint32_t kW8ClassMax = 127u;
 constexpr uint32_t kW8None = 255u;        // biased delta (delta + 128) of "no admissible move"
-constexpr uint32_t kW8ExpMask = 0x7fffu;  // expiries are kept modulo 2^15
+constexpr uint32_t kW8ExpMask = 0x1ffffu;  // expiries are kept modulo 2^17; no tenure reaches it (32,757 + 1,023)
 constexpr uint32_t kW8NoKey = 0xffffffffu;
 constexpr uint32_t kW8Free = 0x80u;  // gamma of a side-list pair: not tabu
 constexpr int kW8Stage = 128;        // tied rows a wave stages: up to 64 waiting and 64 more
@@ -346,7 +346,7 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
   bool mailed = false;  // entries wait in mail (one wave: known without a look)
   const RoundKeys rk = round_keys(key);
   // the tail wave's register part of the side list: vertex, colour, expiry mod
-  // 2^15, gamma | kW8Free; a free lane holds vertex n and a colour that matches nothing
+  // 2^17, gamma | kW8Free; a free lane holds vertex n and a colour that matches nothing
   constexpr int NB = 2;
   constexpr uint32_t kNoColour = 0xfffeu;
   uint32_t sv[NB], sc[NB], sx[NB], sg[NB];

@@ -340,3 +340,47 @@ def test_wave_table_beyond_two_to_the_seventeen_asks_for_no_more_workspace(dlm, 
     n, k = 1000, 223
     G = dlm.Graph.from_csr(gnp(n, 0.9, seed=4))
     assert dlm.tabu_workspace_bytes(G, pop, k, 100) <= dlm.tabu_workspace_bytes(G, pop, k, 100, table="global16")
+
+
+LONG = [  # (n, p, k, T, pop): 4 bits and one wave, four waves, 8 bits, a table beyond 2^17 entries
+    (60, 0.5, 5, 3000, 3), (300, 0.5, 22, 2500, 2), (300, 0.95, 12, 2500, 2), (800, 0.9, 185, 4000, 2)]
+
+
+@pytest.mark.parametrize("shape", LONG, ids=lambda s: "n%d_p%g_k%d" % s[:3])
+def test_wave_tenures_past_two_to_the_fifteen(dlm, dev, shape):
+    """ten_num = 32767, ten_den = 1 and ten_rand = 1024: the capped term of
+    32,757 and the random term pass 2^15 together, so nearly every pair stays
+    tabu to the end.  A stored expiry of 15 bits would free it within 1,012
+    iterations of its move."""
+    n, p, k, T, pop = shape
+    g = gnp(n, p, seed=n + 1)
+    starts = oracle.init_random(n, k, pop, seed=4)
+    ten = {"ten_num": 32767, "ten_den": 1, "ten_rand": 1024}
+    ref = oracle.tabucol_batch(g, starts, np.arange(pop), k, T, seed=12, **ten)
+    assert (ref["f_best"] > 0).all()
+    say(f"wave8 tenures past 2^15 n={n} k={k} T={T}")
+    G = dlm.Graph.from_csr(g)
+    outs = [dlm.tabu_batch(G, torch.from_numpy(starts).cuda(), k, T, 12, **ten)]
+    job = {"graph": G, "colors": torch.from_numpy(starts).cuda(), "k": k, "iters": T, "seed": 12, **ten}
+    mb = dlm.MultiBatch([job])
+    mb.launch()
+    outs.append({**job, "iters": job["iters_out"]})
+    torch.cuda.synchronize()
+    for r, name in zip(outs, ("batch", "multi")):
+        gpu = {x: r[x].cpu().numpy() for x in ("f_best", "iters", "stats", "hash", "colors")}
+        gpu["hash"] = gpu["hash"].view(np.uint64)
+        compare(gpu, ref, range(pop), f"long tenures {name} n{n} k{k}")
+
+
+def test_wave_run_past_two_to_the_seventeen(dlm, dev):
+    """140,000 iterations: the stored expiries (modulo 2^17) wrap, in the
+    registers and, with the long tenures, in the LDS list."""
+    g = gnp(60, 0.5, seed=9)
+    k, T, pop = 6, 140000, 2
+    starts = oracle.init_random(g.n, k, pop, seed=5)
+    for ten in ({}, {"ten_num": 32767, "ten_den": 64, "ten_rand": 1024}):
+        ref = oracle.tabucol_batch(g, starts, np.arange(pop), k, T, seed=8, **ten)
+        assert (ref["iters"] == T).all()
+        say(f"wave8 n=60 k={k} T={T} {ten}")
+        gpu = gpu_run(dlm, g, starts, k, T, 8, **ten)
+        compare(gpu, ref, range(pop), "wave8 2^17")
