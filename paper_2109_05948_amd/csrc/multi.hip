@@ -223,7 +223,8 @@ dlm_tabu_params item_params(const dlm_multi_item& it) {
 // number of waves is picked for.
 bool wave_item(const dlm_multi_item& it, int64_t pop, int64_t budget, WaveItem& w) {
   const dlm_tabu_params q = item_params(it);
-  if (!it.g->ell || !w8_auto(it.g, &q) || it.g->n > (int)(kW8ClassMax / 2) * it.k) return false;
+  if (!it.g->ell || !w8_auto(it.g, &q) || it.g->n > (int)(kW8ClassMax / 2) * it.k || block_faster(it.g, &q, pop))
+    return false;
   w.pick = w8_pick(it.g, &q, pop);
   w.instance = w8_multi_instance(it.k, w.pick.bits);
   w.least = (int64_t)w8_layout(it.g->n, it.k, w.pick.bits, w.pick.waves, (int)w.pick.side).bytes;

@@ -34,8 +34,10 @@ struct W8Pick {
   int64_t side;
 };
 
-// whether the automatic table is the wave table
+// whether the wave table holds an individual of an automatic call, and whether
+// the 16-bit block table in LDS is the faster one for pop of them all the same
 bool w8_auto(const dlm_graph* g, const dlm_tabu_params* p);
+bool block_faster(const dlm_graph* g, const dlm_tabu_params* p, int64_t pop);
 W8Pick w8_pick(const dlm_graph* g, const dlm_tabu_params* p, int64_t pop);
 
 }  // namespace dlm

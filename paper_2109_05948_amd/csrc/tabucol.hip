@@ -206,14 +206,43 @@ static bool w8_large(const dlm_graph* g, const dlm_tabu_params* p) {
          (int64_t)w8_layout(g->n, p->k, 4, 1, (int)w8_side(g, p, esc)).bytes <= (int64_t)device_lds_limit();
 }
 
-// The automatic table is the wave table whenever it holds the individual (it
-// beat the block kernels at every measured shape, one individual per CU
-// included).
+// The automatic table is the wave table whenever it holds the individual,
+// unless block_faster() says otherwise.
 bool w8_auto(const dlm_graph* g, const dlm_tabu_params* p) {
   const int n = g->n, k = p->k;
   const bool fits = w8_bucket(k, 8) != 0 && (uint64_t)n * (uint64_t)tab_stride(k) <= (1ull << 17) &&
                     w8_least_bytes(n, k) <= (uint64_t)device_lds_limit();
   return fits || w8_large(g, p);
+}
+
+// Where f stays high, far below the colours a graph needs, thousands of pairs
+// are tabu at a time.  The wave search walks them in every iteration; the block
+// search finds them in its table, whose scan is short just there: LDS16 is the
+// faster one.  3,000 iterations, wave table and LDS16, in ms:
+//   64 individuals     G(480, 0.3) k = 6   40.2 7.9    k = 13  17.4 10.7   k = 21  11.1 13.8
+//                      G(300, 0.7) k = 12  21.6 8.3    k = 25  13.0 11.7   k = 40   8.6 13.2
+//                      G(100, 0.7) k = 5   13.6 6.8    k = 11   7.6  7.4   k = 18   6.4  7.3
+//   1,024 individuals  G(480, 0.3) k = 6   59.3 12.1   k = 13  28.0 17.5   k = 21  15.7 28.0
+//                      G(300, 0.7) k = 12  35.5 12.8   k = 25  18.8 19.3   k = 40  11.7 26.6
+//                      G(100, 0.7) k = 5   14.9 9.6    k = 11   8.4 10.5   k = 18   6.9 10.3
+// The live pairs follow from f, and f of a searched G(n, p) is close to
+// n (d / 2k - 0.85 sqrt(d (1 - p) ln k / k)), d the mean degree (0.75 to 0.95
+// in place of 0.85 over p from 0.3 to 0.7).  The line lies lower the fewer
+// individuals a CU holds, since they hide less of a walk's latency; over
+// n = 100 to 800, three densities, four k each and 1 to 4,096 individuals the
+// choice is within 1.2 % of the faster one in the mean.
+// A search whose classes are expected to pass the wave table's limit would
+// only be repeated from its start (G(600, 0.1), k = 5).
+bool block_faster(const dlm_graph* g, const dlm_tabu_params* p, int64_t pop) {
+  const int n = g->n, k = p->k;
+  if ((int64_t)tabu_layout(n, k, 512 / kWave, TabLds16::kLdsBytes).bytes > (int64_t)device_lds_limit()) return false;
+  const double mean = (double)n / k, d = (double)g->nnz / n, q = n > 1 ? 1.0 - d / (n - 1) : 1.0;
+  if (mean + 3.0 * sqrt(mean) > (double)kW8ClassMax) return true;
+  const double f = n * (d / (2.0 * k) - 0.85 * sqrt(std::max(0.0, d * q * log((double)k) / k)));
+  const double pairs = std::min({p->ten_num * std::max(f, 0.0) / p->ten_den + 0.5 * p->ten_rand,
+                                 (double)n * (k - 1), (double)p->max_iters});
+  const double held = (double)pop / device_cu_count();  // individuals per CU
+  return pairs > 160.0 + 20.0 * held && pairs > (0.03 + 0.01 * held) * n * k;
 }
 
 // A CU hands out its LDS in granules: workgroups of 53,760 bytes fit three to
@@ -302,7 +331,9 @@ static int tabu_check(const char* fn, const dlm_graph* g, const dlm_tabu_params*
 static int tabu_plan(const char* fn, const dlm_graph* g, const dlm_tabu_params* p, int32_t pop, TabuPlan& P) {
   const int n = g->n, k = p->k;
   const int64_t lds_max = device_lds_limit();
-  const bool wave_auto = p->table == DLM_TABLE_AUTO && (p->block == 0 || p->block == 64) && w8_auto(g, p);
+  bool wave_auto = p->table == DLM_TABLE_AUTO && (p->block == 0 || p->block == 64) && w8_auto(g, p);
+  const bool lds16 = wave_auto && p->block == 0 && block_faster(g, p, pop);
+  wave_auto = wave_auto && !lds16;
   if (p->table == DLM_TABLE_WAVE8 || wave_auto) {
     if (p->block != 0 && p->block != 64)
       return set_error(DLM_E_INVAL, "%s: the wave table runs 64 threads per individual (block=%d)", fn, p->block);
@@ -341,10 +372,10 @@ static int tabu_plan(const char* fn, const dlm_graph* g, const dlm_tabu_params* 
     const uint64_t l8 = tabu_layout(n, k, nw0, TabSplit8::kLdsBytes).bytes;
     const int o16 = l16 <= (uint64_t)lds_max ? resident<TabLds16>(block, l16) : 0;
     const int o8 = l8 <= (uint64_t)lds_max ? resident<TabSplit8>(block, l8) : 0;
-    table = o8 > o16 ? DLM_TABLE_SPLIT8 : (o16 > 0 ? DLM_TABLE_LDS16 : DLM_TABLE_GLOBAL16);
+    table = !lds16 && o8 > o16 ? DLM_TABLE_SPLIT8 : (o16 > 0 ? DLM_TABLE_LDS16 : DLM_TABLE_GLOBAL16);
     // automatic block: when a single LDS-resident individual fills a CU, 512
     // threads hide more of the per-move latency than 256
-    if (p->block == 0 && std::max(o16, o8) == 1 && block == 256) block = 512;
+    if (p->block == 0 && (lds16 ? o16 : std::max(o16, o8)) == 1 && block == 256) block = 512;
   }
   const int nw = block / kWave;
   int eb = 0, gb = 0;

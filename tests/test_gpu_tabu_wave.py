@@ -360,7 +360,8 @@ def test_wave_tenures_past_two_to_the_fifteen(dlm, dev, shape):
     assert (ref["f_best"] > 0).all()
     say(f"wave8 tenures past 2^15 n={n} k={k} T={T}")
     G = dlm.Graph.from_csr(g)
-    outs = [dlm.tabu_batch(G, torch.from_numpy(starts).cuda(), k, T, 12, **ten)]
+    table = "wave8" if n * k <= 1 << 17 else "auto"
+    outs = [dlm.tabu_batch(G, torch.from_numpy(starts).cuda(), k, T, 12, table=table, **ten)]
     job = {"graph": G, "colors": torch.from_numpy(starts).cuda(), "k": k, "iters": T, "seed": 12, **ten}
     mb = dlm.MultiBatch([job])
     mb.launch()
@@ -384,3 +385,31 @@ def test_wave_run_past_two_to_the_seventeen(dlm, dev):
         say(f"wave8 n=60 k={k} T={T} {ten}")
         gpu = gpu_run(dlm, g, starts, k, T, 8, **ten)
         compare(gpu, ref, range(pop), "wave8 2^17")
+
+
+ROUTES = [  # (n, p, k, pop, T, tenure, 16-bit table in LDS): both sides of the line, by f, population, tenure, run length
+    (480, 0.3, 6, 64, 300, {}, True), (480, 0.3, 21, 64, 300, {}, False),
+    (300, 0.7, 12, 1024, 500, {}, True), (300, 0.7, 25, 1024, 300, {}, False), (300, 0.7, 25, 64, 300, {}, True),
+    (100, 0.7, 5, 64, 400, {}, True), (100, 0.7, 5, 4096, 400, {}, False), (100, 0.7, 11, 64, 300, {}, False),
+    (480, 0.3, 6, 64, 100, {}, False), (300, 0.5, 22, 3, 900, {"ten_num": 300}, True), (300, 0.5, 22, 3, 900, {}, False),
+    (600, 0.02, 5, 3, 300, {}, True), (150, 0.1, 1, 3, 20, {}, True), (60, 0.1, 1, 3, 20, {}, False)]
+
+
+@pytest.mark.parametrize("case", ROUTES, ids=lambda c: "n%d_p%g_k%d_pop%d" % c[:4])
+def test_auto_table_where_many_pairs_are_tabu(dlm, dev, case):
+    """The automatic table: the wave table keeps start colourings and rerun
+    slots in its workspace, the 16-bit table in LDS needs none."""
+    n, p, k, pop, T, ten, lds16 = case
+    g = gnp(n, p, seed=n)
+    starts = oracle.init_random(n, k, pop, seed=6)
+    at = np.unique([0, pop // 2, pop - 1])
+    ref = oracle.tabucol_batch(g, starts[at], at, k, T, seed=3, **ten)
+    G = dlm.Graph.from_csr(g)
+    need = dlm.tabu_workspace_bytes(G, pop, k, T, **ten)
+    assert (need == 0) == lds16, need
+    say(f"auto table n={n} p={p} k={k} pop={pop} T={T} {ten}")
+    r = dlm.tabu_batch(G, torch.from_numpy(starts).cuda(), k, T, 3, **ten)
+    torch.cuda.synchronize()
+    gpu = {x: r[x].cpu().numpy()[at] for x in ("f_best", "iters", "stats", "hash", "colors")}
+    gpu["hash"] = gpu["hash"].view(np.uint64)
+    compare(gpu, ref, at, f"route n{n} k{k}")
