@@ -158,6 +158,7 @@ struct TabuPlan {
   int32_t acap = 0;           // WAVE8: side-list entries each individual's LDS holds
   int bits = 8;               // WAVE8: bits per table entry
   uint64_t ws_bytes = 0;      // total, each part on a 256-byte boundary
+  uint64_t ws_ask = 0;        // what dlm_tabu_workspace_bytes reports: enough for either automatic table
 };
 
 // LDS bytes that bound what the wave table serves: a byte per (v, c), 8 bytes
@@ -328,12 +329,35 @@ static int tabu_check(const char* fn, const dlm_graph* g, const dlm_tabu_params*
   return DLM_OK;
 }
 
+// The wave table's start colourings and rerun slots.
+static void w8_workspace(int n, int k, int32_t pop, TabuPlan& P) {
+  if (pop > 0) {
+    P.slot_bytes = tab_entries(n, k) * TabGlobal16::kGlobalBytes;
+    int64_t slots = std::min<int64_t>(pop, 2 * (int64_t)device_cu_count());
+    P.slots = std::max<int64_t>(1, std::min<int64_t>(slots, (int64_t)((1ull << 30) / std::max<uint64_t>(P.slot_bytes, 1))));
+    P.lds_rr = tabu_layout(n, k, 256 / kWave, TabGlobal16::kLdsBytes).bytes;
+    P.start_bytes = sizeof(int16_t) * (uint64_t)pop * (uint64_t)n;
+    // beyond 2^17 entries never more than the device-memory tables of the whole population
+    if ((uint64_t)n * (uint64_t)tab_stride(k) > (1ull << 17)) {
+      const uint64_t whole = P.slot_bytes * (uint64_t)pop, start = align256(P.start_bytes) + 255u;
+      const int64_t left = whole > start ? (int64_t)((whole - start) / P.slot_bytes) : 0;
+      P.slots = std::max<int64_t>(1, std::min(P.slots, left));
+    }
+  }
+  P.ws_bytes = align256(P.start_bytes) + align256(P.slot_bytes * (uint64_t)P.slots);
+}
+
 static int tabu_plan(const char* fn, const dlm_graph* g, const dlm_tabu_params* p, int32_t pop, TabuPlan& P) {
   const int n = g->n, k = p->k;
   const int64_t lds_max = device_lds_limit();
   bool wave_auto = p->table == DLM_TABLE_AUTO && (p->block == 0 || p->block == 64) && w8_auto(g, p);
   const bool lds16 = wave_auto && p->block == 0 && block_faster(g, p, pop);
   wave_auto = wave_auto && !lds16;
+  if (lds16) {  // the choice depends on max_iters and the tenure, what a caller sets aside must not
+    TabuPlan wave;
+    w8_workspace(n, k, pop, wave);
+    P.ws_ask = wave.ws_bytes;
+  }
   if (p->table == DLM_TABLE_WAVE8 || wave_auto) {
     if (p->block != 0 && p->block != 64)
       return set_error(DLM_E_INVAL, "%s: the wave table runs 64 threads per individual (block=%d)", fn, p->block);
@@ -345,20 +369,8 @@ static int tabu_plan(const char* fn, const dlm_graph* g, const dlm_tabu_params* 
                        (unsigned long long)w8_least_bytes(n, k), (long long)lds_max);
     w8_shape(g, p, pop, P);
     P.table = DLM_TABLE_WAVE8;
-    if (pop > 0) {
-      P.slot_bytes = tab_entries(n, k) * TabGlobal16::kGlobalBytes;
-      int64_t slots = std::min<int64_t>(pop, 2 * (int64_t)device_cu_count());
-      P.slots = std::max<int64_t>(1, std::min<int64_t>(slots, (int64_t)((1ull << 30) / std::max<uint64_t>(P.slot_bytes, 1))));
-      P.lds_rr = tabu_layout(n, k, 256 / kWave, TabGlobal16::kLdsBytes).bytes;
-      P.start_bytes = sizeof(int16_t) * (uint64_t)pop * (uint64_t)n;
-      // beyond 2^17 entries never more than the device-memory tables of the whole population
-      if ((uint64_t)n * kp > (1ull << 17)) {
-        const uint64_t whole = P.slot_bytes * (uint64_t)pop, start = align256(P.start_bytes) + 255u;
-        const int64_t left = whole > start ? (int64_t)((whole - start) / P.slot_bytes) : 0;
-        P.slots = std::max<int64_t>(1, std::min(P.slots, left));
-      }
-    }
-    P.ws_bytes = align256(P.start_bytes) + align256(P.slot_bytes * (uint64_t)P.slots);
+    w8_workspace(n, k, pop, P);
+    P.ws_ask = P.ws_bytes;
     return DLM_OK;
   }
   int block = p->block ? p->block : 256;
@@ -403,6 +415,7 @@ static int tabu_plan(const char* fn, const dlm_graph* g, const dlm_tabu_params* 
     P.start_bytes = sizeof(int16_t) * (uint64_t)pop * (uint64_t)n;
   }
   P.ws_bytes = align256(P.gtab_bytes) + align256(P.start_bytes) + align256(P.slot_bytes * (uint64_t)P.slots);
+  P.ws_ask = std::max(P.ws_ask, P.ws_bytes);
   return DLM_OK;
 }
 
@@ -501,7 +514,7 @@ extern "C" int dlm_tabu_workspace_bytes(const dlm_graph* g, const dlm_tabu_param
   if (rc != DLM_OK) return rc;
   TabuPlan P;
   if ((rc = tabu_plan("dlm_tabu_workspace_bytes", g, p, pop, P)) != DLM_OK) return rc;
-  *bytes = (size_t)P.ws_bytes;
+  *bytes = (size_t)P.ws_ask;
   return DLM_OK;
 }
 

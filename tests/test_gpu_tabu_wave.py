@@ -397,18 +397,22 @@ ROUTES = [  # (n, p, k, pop, T, tenure, 16-bit table in LDS): both sides of the 
 
 @pytest.mark.parametrize("case", ROUTES, ids=lambda c: "n%d_p%g_k%d_pop%d" % c[:4])
 def test_auto_table_where_many_pairs_are_tabu(dlm, dev, case):
-    """The automatic table: the wave table keeps start colourings and rerun
-    slots in its workspace, the 16-bit table in LDS needs none."""
+    """The automatic table: the wave table refuses a call without workspace (it
+    holds start colourings and rerun slots), the 16-bit table in LDS needs
+    none; the workspace asked for is the same whatever the run's length."""
     n, p, k, pop, T, ten, lds16 = case
     g = gnp(n, p, seed=n)
     starts = oracle.init_random(n, k, pop, seed=6)
     at = np.unique([0, pop // 2, pop - 1])
     ref = oracle.tabucol_batch(g, starts[at], at, k, T, seed=3, **ten)
     G = dlm.Graph.from_csr(g)
-    need = dlm.tabu_workspace_bytes(G, pop, k, T, **ten)
-    assert (need == 0) == lds16, need
+    assert dlm.tabu_workspace_bytes(G, pop, k, T, **ten) == dlm.tabu_workspace_bytes(G, pop, k, 1, table="wave8")
+    none = torch.empty(0, dtype=torch.uint8, device="cuda")
+    if not lds16:
+        with pytest.raises(dlm.DlmError):
+            dlm.tabu_batch(G, torch.from_numpy(starts).cuda(), k, T, 3, workspace=none, **ten)
     say(f"auto table n={n} p={p} k={k} pop={pop} T={T} {ten}")
-    r = dlm.tabu_batch(G, torch.from_numpy(starts).cuda(), k, T, 3, **ten)
+    r = dlm.tabu_batch(G, torch.from_numpy(starts).cuda(), k, T, 3, workspace=none if lds16 else None, **ten)
     torch.cuda.synchronize()
     gpu = {x: r[x].cpu().numpy()[at] for x in ("f_best", "iters", "stats", "hash", "colors")}
     gpu["hash"] = gpu["hash"].view(np.uint64)
