@@ -197,11 +197,22 @@ static int64_t w8_side(const dlm_graph* g, const dlm_tabu_params* p, double esc)
   return std::min<int64_t>(16384, (want + 63) & ~63ll);
 }
 
+// Whether the largest of k random classes (about the mean and 2 to 3 of its
+// roots) passes the wave table's limit: such a search is only repeated with
+// the 16-bit table.
+static bool w8_classes_pass(int n, int k) {
+  const double mean = (double)n / k;
+  return mean + 3.0 * sqrt(mean) > (double)kW8ClassMax;
+}
+
 // Tables of more than 2^17 bytes fit the LDS with 4-bit entries only: the
 // automatic table takes the wave tier there too when few entries escape
-// (G(1000, 0.9) with k = 220: 112 KB; its byte table would be in device memory).
+// (G(1000, 0.9) with k = 220: 112 KB; its byte table would be in device
+// memory) and the classes stay small: 256 individuals x 1,500 iterations on
+// 4,000 vertices of degree 30, k = 45 (89 a class), 75 ms in device memory and
+// 15 on the wave tier; 4 of them on 5,500 of degree 20, k = 40 (137), 59 and 112.
 static bool w8_large(const dlm_graph* g, const dlm_tabu_params* p) {
-  if (!g->ell || w8_bucket(p->k, 4) == 0) return false;
+  if (!g->ell || w8_bucket(p->k, 4) == 0 || w8_classes_pass(g->n, p->k)) return false;
   const double esc = w8_escapes(g, p->k);
   return esc <= kW4Escapes &&
          (int64_t)w8_layout(g->n, p->k, 4, 1, (int)w8_side(g, p, esc)).bytes <= (int64_t)device_lds_limit();
@@ -237,8 +248,8 @@ bool w8_auto(const dlm_graph* g, const dlm_tabu_params* p) {
 bool block_faster(const dlm_graph* g, const dlm_tabu_params* p, int64_t pop) {
   const int n = g->n, k = p->k;
   if ((int64_t)tabu_layout(n, k, 512 / kWave, TabLds16::kLdsBytes).bytes > (int64_t)device_lds_limit()) return false;
-  const double mean = (double)n / k, d = (double)g->nnz / n, q = n > 1 ? 1.0 - d / (n - 1) : 1.0;
-  if (mean + 3.0 * sqrt(mean) > (double)kW8ClassMax) return true;
+  if (w8_classes_pass(n, k)) return true;
+  const double d = (double)g->nnz / n, q = n > 1 ? 1.0 - d / (n - 1) : 1.0;
   const double f = n * (d / (2.0 * k) - 0.85 * sqrt(std::max(0.0, d * q * log((double)k) / k)));
   const double pairs = std::min({p->ten_num * std::max(f, 0.0) / p->ten_den + 0.5 * p->ten_rand,
                                  (double)n * (k - 1), (double)p->max_iters});

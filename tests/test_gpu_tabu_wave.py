@@ -417,3 +417,24 @@ def test_auto_table_where_many_pairs_are_tabu(dlm, dev, case):
     gpu = {x: r[x].cpu().numpy()[at] for x in ("f_best", "iters", "stats", "hash", "colors")}
     gpu["hash"] = gpu["hash"].view(np.uint64)
     compare(gpu, ref, at, f"route n{n} k{k}")
+
+
+@pytest.mark.parametrize("n,k,d,wave", [(5500, 40, 20, False), (4000, 45, 30, True)])
+def test_auto_table_beyond_two_to_the_seventeen_by_class_size(dlm, dev, n, k, d, wave):
+    """Tables that only 4-bit entries bring into the LDS: classes of 137
+    vertices in the mean cannot stay within the wave table's 127, classes of
+    89 can.  The device-memory table of two individuals asks for exactly
+    their two tables, the wave table for one slot less and the starts."""
+    g = gnp(n, d / n, seed=3)
+    G = dlm.Graph.from_csr(g)
+    T, pop = 150, 2
+    auto, device = (dlm.tabu_workspace_bytes(G, pop, k, T, table=t) for t in ("auto", "global16"))
+    assert (auto < device) == wave, (auto, device)
+    starts = oracle.init_random(n, k, pop, seed=6)
+    ref = oracle.tabucol_batch(g, starts, np.arange(pop), k, T, seed=3)
+    say(f"auto table n={n} k={k} d={d}")
+    r = dlm.tabu_batch(G, torch.from_numpy(starts).cuda(), k, T, 3)
+    torch.cuda.synchronize()
+    gpu = {x: r[x].cpu().numpy() for x in ("f_best", "iters", "stats", "hash", "colors")}
+    gpu["hash"] = gpu["hash"].view(np.uint64)
+    compare(gpu, ref, range(pop), f"large n{n} k{k}")
