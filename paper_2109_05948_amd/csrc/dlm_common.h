@@ -165,7 +165,13 @@ int device_lds_per_cu();  // LDS bytes of one CU on the current device
     if (e_ != hipSuccess) return ::dlm::hip_fail(e_, #call); \
   } while (0)
 
-constexpr int kEllMaxVertices = 20480;  // 160 KB of LDS / 8 bytes: a row of 4 colours, its state and list entry
+// Padded rows are built up to this many vertices: with more, a table that fits
+// the LDS has classes beyond the 127 vertices that the wave searches hold
+// (n <= 127 k and n (k / 2 + 4) <= 160 KB end at 5,960) ...
+constexpr int kEllMaxVertices = 6144;
+// ... and up to so many entries (32 MB; every graph of 4,096 vertices), or four
+// times the graph's own: a few long rows would pad all the others.
+constexpr int64_t kEllCells = 1 << 24;
 
 }  // namespace dlm
 
@@ -178,8 +184,8 @@ struct dlm_graph {
   int32_t* row_ptr = nullptr;  // device int32[n+1]
   int32_t* col_idx = nullptr;  // device int32[nnz]
   int32_t* erow = nullptr;     // device int32[nnz]: source vertex of each CSR entry
-  // Two more forms of the adjacency, null above kEllMaxVertices, where no wave
-  // table fits the LDS:
+  // Two more forms of the adjacency, for the searches with a wave per
+  // individual; both null where kEllMaxVertices and kEllCells leave them out:
   // device uint16[n][ell_stride], the neighbours of v, then n + 1 (at least once).
   // Rows start on 128-byte lines, so a row's address needs no row_ptr and a row
   // of 250 neighbours is 4 lines instead of 9;

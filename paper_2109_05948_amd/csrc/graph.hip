@@ -252,14 +252,21 @@ int dlm_graph_create(int32_t n, const int32_t* row_ptr, const int32_t* col_idx,
     if ((e = upload(&g->weights, weights, n)) != hipSuccess) return fail(e, "graph upload (weights)");
     if ((e = upload(&g->order, order.data(), n)) != hipSuccess) return fail(e, "graph upload (order)");
   }
-  if (n <= kEllMaxVertices) {
-    g->ell_stride = (max_deg + 64) & ~63;
-    if ((e = hipMalloc(&g->ell, sizeof(uint16_t) * (size_t)n * (size_t)g->ell_stride)) != hipSuccess ||
-        (e = hipMalloc(&g->adj, sizeof(uint32_t) * (size_t)n * (size_t)(2 * (n / 64 + 1)))) != hipSuccess)
-      return fail(e, "graph upload (adjacency)");
-    hipLaunchKernelGGL(adjacency_kernel, dim3((unsigned)n), dim3(64), 0, s, g->row_ptr, g->col_idx, n, g->ell_stride,
-                       g->ell, g->adj);
-    if ((e = hipGetLastError()) != hipSuccess) return fail(e, "graph upload (adjacency)");
+  const int64_t stride = (max_deg + 64) & ~63;
+  if (n <= kEllMaxVertices && n * stride <= std::max<int64_t>(kEllCells, 4 * nnz)) {
+    g->ell_stride = (int32_t)stride;
+    if (hipMalloc(&g->ell, sizeof(uint16_t) * (size_t)(n * stride)) == hipSuccess &&
+        hipMalloc(&g->adj, sizeof(uint32_t) * (size_t)n * (size_t)(2 * (n / 64 + 1))) == hipSuccess) {
+      hipLaunchKernelGGL(adjacency_kernel, dim3((unsigned)n), dim3(64), 0, s, g->row_ptr, g->col_idx, n, g->ell_stride,
+                         g->ell, g->adj);
+      if ((e = hipGetLastError()) != hipSuccess) return fail(e, "graph upload (adjacency)");
+    } else {  // every search runs without them
+      (void)hipGetLastError();
+      (void)hipFree(g->ell);
+      g->ell = nullptr;
+      g->adj = nullptr;
+      g->ell_stride = 0;
+    }
   }
   // the host arrays (the caller's and the local ones) are read synchronously
   if ((e = hipStreamSynchronize(s)) != hipSuccess) return fail(e, "hipStreamSynchronize");

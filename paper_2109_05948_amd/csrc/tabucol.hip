@@ -72,6 +72,11 @@ __global__ void copy_i16_kernel(const int16_t* __restrict__ src, int16_t* __rest
   if (i < count) dst[i] = src[i];
 }
 
+__global__ void leave_to_rerun_kernel(int32_t* __restrict__ iters, int32_t count) {
+  const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (i < count) iters[i] = -2;
+}
+
 static int launch_w8(const TabuArgs& a, int pop, int bits, int nw, int acap, size_t lds, hipStream_t s) {
   if (bits == 4) switch (nw) {
       case 1: return launch_w4_1(a, pop, acap, lds, s);
@@ -465,7 +470,12 @@ static int tabu_run(const char* fn, const dlm_graph* g, const dlm_tabu_params* p
       hipLaunchKernelGGL(copy_i16_kernel, dim3((unsigned)((cells + 255) / 256)), dim3(256), 0, s, colors, start,
                          cells);
       DLM_HIP(hipGetLastError());
-      if ((rc = launch_w8(a, pop, P.bits, P.block / kWave, P.acap, P.lds, s)) != DLM_OK) return rc;
+      if (a.ell && n <= (int)kW8ClassMax * k) {
+        if ((rc = launch_w8(a, pop, P.bits, P.block / kWave, P.acap, P.lds, s)) != DLM_OK) return rc;
+      } else {  // no padded rows, or a class past the limit for certain: the rerun is the search
+        hipLaunchKernelGGL(leave_to_rerun_kernel, dim3((unsigned)((pop + 255) / 256)), dim3(256), 0, s, iters, pop);
+        DLM_HIP(hipGetLastError());
+      }
       const Rerun rr{start, slot_mem, (int32_t)P.slots};
       return launch_tab<TabGlobal16>(a, pop, 256, P.lds_rr, s, &rr);
     }

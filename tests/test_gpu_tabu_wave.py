@@ -438,3 +438,57 @@ def test_auto_table_beyond_two_to_the_seventeen_by_class_size(dlm, dev, n, k, d,
     gpu = {x: r[x].cpu().numpy() for x in ("f_best", "iters", "stats", "hash", "colors")}
     gpu["hash"] = gpu["hash"].view(np.uint64)
     compare(gpu, ref, range(pop), f"large n{n} k{k}")
+
+
+def star(n, leaves):
+    """Vertex 0 joined to ``leaves`` others, which form a path."""
+    e = [(0, v) for v in range(1, leaves + 1)] + [(v, v + 1) for v in range(1, leaves)]
+    return from_edges(n, np.array(e, np.int64), f"star{n}")
+
+
+def test_skewed_graph_takes_memory_by_its_entries(dlm, dev):
+    """20,000 vertices, 80,000 entries, one row of 19,999: rows padded to the
+    longest would take 800 MB."""
+    g = star(20000, 19999)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    G = dlm.Graph.from_csr(g)
+    took = free - torch.cuda.mem_get_info()[0]
+    say(f"star of 20,000: {took >> 10} KB")
+    assert took < 16 << 20, took
+    starts = oracle.init_random(g.n, 3, 2, seed=1)
+    conf, _ = dlm.evaluate(G, torch.from_numpy(starts).cuda(), 3)
+    ends = np.concatenate([[(0, v) for v in range(1, 20000)], [(v, v + 1) for v in range(1, 19999)]])
+    assert (conf.cpu().numpy() == (starts[:, ends[:, 0]] == starts[:, ends[:, 1]]).sum(1)).all()
+
+
+SKEWED = [  # (n, leaves, k, table): rows left out, with tables on both sides of 2^17 entries; rows kept
+    (7000, 6999, 4, "wave8"), (7000, 6999, 4, "auto"), (5000, 4500, 50, "auto"), (4000, 3990, 32, "wave8")]
+
+
+@pytest.mark.parametrize("case", SKEWED, ids=lambda c: "n%d_k%d_%s" % (c[0], c[2], c[3]))
+def test_wave_on_skewed_graphs(dlm, dev, case):
+    n, leaves, k, table = case
+    g = star(n, leaves)
+    T, pop = 300, 3
+    starts = oracle.init_random(n, k, pop, seed=1)
+    ref = oracle.tabucol_batch(g, starts, np.arange(pop), k, T, seed=2)
+    bad = starts.copy()
+    bad[1, n - 1] = k
+    G = dlm.Graph.from_csr(g)
+    say(f"star n={n} k={k} {table}")
+    for rep in range(2):
+        r = dlm.tabu_batch(G, torch.from_numpy(starts if rep == 0 else bad).cuda(), k, T, 2, table=table)
+        torch.cuda.synchronize()
+        gpu = {x: r[x].cpu().numpy() for x in ("f_best", "iters", "stats", "hash", "colors")}
+        gpu["hash"] = gpu["hash"].view(np.uint64)
+        at = np.array([0, 1, 2] if rep == 0 else [0, 2])
+        compare({x: gpu[x][at] for x in gpu}, {x: ref[x][at] for x in ("f_best", "iters", "stats", "hash", "colors")},
+                range(len(at)), f"star n{n} k{k}")
+        if rep == 1:
+            assert gpu["f_best"][1] == -1 and gpu["iters"][1] == -1
+    job = {"graph": G, "colors": torch.from_numpy(starts).cuda(), "k": k, "iters": T, "seed": 2}
+    mb = dlm.MultiBatch([job])
+    mb.launch()
+    torch.cuda.synchronize()
+    assert (job["hash"].cpu().numpy().view(np.uint64) == ref["hash"]).all()
