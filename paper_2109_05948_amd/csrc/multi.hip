@@ -87,8 +87,8 @@ __global__ __launch_bounds__(BLOCK) void tabu_multi_kernel(const MultiDesc* __re
   }
 }
 
-// What the wave table gave up on (iters = -2), from its saved start with the
-// packed 16-bit table in device memory, one slot per workgroup.
+// What the wave tables gave up on, from its saved start with the packed 16-bit
+// table in device memory, one slot per workgroup.
 template <int BLOCK>
 __global__ __launch_bounds__(BLOCK) void tabu_multi_rerun_kernel(const WaveDesc* __restrict__ descs, int32_t ndesc,
                                                                  int32_t total, unsigned char* __restrict__ slots,
@@ -100,7 +100,7 @@ __global__ __launch_bounds__(BLOCK) void tabu_multi_rerun_kernel(const WaveDesc*
     while (g + 1 < ndesc && descs[g + 1].first_item <= item) ++g;
     const WaveDesc& d = descs[g];
     const int li = item - d.first_item;
-    if (d.a.iters[li] != -2) continue;
+    if (d.a.iters[li] != kW8GaveUp) continue;
     const size_t row = (size_t)li * (size_t)d.a.n;
     for (int v = threadIdx.x; v < d.a.n; v += BLOCK) d.a.colors[row + v] = d.start[row + v];
     __syncthreads();
@@ -120,10 +120,12 @@ struct dlm_multi_plan {
   MultiDesc* d_descs = nullptr;
   uint32_t* d_queue = nullptr;
   uint32_t* d_slots = nullptr;
-  // the wave table's share: its descriptors by number of waves, descending
-  int32_t wdesc[4] = {0, 0, 0, 0};  // descriptors before class i (4, 2, 1 waves; the end)
-  int32_t witem[4] = {0, 0, 0, 0};  // items before class i
-  size_t wlds[3] = {0, 0, 0};
+  // the wave table's share: its descriptors by number of waves, descending,
+  // then those of the reruns with 8-bit entries
+  int32_t wdesc[5] = {0, 0, 0, 0, 0};  // descriptors before class i (4, 2, 1 waves; the reruns; the end)
+  int32_t witem[4] = {0, 0, 0, 0};     // items before class i
+  size_t wlds[4] = {0, 0, 0, 0};
+  int32_t again_items = 0;
   int32_t rr_grid = 0;
   size_t rr_lds = 0;
   int64_t rr_slot_bytes = 0;
@@ -278,6 +280,11 @@ int capture_plan(const dlm_multi_plan* p, const hipStream_t* cs, const hipEvent_
   }
   for (int c = 0; c < 3; ++c)
     if (items(c) > 0) DLM_HIP(hipStreamWaitEvent(cs[3], ev[c], 0));
+  if (p->again_items > 0) {
+    const int rc = launch_multi_w8_again(p->d_wdescs + p->wdesc[3], p->wdesc[4] - p->wdesc[3], p->again_items,
+                                         p->wlds[3], cs[3]);
+    if (rc != DLM_OK) return rc;
+  }
   if (p->rr_grid > 0) {
     auto kern = tabu_multi_rerun_kernel<kRerunBlock>;
     DLM_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p->rr_lds));
@@ -360,7 +367,7 @@ int dlm_multi_plan_create(const dlm_multi_item* items, int32_t count, const dlm_
   // the wave table's descriptors; an LDS of the class leaves the smaller
   // individuals of the class more side-list entries
   std::vector<WaveDesc> wdescs;
-  std::vector<size_t> start_at;
+  std::vector<size_t> start_at, wave_of;
   size_t start_cells = 0;
   int32_t witems = 0;
   for (int c = 0; c < 3; ++c) {
@@ -369,8 +376,10 @@ int dlm_multi_plan_create(const dlm_multi_item* items, int32_t count, const dlm_
     p->witem[c] = witems;
     for (const WaveItem& w : wave)
       if (w.pick.waves == nwv) p->wlds[c] = std::max(p->wlds[c], (size_t)w.least);
-    for (const WaveItem& w : wave) {
+    for (size_t wi = 0; wi < wave.size(); ++wi) {
+      const WaveItem& w = wave[wi];
       if (w.pick.waves != nwv) continue;
+      wave_of.push_back(wi);
       const dlm_multi_item& it = items[w.oi];
       const int n = it.g->n;
       WaveDesc d{};
@@ -378,7 +387,11 @@ int dlm_multi_plan_create(const dlm_multi_item* items, int32_t count, const dlm_
                      it.stats_dev, it.hash_dev, nullptr, nullptr, make_key(it.seed), n, it.k, it.max_iters,
                      it.ten_num, it.ten_den, it.ten_rand, it.ind_base, 0, it.g->ell, it.g->adj, it.g->ell_stride};
       const int64_t room = (int64_t)p->wlds[c] - (int64_t)w8_layout(n, it.k, w.pick.bits, nwv, 0).bytes;
-      d.acap = (int32_t)std::max<int64_t>(w.pick.side, std::min<int64_t>(16384, (room / 6) & ~63ll));
+      W8Pick b;
+      const dlm_tabu_params q = item_params(it);
+      const bool again = w.pick.bits == 4 && w8_pick_bytes(it.g, &q, it.pop, b);
+      const int64_t most = again ? w.pick.side + kW4Spare : kW8SideMax;
+      d.acap = (int32_t)std::max<int64_t>(w.pick.side, std::min<int64_t>(most, (room / 6) & ~63ll));
       d.instance = w.instance;
       d.first_item = witems;
       d.pop = it.pop;
@@ -392,6 +405,26 @@ int dlm_multi_plan_create(const dlm_multi_item* items, int32_t count, const dlm_
     p->info_lds = std::max(p->info_lds, p->wlds[c]);
   }
   p->wdesc[3] = (int32_t)wdescs.size();
+  // reruns with 8-bit entries: few and late, so four waves each
+  for (int32_t i = 0; i < p->wdesc[3]; ++i) {
+    const WaveItem& w = wave[wave_of[i]];
+    const dlm_multi_item& it = items[w.oi];
+    const dlm_tabu_params q = item_params(it);
+    W8Pick b;
+    if (w.pick.bits != 4 || !w8_pick_bytes(it.g, &q, it.pop, b)) continue;
+    WaveDesc d = wdescs[i];
+    const int64_t room = std::min(budget, lds_max) - (int64_t)w8_layout(it.g->n, it.k, 8, 4, 0).bytes;
+    d.instance = w8_multi_instance(it.k, 8);
+    if (d.instance < 0 || room < 6 * kWave) continue;
+    d.acap = (int32_t)std::min<int64_t>(std::max<int64_t>(w.pick.side, kWave), (room / 6) & ~63ll);
+    d.first_item = p->again_items;
+    p->again_items += it.pop;
+    start_at.push_back(start_at[i]);
+    p->wlds[3] = std::max(p->wlds[3], (size_t)w8_layout(it.g->n, it.k, 8, 4, d.acap).bytes);
+    wdescs.push_back(d);
+  }
+  p->wdesc[4] = (int32_t)wdescs.size();
+  p->info_lds = std::max(p->info_lds, p->wlds[3]);
   p->witem[3] = witems;
   if (witems > 0)
     p->rr_grid = (int32_t)std::max<int64_t>(

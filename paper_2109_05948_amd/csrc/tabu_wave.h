@@ -27,8 +27,14 @@
 //   stage[w]    rows at the wave's best delta
 //   slot[w]     the wave's best move
 //   The colour class sizes live in registers of every wave (gamma <= class
-//   size <= 127 fits seven bits; a run that would pass it gives up with iters =
-//   -2 and is rerun with the 16-bit device table).
+//   size <= 127 fits seven bits).  A run that would pass it, or that finds no
+//   room in a list, gives up with iters = -2.  What 4-bit entries gave up on is
+//   run again with 8-bit entries where the LDS holds those: graphs whose
+//   vertices share neighbourhoods fill the table in ways that the rule for 4
+//   bits does not foresee (64 individuals x 3,000 iterations on 40 groups of 20
+//   vertices, k = 40: 15.0 ms without that run, 4.2 with it, 3.5 in bytes at once).  What is left is
+//   run with the 16-bit device table.  (One code for every reason: two of them
+//   moved the code about and cost one wave 2 %.)
 //
 // One iteration, two barriers (none for a single wave):
 //   scan   lane i takes list entry i of its wave (64 per round) and reads its
@@ -61,6 +67,7 @@ constexpr uint32_t kW8None = 255u;        // biased delta (delta + 128) of "no a
 constexpr uint32_t kW8ExpMask = 0x1ffffu;  // expiries are kept modulo 2^17: no tenure reaches it (32,757 + 1,023)
 constexpr uint32_t kW8NoKey = 0xffffffffu;
 constexpr uint32_t kW8Free = 0x80u;  // gamma of a side-list pair: not tabu
+constexpr int kW8GaveUp = -2;        // iters of a search that is left to a rerun
 constexpr int kW8Stage = 128;        // tied rows a wave stages: up to 64 waiting and 64 more
 constexpr int kW8Mail = 64;          // entries that can escape by growth in one move
 
@@ -227,7 +234,7 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
   // Written by every lane: a lane-masked store here would meet the search
   // loop's end in one block, and the compiler would then keep the loop's
   // uniform values (f, t, the lists' lengths) in vector registers.
-  auto give_up = [&]() { late()->iters[li] = -2; };
+  auto give_up = [&]() { late()->iters[li] = kW8GaveUp; };
 
   // 1. start colouring (rejected whole if a colour is outside [0, k)), class sizes
   int bad = 0;
@@ -395,7 +402,7 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
 
   while (t < T && f > 0) {
     if ((t & 63) == 0) {
-      if (rfl(*full)) {  // an entry was lost: left to the 16-bit rerun
+      if (rfl(*full)) {  // an entry was lost: left to a rerun
         give_up();
         return;
       }

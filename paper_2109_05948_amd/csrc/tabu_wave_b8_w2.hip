@@ -3,8 +3,8 @@
 
 namespace dlm {
 
-int launch_w8_2(const TabuArgs& a, int pop, int acap, size_t lds, hipStream_t s) {
-  return launch_w8_waves<8, 2>(a, pop, acap, lds, s);
+int launch_w8_2(const TabuArgs& a, int pop, int acap, size_t lds, hipStream_t s, const int16_t* again) {
+  return launch_w8_waves<8, 2>(a, pop, acap, lds, s, again);
 }
 
 }  // namespace dlm

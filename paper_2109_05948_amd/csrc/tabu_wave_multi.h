@@ -45,7 +45,9 @@ inline int w8_multi_instance(int k, int bits) {
 
 // Items are ordered longest first, so that the long chains start at once: a
 // batch lasts as long as its longest individual if the card holds them all.
-template <int NW>
+// AGAIN: only the individuals that 4-bit entries had no room for, from their
+// saved start (their descriptors here have 8-bit instances).
+template <int NW, bool AGAIN>
 __global__ __launch_bounds__(64 * NW) void tabu_multi_w8_kernel(const WaveDesc* __restrict__ descs, int32_t ndesc,
                                                                 int32_t base) {
   extern __shared__ __align__(16) unsigned char smem[];
@@ -61,25 +63,32 @@ __global__ __launch_bounds__(64 * NW) void tabu_multi_w8_kernel(const WaveDesc* 
 #pragma unroll
   for (size_t i = 0; i < sizeof(WaveDesc) / 4; ++i) reinterpret_cast<uint32_t*>(&d)[i] = ((words)at)[i];
   const int li = item - d.first_item;
-  // the start waits for a 16-bit rerun
+  // the start waits for a rerun, or this is one
+  if (AGAIN && (int)rfl((uint32_t)d.a.iters[li]) != kW8GaveUp) return;
   {
     const size_t row = (size_t)li * (size_t)d.a.n;
-    for (int v = threadIdx.x; v < d.a.n; v += 64 * NW) d.start[row + v] = d.a.colors[row + v];
+    for (int v = threadIdx.x; v < d.a.n; v += 64 * NW) {
+      if (AGAIN)
+        d.a.colors[row + v] = d.start[row + v];
+      else
+        d.start[row + v] = d.a.colors[row + v];
+    }
   }
   auto late = [at] { return (const TabuArgs*)own_u64(at); };  // a is the descriptor's first member
   switch (d.instance) {
 #define DLM_X(I, BITS, RW, RLO)                                           \
   case I:                                                                 \
-    tabu_w8_individual<BITS, NW, RW, RLO>(d.a, li, d.acap, smem, late);   \
+    if constexpr (!AGAIN || BITS == 8)                                    \
+      tabu_w8_individual<BITS, NW, RW, RLO>(d.a, li, d.acap, smem, late); \
     break;
     DLM_W8_MULTI(DLM_X)
 #undef DLM_X
   }
 }
 
-template <int NW>
+template <int NW, bool AGAIN>
 static int launch_multi_w8(const WaveDesc* descs, int ndesc, int base, int items, size_t lds, hipStream_t s) {
-  auto kern = tabu_multi_w8_kernel<NW>;
+  auto kern = tabu_multi_w8_kernel<NW, AGAIN>;
   DLM_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   hipLaunchKernelGGL(kern, dim3(items), dim3(64 * NW), lds, s, descs, ndesc, base);
   DLM_HIP(hipGetLastError());

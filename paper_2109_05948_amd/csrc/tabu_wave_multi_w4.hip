@@ -4,7 +4,7 @@
 namespace dlm {
 
 int launch_multi_w8_4(const WaveDesc* descs, int ndesc, int base, int items, size_t lds, hipStream_t s) {
-  return launch_multi_w8<4>(descs, ndesc, base, items, lds, s);
+  return launch_multi_w8<4, false>(descs, ndesc, base, items, lds, s);
 }
 
 }  // namespace dlm

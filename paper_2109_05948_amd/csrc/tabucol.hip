@@ -58,7 +58,7 @@ __global__ __launch_bounds__(BLOCK) void tabucol_rerun_kernel(TabuArgs a, const 
   extern __shared__ __align__(16) unsigned char smem[];
   unsigned char* slot = slots + (size_t)blockIdx.x * (size_t)tab_entries(a.n, a.k) * TabGlobal16::kGlobalBytes;
   for (int li = blockIdx.x; li < pop; li += gridDim.x) {
-    if (a.iters[li] != -2) continue;
+    if (a.iters[li] != kW8GaveUp) continue;
     int16_t* gcol = a.colors + (size_t)li * a.n;
     for (int v = threadIdx.x; v < a.n; v += BLOCK) gcol[v] = start[(size_t)li * a.n + v];
     __syncthreads();
@@ -77,16 +77,26 @@ __global__ void leave_to_rerun_kernel(int32_t* __restrict__ iters, int32_t count
   if (i < count) iters[i] = -2;
 }
 
-static int launch_w8(const TabuArgs& a, int pop, int bits, int nw, int acap, size_t lds, hipStream_t s) {
-  if (bits == 4) switch (nw) {
+// How a WAVE8 launch runs its individuals: bits per table entry, waves per
+// individual, side-list entries that its LDS holds.
+struct W8Shape {
+  int bits = 8, waves = 1;
+  int32_t acap = 0;
+  uint64_t lds = 0;
+};
+
+static int launch_w8(const TabuArgs& a, int pop, const W8Shape& w, hipStream_t s, const int16_t* again) {
+  const int nw = w.waves, acap = w.acap;
+  const size_t lds = (size_t)w.lds;
+  if (w.bits == 4) switch (nw) {
       case 1: return launch_w4_1(a, pop, acap, lds, s);
       case 2: return launch_w4_2(a, pop, acap, lds, s);
       default: return launch_w4_4(a, pop, acap, lds, s);
     }
   switch (nw) {
-    case 1: return launch_w8_1(a, pop, acap, lds, s);
-    case 2: return launch_w8_2(a, pop, acap, lds, s);
-    default: return launch_w8_4(a, pop, acap, lds, s);
+    case 1: return launch_w8_1(a, pop, acap, lds, s, again);
+    case 2: return launch_w8_2(a, pop, acap, lds, s, again);
+    default: return launch_w8_4(a, pop, acap, lds, s, again);
   }
 }
 
@@ -160,8 +170,7 @@ struct TabuPlan {
   uint64_t start_bytes = 0;   // SPLIT8: copy of the start colourings
   uint64_t slot_bytes = 0;    // SPLIT8: one rerun slot (packed 16-bit table)
   int64_t slots = 0;          // SPLIT8: rerun slots
-  int32_t acap = 0;           // WAVE8: side-list entries each individual's LDS holds
-  int bits = 8;               // WAVE8: bits per table entry
+  W8Shape wave, bytes;        // WAVE8: the search, and the rerun with 8-bit entries if there is one (acap > 0)
   uint64_t ws_bytes = 0;      // total, each part on a 256-byte boundary
   uint64_t ws_ask = 0;        // what dlm_tabu_workspace_bytes reports: enough for either automatic table
 };
@@ -173,6 +182,12 @@ static uint64_t w8_least_bytes(int n, int k) {
   const uint32_t kp = (uint32_t)tab_stride(k);
   return (uint64_t)align16((uint32_t)(n + 1) * kp) + align16(2u * (uint32_t)(n + 1)) + align16(2u * (uint32_t)n) +
          align16((uint32_t)n) + 4u * 320u + align16(2u * kp) + 16u + 4u * kWave;
+}
+
+// A byte per (v, c), as the tier's bound on shapes has it.
+static bool w8_bytes_fit(int n, int k) {
+  return w8_bucket(k, 8) != 0 && (uint64_t)n * (uint64_t)tab_stride(k) <= (1ull << 17) &&
+         w8_least_bytes(n, k) <= (uint64_t)device_lds_limit();
 }
 
 // Table entries of a colouring of k random classes that reach 15: the number
@@ -199,7 +214,7 @@ static int64_t w8_side(const dlm_graph* g, const dlm_tabu_params* p, double esc)
   const int64_t f0 = g->nnz / 2 / p->k;
   int64_t want = 6 * p->ten_num * f0 / (10 * (int64_t)p->ten_den) + p->ten_rand + 32;
   if (esc <= kW4Escapes) want += (int64_t)(2.0 * esc) + 32;
-  return std::min<int64_t>(16384, (want + 63) & ~63ll);
+  return std::min<int64_t>(kW8SideMax, (want + 63) & ~63ll);
 }
 
 // Whether the largest of k random classes (about the mean and 2 to 3 of its
@@ -226,10 +241,7 @@ static bool w8_large(const dlm_graph* g, const dlm_tabu_params* p) {
 // The automatic table is the wave table whenever it holds the individual,
 // unless block_faster() says otherwise.
 bool w8_auto(const dlm_graph* g, const dlm_tabu_params* p) {
-  const int n = g->n, k = p->k;
-  const bool fits = w8_bucket(k, 8) != 0 && (uint64_t)n * (uint64_t)tab_stride(k) <= (1ull << 17) &&
-                    w8_least_bytes(n, k) <= (uint64_t)device_lds_limit();
-  return fits || w8_large(g, p);
+  return w8_bytes_fit(g->n, p->k) || w8_large(g, p);
 }
 
 // Where f stays high, far below the colours a graph needs, thousands of pairs
@@ -294,12 +306,11 @@ static int64_t w8_resident(const dlm_graph* g, int k, int64_t pop, int bits, int
 // come.  Where the LDS of their lists costs residents they still pay as long
 // as the population passes through the CUs in about as many turns (G(900,
 // 0.75), 1,024 individuals: 184 157 139).
-W8Pick w8_pick(const dlm_graph* g, const dlm_tabu_params* p, int64_t pop) {
+static W8Pick w8_pick_waves(const dlm_graph* g, const dlm_tabu_params* p, int64_t pop, int bits, int64_t side) {
   const int n = g->n, k = p->k;
   W8Pick r;
-  const double esc = w8_escapes(g, k);
-  r.bits = esc <= kW4Escapes ? 4 : 8;
-  r.side = w8_side(g, p, esc);
+  r.bits = bits;
+  r.side = side;
   const int64_t cus = device_cu_count(), share = (std::max<int64_t>(pop, 1) + cus - 1) / cus;
   auto resident = [&](int w) { return w8_resident(g, k, pop, r.bits, r.side, w); };
   auto turns = [&](int64_t held) { return (share + held - 1) / held; };
@@ -313,17 +324,28 @@ W8Pick w8_pick(const dlm_graph* g, const dlm_tabu_params* p, int64_t pop) {
   return r;
 }
 
+W8Pick w8_pick(const dlm_graph* g, const dlm_tabu_params* p, int64_t pop) {
+  const double esc = w8_escapes(g, p->k);
+  return w8_pick_waves(g, p, pop, esc <= kW4Escapes ? 4 : 8, w8_side(g, p, esc));
+}
+
+bool w8_pick_bytes(const dlm_graph* g, const dlm_tabu_params* p, int64_t pop, W8Pick& r) {
+  if (!w8_bytes_fit(g->n, p->k)) return false;
+  r = w8_pick_waves(g, p, pop, 8, w8_side(g, p, kW4Escapes + 1.0));
+  return (int64_t)w8_layout(g->n, p->k, 8, r.waves, kWave).bytes <= (int64_t)device_lds_limit();
+}
+
 // ... and its LDS: as many individuals per CU as the table allows; the rest
-// of their share of the CU's LDS holds side-list entries.
-static void w8_shape(const dlm_graph* g, const dlm_tabu_params* p, int pop, TabuPlan& P) {
-  const int n = g->n, k = p->k;
-  const W8Pick w = w8_pick(g, p, pop);
+// of their share of the CU's LDS holds side-list entries, at most `most` of them.
+static W8Shape w8_shape(const dlm_graph* g, int k, int pop, const W8Pick& w, int64_t most) {
   const int64_t per_cu = std::max<int64_t>(1, w8_resident(g, k, pop, w.bits, w.side, w.waves));
   const int64_t budget = std::min<int64_t>(device_lds_limit(), device_lds_per_cu() / kLdsGranule / per_cu * kLdsGranule);
-  P.bits = w.bits;
-  P.acap = (int32_t)std::min<int64_t>(16384, ((budget - (int64_t)w8_layout(n, k, w.bits, w.waves, 0).bytes) / 6) & ~63ll);
-  P.block = w.waves * kWave;
-  P.lds = w8_layout(n, k, w.bits, w.waves, P.acap).bytes;
+  W8Shape r;
+  r.bits = w.bits;
+  r.waves = w.waves;
+  r.acap = (int32_t)std::min<int64_t>(most, ((budget - (int64_t)w8_layout(g->n, k, w.bits, w.waves, 0).bytes) / 6) & ~63ll);
+  r.lds = w8_layout(g->n, k, w.bits, w.waves, r.acap).bytes;
+  return r;
 }
 
 static uint64_t align256(uint64_t x) { return (x + 255u) & ~255ull; }
@@ -383,7 +405,11 @@ static int tabu_plan(const char* fn, const dlm_graph* g, const dlm_tabu_params* 
     if (!wave_auto && w8_least_bytes(n, k) > (uint64_t)lds_max)
       return set_error(DLM_E_UNSUPPORTED, "%s: %llu bytes of LDS needed, %lld available", fn,
                        (unsigned long long)w8_least_bytes(n, k), (long long)lds_max);
-    w8_shape(g, p, pop, P);
+    const W8Pick pick = w8_pick(g, p, pop);
+    W8Pick bytes;
+    const bool again = pick.bits == 4 && w8_pick_bytes(g, p, pop, bytes);
+    if (again) P.bytes = w8_shape(g, k, pop, bytes, kW8SideMax);
+    P.wave = w8_shape(g, k, pop, pick, again ? pick.side + kW4Spare : kW8SideMax);
     P.table = DLM_TABLE_WAVE8;
     w8_workspace(n, k, pop, P);
     P.ws_ask = P.ws_bytes;
@@ -471,7 +497,8 @@ static int tabu_run(const char* fn, const dlm_graph* g, const dlm_tabu_params* p
                          cells);
       DLM_HIP(hipGetLastError());
       if (a.ell && n <= (int)kW8ClassMax * k) {
-        if ((rc = launch_w8(a, pop, P.bits, P.block / kWave, P.acap, P.lds, s)) != DLM_OK) return rc;
+        if ((rc = launch_w8(a, pop, P.wave, s, nullptr)) != DLM_OK) return rc;
+        if (P.bytes.acap > 0 && (rc = launch_w8(a, pop, P.bytes, s, start)) != DLM_OK) return rc;
       } else {  // no padded rows, or a class past the limit for certain: the rerun is the search
         hipLaunchKernelGGL(leave_to_rerun_kernel, dim3((unsigned)((pop + 255) / 256)), dim3(256), 0, s, iters, pop);
         DLM_HIP(hipGetLastError());

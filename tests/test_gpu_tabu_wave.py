@@ -493,3 +493,43 @@ def test_wave_on_skewed_graphs(dlm, dev, case):
     mb.launch()
     torch.cuda.synchronize()
     assert (job["hash"].cpu().numpy().view(np.uint64) == ref["hash"]).all()
+
+
+def groups(q, s, p, seed):
+    """q groups of s vertices; two groups are joined completely with probability p."""
+    rng = np.random.default_rng(seed)
+    m = np.triu(rng.random((q, q)) < p, 1)
+    lab = np.repeat(np.arange(q), s)
+    e = np.argwhere(np.triu(m[np.ix_(lab, lab)] | m.T[np.ix_(lab, lab)], 1))
+    return from_edges(q * s, e.astype(np.int64), f"groups{q}x{s}")
+
+
+@pytest.mark.parametrize("q,s,p,k,pop", [(40, 20, 0.3, 40, 5), (16, 25, 0.3, 16, 40), (16, 25, 0.3, 16, 1500)])
+def test_wave_reruns_with_bytes(dlm, dev, q, s, p, k, pop):
+    """Groups of vertices with the same neighbours: a random start has few
+    entries past 14, a good colouring thousands, so 4-bit entries give up on
+    most individuals, whose rerun has 8-bit entries (and, for what these give
+    up on, 16-bit ones); single calls and an uneven batch."""
+    g = groups(q, s, p, seed=1)
+    T = 500
+    starts = oracle.init_random(g.n, k, pop, seed=2)
+    at = np.unique(np.linspace(0, pop - 1, 40).astype(int))
+    ref = oracle.tabucol_batch(g, starts[at], at, k, T, seed=7)
+    say(f"wave8 groups {q}x{s} p={p} k={k} pop={pop}")
+    gpu = gpu_run(dlm, g, starts, k, T, 7)
+    compare({x: gpu[x][at] for x in ("f_best", "iters", "stats", "hash", "colors")}, ref, at, "groups")
+    job = {"graph": dlm.Graph.from_csr(g), "colors": torch.from_numpy(starts).cuda(), "k": k, "iters": T, "seed": 7}
+    other = gnp(150, 0.5, seed=1)
+    st2 = oracle.init_random(150, 14, 6, seed=3)
+    job2 = {"graph": dlm.Graph.from_csr(other), "colors": torch.from_numpy(st2).cuda(), "k": 14, "iters": 600, "seed": 8}
+    ref2 = oracle.tabucol_batch(other, st2, np.arange(6), 14, 600, seed=8)
+    mb = dlm.MultiBatch([job2, job])
+    for rep in range(2):
+        for j, st in ((job, starts), (job2, st2)):
+            j["colors"].copy_(torch.from_numpy(st))
+        mb.launch()
+        torch.cuda.synchronize()
+        for j, r, idx in ((job, ref, at), (job2, ref2, np.arange(6))):
+            assert (j["hash"].cpu().numpy().view(np.uint64)[idx] == r["hash"]).all(), rep
+            assert (j["iters_out"].cpu().numpy()[idx] == r["iters"]).all(), rep
+            assert (j["colors"].cpu().numpy()[idx] == r["colors"]).all(), rep
