@@ -178,9 +178,8 @@ __device__ __forceinline__ int w8_compact_list(uint16_t* cg, uint16_t* list, int
 template <int G, class F>
 __device__ __forceinline__ void for_groups(int len, F f) {
   int i = 0;
-  if constexpr (G > 1)
-    for (; len - i > kWave; i += G * kWave) f(std::integral_constant<int, G>{}, i);
-  for (; i < len; i += kWave) f(std::integral_constant<int, 1>{}, i);
+  for (; len - i > kWave; i += G * kWave) f(std::integral_constant<int, G>{}, i);
+  if (i < len) f(std::integral_constant<int, 1>{}, i);
 }
 
 // One individual (row li of a.colors) searched by the NW waves of the calling
@@ -378,11 +377,14 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
   }
   // Groups of the LDS part walked together: a long list (f stays high with far
   // too few colours) is walked in every iteration, one round trip to the LDS
-  // and the L2 after the other.  64 individuals x 3,000 iterations of G(800,
-  // 0.95) with k = 68 (1,600 live pairs): 51.0 ms one group at a time, 38.1 ms
-  // with four.  With one or two waves per individual the registers it takes
-  // cost the short lists 2 to 5 %, and long ones are rarer there.
-  constexpr int GROUPS = NW == 4 ? 4 : 1;
+  // and the L2 after the other, and the tie pass walks it only if a pair of it
+  // is at the best delta.  An uneven batch of 12 graphs of 100 to 1,000 vertices:
+  // 101.7 ms one group at a time, 95.5 two at a time, 79.5 with the tie pass
+  // skipped as well (four at a time: 79.4, but 3 % more where lists are short).
+  // With one or two waves per individual the registers it takes cost short
+  // lists 2 to 5 %, and long ones are rarer there; their plain loops stand
+  // apart because going through the same lambda cost one wave 2 to 3 %.
+  constexpr int GROUPS = NW == 4 ? 2 : 1;
   auto refill = [&]() {  // from the end of act
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
@@ -467,16 +469,22 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
       const int g = (int)((x >> 8) & 0x7fu), dd = (int)(ga & 0x7fu) - g;
       return g != 0 && (ga >= kW8Free || dd <= aspd) ? (uint32_t)(dd + 128) : kW8None;
     };
-    auto act_deltas = [&](auto groups, int i0, uint32_t* v, uint32_t* c, uint32_t* x, uint32_t* d) {
+    auto act_delta = [&](int i0, uint32_t& v, uint32_t& c, uint32_t& x) -> uint32_t {
+      const int i = i0 + lane < A ? i0 + lane : acap;
+      const uint32_t e = act[i], ga = actg[i] & 0xffu;
+      v = i < acap ? e >> 17 : (uint32_t)n;
+      c = (e >> 9) & 0xffu;
+      x = cg[v];
+      return pair_delta(x, ga);
+    };
+    auto act_deltas = [&](auto groups, int i0, uint32_t* d) {
       constexpr int U = decltype(groups)::value;
-      uint32_t ga[U];
+      uint32_t v[U], ga[U], x[U];
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         const int i = i0 + kWave * u + lane < A ? i0 + kWave * u + lane : acap;
-        const uint32_t e = act[i];
         ga[u] = actg[i] & 0xffu;
-        v[u] = i < acap ? e >> 17 : (uint32_t)n;
-        c[u] = (e >> 9) & 0xffu;
+        v[u] = i < acap ? act[i] >> 17 : (uint32_t)n;
       }
 #pragma unroll
       for (int u = 0; u < U; ++u) x[u] = cg[v[u]];
@@ -508,14 +516,21 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
           side[b] = pair_delta(sxg[b], sg[b]);
           best = min(best, side[b]);
         }
-      for_groups<GROUPS>(A, [&](auto groups, int i0) {
-        constexpr int U = decltype(groups)::value;
-        uint32_t v[U], c[U], x[U], d[U];
-        act_deltas(groups, i0, v, c, x, d);
+      if constexpr (GROUPS == 1) {
+        for (int i0 = 0; i0 < A; i0 += kWave) {
+          uint32_t v, c, x;
+          best = min(best, act_delta(i0, v, c, x));
+        }
+      } else {
+        for_groups<GROUPS>(A, [&](auto groups, int i0) {
+          constexpr int U = decltype(groups)::value;
+          uint32_t d[U];
+          act_deltas(groups, i0, d);
 #pragma unroll
-        for (int u = 0; u < U; ++u) listed = min(listed, d[u]);
-      });
-      best = min(best, listed);
+          for (int u = 0; u < U; ++u) listed = min(listed, d[u]);
+        });
+        best = min(best, listed);
+      }
     }
     const uint32_t cur = wave_min_u32(best);
 
@@ -578,10 +593,10 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
             hash_move(side[b] == cur, sv[b], sc[b], sxg[b]);
             seen += __popcll(m);
           }
-        if (NW < 4 || (A > 0 && __ballot(listed == cur)))
+        if (NW < 4 || __ballot(listed == cur))  // (a test of A before it cost 3 %)
           for (int i0 = 0; i0 < A; i0 += kWave) {
-            uint32_t v, c, x, d;
-            act_deltas(std::integral_constant<int, 1>{}, i0, &v, &c, &x, &d);
+            uint32_t v, c, x;
+            const uint32_t d = act_delta(i0, v, c, x);
             if (const uint64_t m = __ballot(d == cur)) {
               hash_move(d == cur, v, c, x);
               seen += __popcll(m);
@@ -765,36 +780,55 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
         }
       if (A > 0) {
         int base = 0;
-        // in place: entries are read before those positions are written (base <= i0)
-        for_groups<GROUPS>(A, [&](auto groups, int i0) {
-          constexpr int U = decltype(groups)::value;
-          uint32_t e[U], eg[U], ad[U];
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const int i = i0 + kWave * u + lane < A ? i0 + kWave * u + lane : acap;
-            e[u] = act[i];
-            eg[u] = actg[i];
-          }
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const uint32_t v = i0 + kWave * u + lane < A ? e[u] >> 17 : (uint32_t)n;
-            ad[u] = dstar != kW8None ? adj_word(v) >> (v & 31u) : 0u;
-          }
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const bool alive = i0 + kWave * u + lane < A;
-            const uint32_t v = alive ? e[u] >> 17 : (uint32_t)n, c = alive ? (e[u] >> 9) & 0xffu : kNoColour;
-            uint32_t ga = eg[u] & 0xffu;
+        if constexpr (GROUPS == 1) {
+          for (int i0 = 0; i0 < A; i0 += kWave) {
+            const bool alive = i0 + lane < A;
+            const int i = alive ? i0 + lane : acap;
+            const uint32_t e = act[i], eg = actg[i], v = alive ? e >> 17 : (uint32_t)n;
+            const uint32_t c = alive ? (e >> 9) & 0xffu : kNoColour;
+            uint32_t ga = eg & 0xffu;
+            const uint32_t ad = dstar != kW8None ? adj_word(v) >> (v & 31u) : 0u;
             bool gone;
-            walk(v, c, (e[u] & 0x1ffu) | ((eg[u] >> 8) << 9), ga, (ad[u] & 1u) != 0u, gone);
+            walk(v, c, (e & 0x1ffu) | ((eg >> 8) << 9), ga, (ad & 1u) != 0u, gone);
             const bool keep = alive && !gone;
             const uint64_t mk = __ballot(keep);
             const int p = keep ? base + (int)lane_rank(mk) : acap;
-            act[p] = e[u];
-            actg[p] = (uint16_t)((eg[u] & 0xff00u) | ga);
+            act[p] = e;
+            actg[p] = (uint16_t)((eg & 0xff00u) | ga);
             base += __popcll(mk);
           }
-        });
+        } else {
+          // in place: entries are read before those positions are written (base <= i0)
+          for_groups<GROUPS>(A, [&](auto groups, int i0) {
+            constexpr int U = decltype(groups)::value;
+            uint32_t e[U], eg[U], ad[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              const int i = i0 + kWave * u + lane < A ? i0 + kWave * u + lane : acap;
+              e[u] = act[i];
+              eg[u] = actg[i];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              const uint32_t v = i0 + kWave * u + lane < A ? e[u] >> 17 : (uint32_t)n;
+              ad[u] = dstar != kW8None ? adj_word(v) >> (v & 31u) : 0u;
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+              const bool alive = i0 + kWave * u + lane < A;
+              const uint32_t v = alive ? e[u] >> 17 : (uint32_t)n, c = alive ? (e[u] >> 9) & 0xffu : kNoColour;
+              uint32_t ga = eg[u] & 0xffu;
+              bool gone;
+              walk(v, c, (e[u] & 0x1ffu) | ((eg[u] >> 8) << 9), ga, (ad[u] & 1u) != 0u, gone);
+              const bool keep = alive && !gone;
+              const uint64_t mk = __ballot(keep);
+              const int p = keep ? base + (int)lane_rank(mk) : acap;
+              act[p] = e[u];
+              actg[p] = (uint16_t)((eg[u] & 0xff00u) | ga);
+              base += __popcll(mk);
+            }
+          });
+        }
         A = base;
       }
       if (dstar != kW8None) {
