@@ -120,12 +120,15 @@ struct dlm_multi_plan {
   MultiDesc* d_descs = nullptr;
   uint32_t* d_queue = nullptr;
   uint32_t* d_slots = nullptr;
-  // the wave table's share: its descriptors by number of waves, descending,
-  // then those of the reruns with 8-bit entries
-  int32_t wdesc[5] = {0, 0, 0, 0, 0};  // descriptors before class i (4, 2, 1 waves; the reruns; the end)
-  int32_t witem[4] = {0, 0, 0, 0};     // items before class i
-  size_t wlds[4] = {0, 0, 0, 0};
-  int32_t again_items = 0;
+  // the wave table's share: its descriptors launch by launch, then those of the
+  // reruns with 8-bit entries
+  struct Launch {
+    int32_t waves, desc, ndesc, item, items;
+    size_t lds;
+  };
+  std::vector<Launch> launches;
+  int32_t wave_descs = 0, wave_items = 0, again_descs = 0, again_items = 0;
+  size_t again_lds = 0;
   int32_t rr_grid = 0;
   size_t rr_lds = 0;
   int64_t rr_slot_bytes = 0;
@@ -234,62 +237,126 @@ bool wave_item(const dlm_multi_item& it, int64_t pop, int64_t budget, WaveItem& 
   return w.instance >= 0 && w.least <= budget && rr <= device_lds_limit();
 }
 
-// The wave table's graphs, longest first.  A batch that the card holds whole
-// is as long as its longest individual: each graph gets the waves it would get
-// alone.  Otherwise the individuals share the CUs and the whole batch counts.
-std::vector<WaveItem> wave_items(const dlm_multi_item* items, const std::vector<int>& order, int64_t budget) {
-  std::vector<WaveItem> r;
-  int64_t total = 0, lds = 0, waves = 0;
-  for (int oi : order) total += items[oi].pop;
-  for (int oi : order) {
-    WaveItem w{};
-    w.oi = oi;
-    if (items[oi].pop == 0 || !wave_item(items[oi], items[oi].pop, budget, w)) continue;
-    lds += items[oi].pop * w.least;
-    waves += (int64_t)items[oi].pop * w.pick.waves;
-    r.push_back(w);
+// A launch of the wave search: graphs with the same number of waves, longest
+// first.  Every workgroup of it gets the LDS of the largest.
+struct WaveLaunch {
+  std::vector<WaveItem> graphs;
+  int64_t lds = 0, pop = 0;
+
+  void add(const WaveItem& w, int64_t individuals) {
+    graphs.push_back(w);
+    lds = std::max(lds, w.least);
+    pop += individuals;
   }
-  const int64_t cus = device_cu_count();
-  if (lds > cus * device_lds_per_cu() || waves > 16 * cus) {
-    size_t kept = 0;
-    for (WaveItem& w : r)
-      if (wave_item(items[w.oi], total, budget, w)) r[kept++] = w;
-    r.resize(kept);
+  // CUs that its individuals fill by their LDS
+  double cus() const {
+    return pop == 0 ? 0.0 : (double)pop / std::max<int64_t>(1, device_lds_per_cu() / kLdsGranule / ((lds + kLdsGranule - 1) / kLdsGranule));
+  }
+};
+
+// CUs that the individuals fill by their LDS, each launch by itself.
+double cus_of(const std::vector<WaveLaunch>& launches) {
+  double c = 0.0;
+  for (const WaveLaunch& l : launches) c += l.cus();
+  return c;
+}
+
+// At most `most` launches: one per number of waves; while the card does not hold
+// them, the one whose parting by LDS leaves the most CUs free is parted.  Without
+// it one graph of 854 vertices (88 KB) gave 576 individuals of four waves a CU
+// each, though most of them need 12 to 63 KB, and 320 of them had to queue.
+std::vector<WaveLaunch> wave_launches(const dlm_multi_item* items, const std::vector<WaveItem>& graphs, size_t most) {
+  std::vector<WaveLaunch> r;
+  for (int waves : {4, 2, 1}) {
+    WaveLaunch l;
+    for (const WaveItem& w : graphs)
+      if (w.pick.waves == waves) l.add(w, items[w.oi].pop);
+    if (!l.graphs.empty()) r.push_back(l);
+  }
+  while (r.size() < most && cus_of(r) > device_cu_count()) {
+    double best = 1.0;  // CUs
+    size_t at = 0;
+    WaveLaunch large, small;
+    for (size_t i = 0; i < r.size(); ++i)
+      for (const WaveItem& cut : r[i].graphs) {
+        WaveLaunch a, b;
+        for (const WaveItem& w : r[i].graphs) (w.least >= cut.least ? a : b).add(w, items[w.oi].pop);
+        const double free = r[i].cus() - a.cus() - b.cus();
+        if (free > best) {
+          best = free;
+          at = i;
+          large = a;
+          small = b;
+        }
+      }
+    if (large.graphs.empty()) break;
+    r[at] = large;
+    r.insert(r.begin() + (std::ptrdiff_t)at + 1, small);
   }
   return r;
 }
 
-// The plan's nodes onto cs[3] (capturing): class c of the wave table on the
-// branch of cs[c], the persistent kernel on cs[3] itself.
+// Launches side by side.  A process has four hardware queues; with four branches
+// two of them came to lie on one queue, one after the other (a batch of 9 graphs
+// of 75 to 534 vertices: 47 ms instead of 27).
+constexpr size_t kBranches = 3;
+
+// The launches of the wave table's graphs.  A batch that the card holds whole
+// is as long as its longest individual: each graph gets the waves it would get
+// alone.  Otherwise the individuals share the CUs and the whole batch counts.
+std::vector<WaveLaunch> wave_plan(const dlm_multi_item* items, const std::vector<int>& order, int64_t budget) {
+  int64_t total = 0;
+  for (int oi : order) total += items[oi].pop;
+  auto launches = [&](bool alone) {
+    std::vector<WaveItem> graphs;
+    bool block = false;  // the block search takes a branch
+    for (int oi : order) {
+      WaveItem w{};
+      w.oi = oi;
+      if (items[oi].pop == 0) continue;
+      if (wave_item(items[oi], alone ? items[oi].pop : total, budget, w))
+        graphs.push_back(w);
+      else
+        block = true;
+    }
+    return wave_launches(items, graphs, kBranches - (block ? 1 : 0));
+  };
+  std::vector<WaveLaunch> r = launches(true);
+  int64_t waves = 0;
+  for (const WaveLaunch& l : r) waves += l.pop * l.graphs[0].pick.waves;
+  if (cus_of(r) > device_cu_count() || waves > 16 * (int64_t)device_cu_count()) r = launches(false);
+  return r;
+}
+
+// The plan's nodes onto cs[kBranches - 1] (capturing), the launches of the
+// wave table on branches of their own; the last is the block search's.
 int capture_plan(const dlm_multi_plan* p, const hipStream_t* cs, const hipEvent_t* ev) {
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, cs[3], p->d_queue, 1, 0u);
+  hipStream_t s = cs[kBranches - 1];
+  hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, p->d_queue, 1, 0u);
   DLM_HIP(hipGetLastError());
-  DLM_HIP(hipEventRecord(ev[3], cs[3]));
-  auto items = [&](int c) { return p->witem[c + 1] - p->witem[c]; };
-  for (int c = 0; c < 3; ++c) {
-    if (items(c) == 0) continue;
-    DLM_HIP(hipStreamWaitEvent(cs[c], ev[3], 0));
-    const auto launch = c == 0 ? launch_multi_w8_4 : c == 1 ? launch_multi_w8_2 : launch_multi_w8_1;
-    const int rc = launch(p->d_wdescs + p->wdesc[c], p->wdesc[c + 1] - p->wdesc[c], p->witem[c], items(c), p->wlds[c], cs[c]);
+  DLM_HIP(hipEventRecord(ev[kBranches - 1], s));
+  for (size_t i = 0; i < p->launches.size(); ++i) {
+    const dlm_multi_plan::Launch& l = p->launches[i];
+    if (i < kBranches - 1) DLM_HIP(hipStreamWaitEvent(cs[i], ev[kBranches - 1], 0));
+    const auto launch = l.waves == 4 ? launch_multi_w8_4 : l.waves == 2 ? launch_multi_w8_2 : launch_multi_w8_1;
+    const int rc = launch(p->d_wdescs + l.desc, l.ndesc, l.item, l.items, l.lds, cs[i]);
     if (rc != DLM_OK) return rc;
-    DLM_HIP(hipEventRecord(ev[c], cs[c]));
+    if (i < kBranches - 1) DLM_HIP(hipEventRecord(ev[i], cs[i]));
   }
   if (p->block_items > 0) {
-    const int rc = launch_persistent(p, cs[3]);
+    const int rc = launch_persistent(p, s);
     if (rc != DLM_OK) return rc;
   }
-  for (int c = 0; c < 3; ++c)
-    if (items(c) > 0) DLM_HIP(hipStreamWaitEvent(cs[3], ev[c], 0));
+  for (size_t i = 0; i < p->launches.size() && i < kBranches - 1; ++i) DLM_HIP(hipStreamWaitEvent(s, ev[i], 0));
   if (p->again_items > 0) {
-    const int rc = launch_multi_w8_again(p->d_wdescs + p->wdesc[3], p->wdesc[4] - p->wdesc[3], p->again_items,
-                                         p->wlds[3], cs[3]);
+    const int rc = launch_multi_w8_again(p->d_wdescs + p->wave_descs, p->again_descs, p->again_items, p->again_lds, s);
     if (rc != DLM_OK) return rc;
   }
   if (p->rr_grid > 0) {
     auto kern = tabu_multi_rerun_kernel<kRerunBlock>;
     DLM_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p->rr_lds));
-    hipLaunchKernelGGL(kern, dim3(p->rr_grid), dim3(kRerunBlock), p->rr_lds, cs[3], p->d_wdescs, p->wdesc[3],
-                       p->witem[3], p->d_rr_slots, p->rr_slot_bytes);
+    hipLaunchKernelGGL(kern, dim3(p->rr_grid), dim3(kRerunBlock), p->rr_lds, s, p->d_wdescs, p->wave_descs,
+                       p->wave_items, p->d_rr_slots, p->rr_slot_bytes);
     DLM_HIP(hipGetLastError());
   }
   return DLM_OK;
@@ -323,9 +390,10 @@ int dlm_multi_plan_create(const dlm_multi_item* items, int32_t count, const dlm_
   p->block = block;
   p->lds_budget = (int32_t)budget;
   std::vector<MultiDesc> descs;
-  const std::vector<WaveItem> wave = wave_items(items, order, budget);
+  const std::vector<WaveLaunch> wave = wave_plan(items, order, budget);
   std::vector<char> on_wave(count, 0);
-  for (const WaveItem& w : wave) on_wave[w.oi] = 1;
+  for (const WaveLaunch& l : wave)
+    for (const WaveItem& w : l.graphs) on_wave[w.oi] = 1;
   int32_t first = 0;
   size_t lds = tabu_layout(1, 1, nw, 0).bytes;
   for (int oi : order) {
@@ -364,29 +432,25 @@ int dlm_multi_plan_create(const dlm_multi_item* items, int32_t count, const dlm_
   }
   p->slot_words = (p->slot_words + 3) & ~int64_t(3);  // 16-byte aligned slots
   p->block_items = first;
-  // the wave table's descriptors; an LDS of the class leaves the smaller
-  // individuals of the class more side-list entries
+  // the wave table's descriptors; a launch's LDS leaves its smaller individuals
+  // more side-list entries
   std::vector<WaveDesc> wdescs;
-  std::vector<size_t> start_at, wave_of;
+  std::vector<size_t> start_at;
+  std::vector<const WaveItem*> wave_of;
   size_t start_cells = 0;
   int32_t witems = 0;
-  for (int c = 0; c < 3; ++c) {
-    const int nwv = 4 >> c;
-    p->wdesc[c] = (int32_t)wdescs.size();
-    p->witem[c] = witems;
-    for (const WaveItem& w : wave)
-      if (w.pick.waves == nwv) p->wlds[c] = std::max(p->wlds[c], (size_t)w.least);
-    for (size_t wi = 0; wi < wave.size(); ++wi) {
-      const WaveItem& w = wave[wi];
-      if (w.pick.waves != nwv) continue;
-      wave_of.push_back(wi);
+  for (const WaveLaunch& l : wave) {
+    const int nwv = l.graphs[0].pick.waves;
+    p->launches.push_back({nwv, (int32_t)wdescs.size(), (int32_t)l.graphs.size(), witems, (int32_t)l.pop, (size_t)l.lds});
+    for (const WaveItem& w : l.graphs) {
+      wave_of.push_back(&w);
       const dlm_multi_item& it = items[w.oi];
       const int n = it.g->n;
       WaveDesc d{};
       d.a = TabuArgs{it.g->row_ptr, it.g->col_idx, it.g->erow, it.colors_dev, it.f_best_dev, it.iters_dev,
                      it.stats_dev, it.hash_dev, nullptr, nullptr, make_key(it.seed), n, it.k, it.max_iters,
                      it.ten_num, it.ten_den, it.ten_rand, it.ind_base, 0, it.g->ell, it.g->adj, it.g->ell_stride};
-      const int64_t room = (int64_t)p->wlds[c] - (int64_t)w8_layout(n, it.k, w.pick.bits, nwv, 0).bytes;
+      const int64_t room = l.lds - (int64_t)w8_layout(n, it.k, w.pick.bits, nwv, 0).bytes;
       W8Pick b;
       const dlm_tabu_params q = item_params(it);
       const bool again = w.pick.bits == 4 && w8_pick_bytes(it.g, &q, it.pop, b);
@@ -402,12 +466,12 @@ int dlm_multi_plan_create(const dlm_multi_item* items, int32_t count, const dlm_
       p->rr_slot_bytes = std::max<int64_t>(p->rr_slot_bytes, (int64_t)((tab_entries(n, it.k) * TabGlobal16::kGlobalBytes + 15) & ~15ull));
       p->rr_lds = std::max(p->rr_lds, (size_t)tabu_layout(n, it.k, kRerunBlock / kWave, 0).bytes);
     }
-    p->info_lds = std::max(p->info_lds, p->wlds[c]);
+    p->info_lds = std::max(p->info_lds, (size_t)l.lds);
   }
-  p->wdesc[3] = (int32_t)wdescs.size();
+  p->wave_descs = (int32_t)wdescs.size();
   // reruns with 8-bit entries: few and late, so four waves each
-  for (int32_t i = 0; i < p->wdesc[3]; ++i) {
-    const WaveItem& w = wave[wave_of[i]];
+  for (int32_t i = 0; i < p->wave_descs; ++i) {
+    const WaveItem& w = *wave_of[i];
     const dlm_multi_item& it = items[w.oi];
     const dlm_tabu_params q = item_params(it);
     W8Pick b;
@@ -420,12 +484,12 @@ int dlm_multi_plan_create(const dlm_multi_item* items, int32_t count, const dlm_
     d.first_item = p->again_items;
     p->again_items += it.pop;
     start_at.push_back(start_at[i]);
-    p->wlds[3] = std::max(p->wlds[3], (size_t)w8_layout(it.g->n, it.k, 8, 4, d.acap).bytes);
+    p->again_lds = std::max(p->again_lds, (size_t)w8_layout(it.g->n, it.k, 8, 4, d.acap).bytes);
     wdescs.push_back(d);
   }
-  p->wdesc[4] = (int32_t)wdescs.size();
-  p->info_lds = std::max(p->info_lds, p->wlds[3]);
-  p->witem[3] = witems;
+  p->again_descs = (int32_t)wdescs.size() - p->wave_descs;
+  p->info_lds = std::max(p->info_lds, p->again_lds);
+  p->wave_items = witems;
   if (witems > 0)
     p->rr_grid = (int32_t)std::max<int64_t>(
         1, std::min<int64_t>({(int64_t)witems, 2 * (int64_t)device_cu_count(), (int64_t)(kRerunSlotBytes / (uint64_t)p->rr_slot_bytes)}));
@@ -477,26 +541,26 @@ int dlm_multi_plan_create(const dlm_multi_item* items, int32_t count, const dlm_
   }
   // capture: queue reset (a fill kernel, no memset node), the wave launches and
   // the persistent kernel side by side, the reruns
-  hipStream_t cs[4] = {};
-  hipEvent_t ev[4] = {};
+  hipStream_t cs[kBranches] = {};
+  hipEvent_t ev[kBranches] = {};
   auto release = [&]() {
-    for (int i = 0; i < 4; ++i) {
+    for (size_t i = 0; i < kBranches; ++i) {
       if (ev[i]) (void)hipEventDestroy(ev[i]);
       if (cs[i]) (void)hipStreamDestroy(cs[i]);
     }
   };
-  for (int i = 0; i < 4; ++i)
+  for (size_t i = 0; i < kBranches; ++i)
     if ((e = hipStreamCreateWithFlags(&cs[i], hipStreamNonBlocking)) != hipSuccess ||
         (e = hipEventCreateWithFlags(&ev[i], hipEventDisableTiming)) != hipSuccess) {
       release();
       return fail(e, "hipStreamCreate");
     }
-  if ((e = hipStreamBeginCapture(cs[3], hipStreamCaptureModeThreadLocal)) != hipSuccess) {
+  if ((e = hipStreamBeginCapture(cs[kBranches - 1], hipStreamCaptureModeThreadLocal)) != hipSuccess) {
     release();
     return fail(e, "hipStreamBeginCapture");
   }
   rc = capture_plan(p, cs, ev);
-  e = hipStreamEndCapture(cs[3], &p->graph);
+  e = hipStreamEndCapture(cs[kBranches - 1], &p->graph);
   release();
   if (rc != DLM_OK) {
     free_plan(p);
@@ -519,7 +583,7 @@ int dlm_multi_plan_launch(dlm_multi_plan* p, void* stream) {
 int dlm_multi_plan_info(const dlm_multi_plan* p, int32_t* grid, int32_t* lds_bytes, int32_t* n_global,
                         int32_t* total_items) {
   if (!p) return set_error(DLM_E_INVAL, "dlm_multi_plan_info: plan is NULL");
-  if (grid) *grid = (p->block_items > 0 ? p->grid : 0) + p->witem[3];
+  if (grid) *grid = (p->block_items > 0 ? p->grid : 0) + p->wave_items;
   if (lds_bytes) *lds_bytes = (int32_t)p->info_lds;
   if (n_global) *n_global = p->n_global;
   if (total_items) *total_items = p->total;

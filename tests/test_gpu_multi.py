@@ -149,3 +149,27 @@ def test_multi_wave_widths_and_reruns(dlm, dev):
             assert (j["iters_out"].cpu().numpy() == ref["iters"]).all(), (rep, gi)
             assert (j["hash"].cpu().numpy().view(np.uint64) == ref["hash"]).all(), (rep, gi)
             assert (j["colors"].cpu().numpy() == ref["colors"]).all(), (rep, gi)
+
+
+def test_multi_parts_a_launch_by_lds(dlm, dev):
+    """One graph whose individuals fill a CU each beside many that need a
+    fraction of one, all of four waves: more CUs than the card has if every
+    workgroup got the largest's LDS, so the launch is parted."""
+    jobs, starts = make_jobs(dlm, [("gnp", 860, 0.8, 172, 64, 40)] +
+                             [("gnp", 300 + 12 * i, 0.5, 26 + i, 64, 150) for i in range(8)] + [("gnp", 90, 0.5, 11, 64, 300)])
+    say("multi parted launch")
+    mb = dlm.MultiBatch(jobs)
+    at = np.array([0, 31, 63])
+    refs = [oracle.tabucol_batch(j["g"], st[at], j["ind_base"] + at, j["k"], j["iters"], seed=j["seed"])
+            for j, st in zip(jobs, starts)]
+    for rep in range(3):
+        for j, st in zip(jobs, starts):
+            j["colors"].copy_(torch.from_numpy(st))
+        mb.launch()
+        torch.cuda.synchronize()
+        for gi, (j, ref) in enumerate(zip(jobs, refs)):
+            assert (j["iters_out"].cpu().numpy()[at] == ref["iters"]).all(), (rep, gi)
+            assert (j["hash"].cpu().numpy().view(np.uint64)[at] == ref["hash"]).all(), (rep, gi)
+            assert (j["colors"].cpu().numpy()[at] == ref["colors"]).all(), (rep, gi)
+            conf, _ = dlm.evaluate(j["graph"], j["colors"], j["k"])
+            assert (conf.cpu().numpy() == j["f_best"].cpu().numpy()).all(), (rep, gi)
