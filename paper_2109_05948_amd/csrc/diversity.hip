@@ -745,15 +745,24 @@ int dlm_partition_distance(int32_t n, int32_t k, const int16_t* a, int32_t na, c
 
 // Whether the lanes kernel is the faster one.  However few the pairs, its two
 // launches take one wave through one row each, about 10 + 0.2 n + 0.6 k us;
-// the pair kernel takes about 0.7 + k^2 / 1000 ns a pair (1.8 k^2 beyond one
-// column per lane), two thirds of that in the triangle form.  Pair kernel and
-// lanes kernel, in us, around the line: n = 500, k = 49, 128 x 128 pairs 61
-// and 128, 256 x 256 181 and 129; n = 1000, k = 85, 64 x 64 77 and 151,
-// 256 x 256 879 and 279; n = 100, k = 15, 128 x 128 26 and 30, 256 x 256 68
-// and 31; n = 1000, k = 20, 128 x 128 40 and 200.
-static bool lanes_faster(int32_t na, int32_t nb, int32_t tri, int32_t n, int32_t k) {
+// beyond that each row of one side against 64 of the other costs the card
+// about 0.3 + 0.025 n + 0.13 k ns (more of the n where a CU holds few waves),
+// also where those 64 are few: one row against 50,000 is 50,782 of them, of
+// which 50,000 have one lane at work.  The pair kernel takes about
+// 0.45 + (n / 2 + k^2) / 1000 ns a pair (1.8 k^2 beyond one column per lane).
+// The triangle form has two thirds of the pairs' work and half the rows'.  Pair kernel and lanes
+// kernel, in us, around the line: n = 500, k = 49, 128 x 128 pairs 61 and 128,
+// 256 x 256 181 and 129, 1 x 50,000 187 and 952, 16 x 4,000 190 and 183;
+// n = 1000, k = 85, 64 x 64 77 and 151, 256 x 256 879 and 279, 5 x 10,000 759
+// and 1,016, 32 x 4,000 1,665 and 656; n = 100, k = 15, 128 x 128 26 and 30,
+// 256 x 256 68 and 31; n = 1000, k = 20, 128 x 128 40 and 200, 600 x 600 507
+// and 389.
+static bool lanes_faster(int32_t na, int32_t nb, int32_t tri, int32_t n, int32_t k, int waves) {
   const double pairs = (double)na * nb * (tri ? 2.0 / 3.0 : 1.0);
-  return pairs * (700.0 + (k <= kWave ? 1.0 : 1.8) * k * k) >= 1e6 * (10.0 + 0.2 * n + 0.6 * k);
+  const double rows = ((double)na * ((nb + 63) / 64) + (double)nb * ((na + 63) / 64)) * (tri ? 0.5 : 1.0);
+  const double least = 1e3 * (10.0 + 0.2 * n + 0.6 * k);  // ns
+  const double row = 0.3 + 0.025 * n * std::max(1.0, 7.0 / waves) + 0.13 * k;
+  return pairs * (0.45 + 5e-4 * n + 1e-3 * (k <= kWave ? 1.0 : 1.8) * k * k) >= std::max(least, 0.5 * least + rows * row);
 }
 
 static int distance_pairs(const int16_t* a, const int16_t* b, const int16_t* recA, const int16_t* recB, int32_t na,
@@ -766,9 +775,10 @@ static int distance_pairs(const int16_t* a, const int16_t* b, const int16_t* rec
   const bool half = ((int64_t)n << bits) < (1 << 15);
   int waves = half ? 16 : 8;
   while (waves > 0 && (int64_t)lanes_bytes(n, k, waves, half) > (int64_t)device_lds_limit()) waves -= half ? 2 : 1;
+  const int held = waves;  // by a CU, give or take
   // few jobs: fewer waves to a workgroup, on more CUs
   while (waves > 4 && waves % 4 == 0 && (int64_t)((nb + 63) / 64) * na < (int64_t)waves * device_cu_count()) waves /= 2;
-  if (k <= kLaneK && waves >= 2 && lanes_faster(na, nb, tri, n, k)) {
+  if (k <= kLaneK && waves >= 2 && lanes_faster(na, nb, tri, n, k, held)) {
     auto pass = [&](auto kern, int dir, const int16_t* x, const int16_t* rx, int32_t nx, const int16_t* y,
                     const int16_t* ry, int32_t ny) -> int {
       // rows per workgroup: at least one per wave, more once every CU has work

@@ -274,3 +274,25 @@ def test_distance_many_pairs(dlm, dev, k, n, na, nb):
     want = small_blocks(ga, ga).cpu().numpy()
     iu = np.triu_indices(na, 1)
     assert (tri[iu] == want[iu]).all() and (tri.T == tri).all() and (np.diag(tri) == 0).all()
+
+
+@pytest.mark.parametrize("k,n,na,nb", [(49, 500, 1, 20000), (49, 500, 20000, 1), (49, 500, 5, 3000), (49, 500, 63, 1500),
+                                       (49, 500, 1500, 63), (85, 900, 2, 2000), (100, 200, 3, 20000), (100, 200, 40, 700)])
+def test_distance_narrow_blocks(dlm, dev, k, n, na, nb):
+    """One side far below the 64 rows that the lanes of a wave take, on both
+    sides of the choice between the kernels: against blocks of 40 rows by 8,
+    too small for the lanes kernel, and the oracle on some pairs."""
+    rng = np.random.default_rng(n + na)
+    a = colourings(rng, na, n, k)
+    b = colourings(rng, nb, n, k, close_to=a, moved=n // 10)
+    some = [(int(rng.integers(na)), int(rng.integers(nb))) for _ in range(10)] + [(na - 1, nb - 1)]
+    ref = [dv.distance_matrix(a[i:i + 1], b[j:j + 1], k)[0, 0] for i, j in some]
+    ga, gb = cuda(a), cuda(b)
+    say(f"distance narrow k={k} n={n} {na}x{nb}")
+    got = dlm.partition_distance(ga, k, gb).cpu().numpy()
+    for (i, j), d in zip(some, ref):
+        assert got[i, j] == d, (i, j)
+    rows, cols = np.unique(np.r_[0, na // 2, na - 1]), np.unique(np.r_[rng.integers(0, nb, 60), 0, nb - 1])
+    gr, gc = cuda(a[rows]), cuda(b[cols])
+    want = torch.cat([dlm.partition_distance(gr, k, gc[j:j + 8]) for j in range(0, len(cols), 8)], dim=1).cpu().numpy()
+    assert (got[np.ix_(rows, cols)] == want).all()
