@@ -77,10 +77,11 @@ struct W8Layout {
 
 __host__ __device__ constexpr int w8_row_dwords(int k, int bits) { return (k * bits + 31) >> 5; }
 
-// Vertices one wave's list holds: all of them for one wave.  Several waves share
-// them evenly but for chance (about sqrt(n)); half of them and 64 is room enough
-// in earnest, and a list that is full all the same leaves the individual to the
-// 16-bit rerun.
+// Vertices one wave's list holds: all of them for one wave.  Several waves
+// start with equal shares, and rows of many neighbours keep them so; what joins
+// by rows of up to 16 neighbours joins wave 0.  Half of the vertices and 64 is
+// room enough in earnest (G(450, 0.03), four waves: lists of 121, 50, 64 and 63
+// in the mean); a list that is full all the same leaves the individual to a rerun.
 __host__ __device__ constexpr int w8_list_cap(int n, int nw) { return nw == 1 || n / 2 + 64 > n ? n : n / 2 + 64; }
 
 // LDS of one individual searched by nw waves, with room for acap side-list
@@ -646,9 +647,11 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
     }
     // ---- apply.  Neighbour u of v*: gamma[u][old] - 1, gamma[u][c*] + 1; if
     // u has colour old or c*, its own gamma and list membership follow.
-    // Groups of 16 consecutive neighbours go to the waves in turn, so that
-    // short rows and every wave's list stay balanced.  A row ends in entries
-    // n + 1, where nothing changes.
+    // Groups of 16 consecutive neighbours go to the waves in turn, the first to
+    // wave 0: the waves share rows of 64 and more evenly, a row of up to 16 is
+    // wave 0's alone.  (Turning the first wave with v* evened the lists of sparse
+    // graphs out, but changed no time: G(450, 0.03), k = 4, 9.84 and 9.84 ms.)  A
+    // row ends in entries n + 1, where nothing changes.
     const uint32_t nrow = 2u * vs * stride, arow = 4u * vs * aw;  // bytes
     auto adj_word = [&](uint32_t v) { return *(gptr<const uint32_t>)((gptr<const char>)adj + (arow + 4u * (v >> 5))); };
     const uint32_t e0 = (uint32_t)(((lane & ~15) * NW) + (wid << 4) + (lane & 15));

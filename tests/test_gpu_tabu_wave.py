@@ -533,3 +533,41 @@ def test_wave_reruns_with_bytes(dlm, dev, q, s, p, k, pop):
             assert (j["hash"].cpu().numpy().view(np.uint64)[idx] == r["hash"]).all(), rep
             assert (j["iters_out"].cpu().numpy()[idx] == r["iters"]).all(), rep
             assert (j["colors"].cpu().numpy()[idx] == r["colors"]).all(), rep
+
+
+def test_wave_reruns_when_a_conflict_list_is_full(dlm, dev):
+    """Degrees of at most 16, so that every vertex that starts to conflict joins
+    the list of the first of four waves (n / 2 + 64 entries); ten 4-cliques keep
+    k = 3 conflicting, and tenures longer than the run force ever worse moves,
+    until most of a colouring without other conflicts is in conflict."""
+    n, k, d, T, pop = 330, 3, 16, 2000, 3
+    rng = np.random.default_rng(1)
+    deg, e = np.zeros(n, int), set()
+    for q in rng.permutation(n)[:10 * (k + 1)].reshape(10, k + 1):
+        for i in range(k + 1):
+            for j in range(i):
+                e.add((min(q[i], q[j]), max(q[i], q[j])))
+                deg[q[i]] += 1
+                deg[q[j]] += 1
+    for a, b in rng.integers(0, n, (40 * n * d, 2)):
+        if a % k != b % k and deg[a] < d and deg[b] < d and (min(a, b), max(a, b)) not in e:
+            e.add((min(a, b), max(a, b)))
+            deg[a] += 1
+            deg[b] += 1
+    g = from_edges(n, np.array(sorted(e), np.int64), "cliques")
+    starts = np.tile((np.arange(n) % k).astype(np.int16), (pop, 1))
+    ten = {"ten_num": 32767, "ten_den": 1, "ten_rand": 1024}
+    for i in range(pop):  # conflicting vertices that began without a conflict, at the most
+        tr = oracle.tabucol(g, starts[i], k, 400, seed=5, ind=i, trace_cap=400, **ten)
+        col, most = starts[i].astype(int), 0
+        ends = np.array(sorted(e))
+        for rec in tr["trace"][:tr["iters"], 0]:
+            if rec >= 0:
+                col[rec & 0xffff] = rec >> 16
+            bad = ends[col[ends[:, 0]] == col[ends[:, 1]]]
+            most = max(most, len(np.unique(bad)))
+        assert most - 10 * (k + 1) > n // 2, most
+    ref = oracle.tabucol_batch(g, starts, np.arange(pop), k, T, seed=5, **ten)
+    say("wave8 full conflict list")
+    gpu = gpu_run(dlm, g, starts, k, T, 5, **ten)
+    compare(gpu, ref, range(pop), "full list")
