@@ -32,7 +32,7 @@ import time
 
 import numpy as np
 
-GNP500_BLOCK = 64
+GNP500_BLOCK = 0  # the library's choice
 GNP500_TABLE = "wave8"
 LDS_PEAK_GBS = 256 * 128 * 2.4  # GB/s: 256 CUs x 128 B/clk x 2.4 GHz
 HBM_PEAK_GBS = 8000.0
@@ -46,10 +46,11 @@ METRIC = "tabu moves/sec (population, 1 GPU) + time-to-legal-k-coloring, learned
 # for a 1 GiB device-to-device copy.  Valid only for the kernel sources they
 # were taken on (digest below) and the same table and block; otherwise null.
 MEASURED_TRAFFIC = {"sources_sha256": "90f622ede0f2d30055248402ea1008c515523046e0683b22b3d379670c082e06",
-                    "table": "wave8", "block": 64, "bytes": 27144576}  # profiles/tabucol_wave8_gnp500.md
+                    "table": "wave8", "block": 0, "bytes": 27144576}  # profiles/tabucol_wave8_gnp500.md
 KERNEL_SOURCES = ("paper_2109_05948_amd/csrc/tabu_body.h", "paper_2109_05948_amd/csrc/tabucol.hip",
                   "paper_2109_05948_amd/csrc/dlm_common.h", "paper_2109_05948_amd/csrc/tabu_wave.h",
-                  "paper_2109_05948_amd/csrc/tabu_wave_kernel.h")
+                  "paper_2109_05948_amd/csrc/tabu_wave_kernel.h", "paper_2109_05948_amd/csrc/tabu_wave_launch.h",
+                  "paper_2109_05948_amd/csrc/wave_util.h")
 
 
 # HBM bytes of the two distance launches of one diversity step (old x new
@@ -308,7 +309,7 @@ def main():
         "dtype": "int32",
         "data": "synthetic",
         "config": {"workload": args.workload, "graph": f"G(n={g.n}, p=0.5) seed 0", "k": k,
-                   "population": pop, "iters_per_individual": T, "block": args.block,
+                   "population": pop, "iters_per_individual": T, "block": args.block or "auto",
                    "table": args.table, "parallelism": "population (one workgroup per individual)"},
         "roofline": {"bound": "lds", "achieved": lds_gbs, "peak": LDS_PEAK_GBS, "unit": "GB/s",
                      "frac": lds_gbs / LDS_PEAK_GBS, "traffic": traffic,

@@ -119,8 +119,10 @@ int dlm_init_population(const dlm_graph* g, int32_t k, int32_t pop, uint64_t see
  *     L = floor(w0 * ten_rand / 2^32), w0 = Philox(seed; ind, t, 0, 0x80000001);
  *   the best colouring met (smallest f) is kept.
  * ---------------------------------------------------------------------- */
-#define DLM_TABLE_AUTO 0       /* WAVE8 when it holds the individual and block is 0 or 64; otherwise LDS16 or
-                                  SPLIT8, whichever keeps more workgroups per CU; GLOBAL16 if neither fits */
+#define DLM_TABLE_AUTO 0       /* WAVE8 when it holds the individual and block is 0 or 64 (with block 0, LDS16
+                                  where most pairs are expected to be tabu or classes to pass 127 vertices);
+                                  otherwise LDS16 or SPLIT8, whichever keeps more workgroups per CU; GLOBAL16
+                                  if neither fits */
 #define DLM_TABLE_LDS16 1      /* 32-bit word per (v,c): gamma 16 bits | tabu 16 bits, LDS */
 #define DLM_TABLE_LDS32 2      /* 64-bit word per (v,c): gamma int32 | tabu expiry, LDS */
 #define DLM_TABLE_GLOBAL16 3   /* packed 16-bit words in device memory (large n*k) */
@@ -133,8 +135,8 @@ int dlm_init_population(const dlm_graph* g, int32_t k, int32_t pop, uint64_t see
                                   tabu pairs and gammas that do not fit, and a side list of the escaped pairs;
                                   needs k <= 256 and n * kp <= 2^17 when asked for (AUTO also takes it for
                                   larger tables that fit in 4 bits).  An individual whose colour classes would pass
-                                  127 vertices, or whose side list would overflow, is rerun from its start with
-                                  GLOBAL16 (same results) */
+                                  127 vertices, or whose side list would overflow, is rerun from its start: with 8
+                                  bits if it had 4 and the LDS holds them, then with GLOBAL16 (same results) */
 
 typedef struct dlm_tabu_params {
   int32_t k;          /* colours, 1 <= k <= 32767 */
@@ -156,7 +158,10 @@ typedef struct dlm_tabu_params {
 /*
  * Device workspace a dlm_tabu_batch call with these arguments needs, in
  * bytes (0 for the LDS tiers).  The automatic table and block are resolved
- * as the call resolves them, on the current device.  The device-memory tiers
+ * as the call resolves them, on the current device; where AUTO chooses between
+ * WAVE8 and LDS16 by the run's length and tenure, what WAVE8 needs is reported
+ * for both.  WAVE8 needs a copy of the start colourings and rerun tables (at
+ * most 2 per CU and 1 GiB).  The device-memory tiers
  * need their tables (pop * (n + 1) * kp entries of 4 bytes for GLOBAL16, 2
  * for SPLIT16 and SPLIT8); SPLIT8 adds a copy of the start colourings and
  * the rerun tables (at most 2 per CU and 1 GiB).
@@ -211,7 +216,7 @@ int dlm_tabu_batch(const dlm_graph* g, const dlm_tabu_params* p, int32_t pop,
  *   Nothing in the array needs clearing between calls: each launch writes
  *   every byte of the workspace it reads first.
  * Errors: as dlm_tabu_batch; DLM_E_UNSUPPORTED when the workspace this call
- * would need (dlm_tabu_workspace_bytes) exceeds DLM_STATIC_SCRATCH_BYTES, in
+ * uses (at most dlm_tabu_workspace_bytes) exceeds DLM_STATIC_SCRATCH_BYTES, in
  * which case nothing is launched.
  */
 #define DLM_STATIC_SCRATCH_BYTES (64ull << 20)
