@@ -234,9 +234,10 @@ __global__ __launch_bounds__(256) void distance_kernel(const int16_t* __restrict
 // below 2^15 two waves share a counter's dword, a half each: an atomic on one
 // half never carries into the other.
 //
-// Bound by the issue of each wave's instructions (about 6 per vertex), so by
-// the waves that the LDS holds: n = 500, k = 49 has 14 with halves and 8
-// without.  4096 x 4096 pairs of that shape, both passes: 42.3 ms with one
+// Bound by the LDS, which takes one instruction every 5 cycles of a CU (59 % of
+// them atomics; the waves wait 31 % of their time for it to take one), and by
+// the waves that it holds to hide the rest: n = 500, k = 49 has 14 with halves
+// and 8 without.  4096 x 4096 pairs of that shape, both passes: 42.3 ms with one
 // wave per pair, 9.4 with whole counters, 7.9 with halves.  Reading the
 // next classes' colours ahead cost more in branches than it hid (16.8 ms), as
 // did stores instead of the lowering atomics in selects (10.0 ms).

@@ -48,8 +48,12 @@
 //          over the waves; a neighbour's row and cg word belong to one lane;
 //          the last wave also writes v*'s state and walks the side list.
 //
-// What bounds it: one wave's chain of dependent steps.  Measured here, in
-// cycles: a vector operation 4, an LDS read 57, a neighbour row from the L2
+// What bounds it: one wave's chain of dependent steps.  G(500, 0.5), k = 49,
+// eight individuals of one wave per CU: 518 vector, 288 scalar and 57 memory
+// instructions in 7,500 cycles a move, half of them the wave's own issue, the
+// rest latency (36 %) and the other wave of the SIMD.  G(1000, 0.5), k = 85, two
+// of four waves: 12,200 cycles, the waves waiting 58 % of them for one another
+// or for memory.  Measured here, in cycles: a vector operation 4, an LDS read 57, a neighbour row from the L2
 // about 200, a vector result brought to the scalar unit 31, a branch on it
 // 52, a lane-masked block 44.  So Philox (about 190) is cheaper than avoiding
 // it, and the code selects addresses and values instead of branching.
