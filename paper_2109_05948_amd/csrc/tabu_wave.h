@@ -380,15 +380,14 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
     sg[b] = 0u;
     room[b] = ~0ull;
   }
-  // Groups of the LDS part walked together: a long list (f stays high with far
-  // too few colours) is walked in every iteration, one round trip to the LDS
-  // and the L2 after the other, and the tie pass walks it only if a pair of it
-  // is at the best delta.  An uneven batch of 12 graphs of 100 to 1,000 vertices:
-  // 101.7 ms one group at a time, 95.5 two at a time, 79.5 with the tie pass
-  // skipped as well (four at a time: 79.4, but 3 % more where lists are short).
-  // With one or two waves per individual the registers it takes cost short
-  // lists 2 to 5 %, and long ones are rarer there; their plain loops stand
-  // apart because going through the same lambda cost one wave 2 to 3 %.
+  // Groups of the LDS part that the scan looks at together: a long list (f stays
+  // high with far too few colours) is walked in every iteration, one round trip
+  // to the LDS after the other, and the tie pass walks it only if a pair of it is
+  // at the best delta.  An uneven batch of 12 graphs of 100 to 1,000 vertices:
+  // 101.7 ms one group at a time, 95.5 two at a time, 80.4 with the tie pass
+  // skipped as well.  (Four at a time, and the walk after the move by groups, gave
+  // no more and cost short lists 2 to 3 %.)  With one or two waves per individual
+  // the registers it takes cost short lists 2 to 5 %, and long ones are rarer there.
   constexpr int GROUPS = NW == 4 ? 2 : 1;
   auto refill = [&]() {  // from the end of act
 #pragma unroll
@@ -592,9 +591,8 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
         }
       }
       if (tail_wave) {
-        // both banks asked at once first: 1 to 2 % of a lone individual's time (four
-        // waves in an uneven batch lost 3 % by it)
-        if (NW == 4 || __ballot(min(side[0], side[NB - 1]) == cur)) {
+        // both banks asked at once first: 1 to 2 % of a lone individual's time
+        if (__ballot(min(side[0], side[NB - 1]) == cur)) {
 #pragma unroll
           for (int b = 0; b < NB; ++b)
             if (const uint64_t m = __ballot(side[b] == cur)) {
@@ -602,15 +600,15 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
               seen += __popcll(m);
             }
         }
-        if (NW < 4 || __ballot(listed == cur))  // (a test of A before it cost 3 %)
-          for (int i0 = 0; i0 < A; i0 += kWave) {
-            uint32_t v, c, x;
-            const uint32_t d = act_delta(i0, v, c, x);
-            if (const uint64_t m = __ballot(d == cur)) {
-              hash_move(d == cur, v, c, x);
-              seen += __popcll(m);
-            }
+        for (int i0 = 0; i0 < A; i0 += kWave) {
+          if (NW == 4 && i0 == 0 && !__ballot(listed == cur)) break;
+          uint32_t v, c, x;
+          const uint32_t d = act_delta(i0, v, c, x);
+          if (const uint64_t m = __ballot(d == cur)) {
+            hash_move(d == cur, v, c, x);
+            seen += __popcll(m);
           }
+        }
       }
       h = wave_min_u32((uint32_t)(hk >> 32));
       uint64_t at = __ballot((uint32_t)(hk >> 32) == h);
@@ -791,54 +789,22 @@ __device__ __forceinline__ void tabu_w8_individual(const TabuArgs& a, int li, in
         }
       if (A > 0) {
         int base = 0;
-        if constexpr (GROUPS == 1) {
-          for (int i0 = 0; i0 < A; i0 += kWave) {
-            const bool alive = i0 + lane < A;
-            const int i = alive ? i0 + lane : acap;
-            const uint32_t e = act[i], eg = actg[i], v = alive ? e >> 17 : (uint32_t)n;
-            const uint32_t c = alive ? (e >> 9) & 0xffu : kNoColour;
-            uint32_t ga = eg & 0xffu;
-            const uint32_t ad = dstar != kW8None ? adj_word(v) >> (v & 31u) : 0u;
-            bool gone;
-            walk(v, c, (e & 0x1ffu) | ((eg >> 8) << 9), ga, (ad & 1u) != 0u, gone);
-            const bool keep = alive && !gone;
-            const uint64_t mk = __ballot(keep);
-            const int p = keep ? base + (int)lane_rank(mk) : acap;
-            act[p] = e;
-            actg[p] = (uint16_t)((eg & 0xff00u) | ga);
-            base += __popcll(mk);
-          }
-        } else {
-          // in place: entries are read before those positions are written (base <= i0)
-          for_groups<GROUPS>(A, [&](auto groups, int i0) {
-            constexpr int U = decltype(groups)::value;
-            uint32_t e[U], eg[U], ad[U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-              const int i = i0 + kWave * u + lane < A ? i0 + kWave * u + lane : acap;
-              e[u] = act[i];
-              eg[u] = actg[i];
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-              const uint32_t v = i0 + kWave * u + lane < A ? e[u] >> 17 : (uint32_t)n;
-              ad[u] = dstar != kW8None ? adj_word(v) >> (v & 31u) : 0u;
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-              const bool alive = i0 + kWave * u + lane < A;
-              const uint32_t v = alive ? e[u] >> 17 : (uint32_t)n, c = alive ? (e[u] >> 9) & 0xffu : kNoColour;
-              uint32_t ga = eg[u] & 0xffu;
-              bool gone;
-              walk(v, c, (e[u] & 0x1ffu) | ((eg[u] >> 8) << 9), ga, (ad[u] & 1u) != 0u, gone);
-              const bool keep = alive && !gone;
-              const uint64_t mk = __ballot(keep);
-              const int p = keep ? base + (int)lane_rank(mk) : acap;
-              act[p] = e[u];
-              actg[p] = (uint16_t)((eg[u] & 0xff00u) | ga);
-              base += __popcll(mk);
-            }
-          });
+        // in place: entries are read before those positions are written (base <= i0)
+        for (int i0 = 0; i0 < A; i0 += kWave) {
+          const bool alive = i0 + lane < A;
+          const int i = alive ? i0 + lane : acap;
+          const uint32_t e = act[i], eg = actg[i], v = alive ? e >> 17 : (uint32_t)n;
+          const uint32_t c = alive ? (e >> 9) & 0xffu : kNoColour;
+          uint32_t ga = eg & 0xffu;
+          const uint32_t ad = dstar != kW8None ? adj_word(v) >> (v & 31u) : 0u;
+          bool gone;
+          walk(v, c, (e & 0x1ffu) | ((eg >> 8) << 9), ga, (ad & 1u) != 0u, gone);
+          const bool keep = alive && !gone;
+          const uint64_t mk = __ballot(keep);
+          const int p = keep ? base + (int)lane_rank(mk) : acap;
+          act[p] = e;
+          actg[p] = (uint16_t)((eg & 0xff00u) | ga);
+          base += __popcll(mk);
         }
         A = base;
       }
