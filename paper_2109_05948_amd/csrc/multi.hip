@@ -225,10 +225,10 @@ dlm_tabu_params item_params(const dlm_multi_item& it) {
 // Whether a graph of the batch runs the wave table, and how.  Classes of more
 // than half the limit in the mean are left to the block search: a rerun here
 // begins when everything else has ended.  pop: the individuals that the
-// number of waves is picked for.
-bool wave_item(const dlm_multi_item& it, int64_t pop, int64_t budget, WaveItem& w) {
+// number of waves is picked for; crowd: those that share the card.
+bool wave_item(const dlm_multi_item& it, int64_t pop, int64_t crowd, int64_t budget, WaveItem& w) {
   const dlm_tabu_params q = item_params(it);
-  if (!it.g->ell || !w8_auto(it.g, &q) || it.g->n > (int)(kW8ClassMax / 2) * it.k || block_faster(it.g, &q, pop))
+  if (!it.g->ell || !w8_auto(it.g, &q) || it.g->n > (int)(kW8ClassMax / 2) * it.k || block_faster(it.g, &q, crowd))
     return false;
   w.pick = w8_pick(it.g, &q, pop);
   w.instance = w8_multi_instance(it.k, w.pick.bits);
@@ -296,10 +296,13 @@ std::vector<WaveLaunch> wave_launches(const dlm_multi_item* items, const std::ve
   return r;
 }
 
-// Launches side by side.  A process has four hardware queues; with four branches
-// two of them came to lie on one queue, one after the other (a batch of 9 graphs
-// of 75 to 534 vertices: 47 ms instead of 27).
-constexpr size_t kBranches = 3;
+// Branches of the plan's graph: up to three launches of the wave table, one per
+// number of waves, and the block search.
+constexpr size_t kStreams = 4;
+// Launches are parted up to so many branches.  A process has four hardware
+// queues; with a fourth wave launch two of them came to lie on one queue, one
+// after the other (a batch of 9 graphs of 75 to 534 vertices: 47 ms instead of 27).
+constexpr size_t kParted = 3;
 
 // The launches of the wave table's graphs.  A batch that the card holds whole
 // is as long as its longest individual: each graph gets the waves it would get
@@ -314,12 +317,18 @@ std::vector<WaveLaunch> wave_plan(const dlm_multi_item* items, const std::vector
       WaveItem w{};
       w.oi = oi;
       if (items[oi].pop == 0) continue;
-      if (wave_item(items[oi], alone ? items[oi].pop : total, budget, w))
+      // a graph that the budget holds only with fewer waves than it would get
+      // alone is the batch's longest chain on the wave table: left to the block
+      // search (one of 832 vertices in the 64-graph batch: 1,400 instead of 1,030 ms)
+      const int64_t crowd = alone ? items[oi].pop : total;
+      bool fits = wave_item(items[oi], items[oi].pop, crowd, budget, w);
+      if (fits && !alone) fits = wave_item(items[oi], total, crowd, budget, w);
+      if (fits)
         graphs.push_back(w);
       else
         block = true;
     }
-    return wave_launches(items, graphs, kBranches - (block ? 1 : 0));
+    return wave_launches(items, graphs, kParted - (block ? 1 : 0));
   };
   std::vector<WaveLaunch> r = launches(true);
   int64_t waves = 0;
@@ -328,26 +337,27 @@ std::vector<WaveLaunch> wave_plan(const dlm_multi_item* items, const std::vector
   return r;
 }
 
-// The plan's nodes onto cs[kBranches - 1] (capturing), the launches of the
-// wave table on branches of their own; the last is the block search's.
+// The plan's nodes onto cs[kStreams - 1] (capturing), the launches of the wave
+// table on branches of their own; the last is the block search's.
 int capture_plan(const dlm_multi_plan* p, const hipStream_t* cs, const hipEvent_t* ev) {
-  hipStream_t s = cs[kBranches - 1];
+  static_assert(kParted < kStreams, "every wave launch has a stream of its own");
+  hipStream_t s = cs[kStreams - 1];
   hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, s, p->d_queue, 1, 0u);
   DLM_HIP(hipGetLastError());
-  DLM_HIP(hipEventRecord(ev[kBranches - 1], s));
+  DLM_HIP(hipEventRecord(ev[kStreams - 1], s));
   for (size_t i = 0; i < p->launches.size(); ++i) {
     const dlm_multi_plan::Launch& l = p->launches[i];
-    if (i < kBranches - 1) DLM_HIP(hipStreamWaitEvent(cs[i], ev[kBranches - 1], 0));
+    DLM_HIP(hipStreamWaitEvent(cs[i], ev[kStreams - 1], 0));
     const auto launch = l.waves == 4 ? launch_multi_w8_4 : l.waves == 2 ? launch_multi_w8_2 : launch_multi_w8_1;
     const int rc = launch(p->d_wdescs + l.desc, l.ndesc, l.item, l.items, l.lds, cs[i]);
     if (rc != DLM_OK) return rc;
-    if (i < kBranches - 1) DLM_HIP(hipEventRecord(ev[i], cs[i]));
+    DLM_HIP(hipEventRecord(ev[i], cs[i]));
   }
   if (p->block_items > 0) {
     const int rc = launch_persistent(p, s);
     if (rc != DLM_OK) return rc;
   }
-  for (size_t i = 0; i < p->launches.size() && i < kBranches - 1; ++i) DLM_HIP(hipStreamWaitEvent(s, ev[i], 0));
+  for (size_t i = 0; i < p->launches.size(); ++i) DLM_HIP(hipStreamWaitEvent(s, ev[i], 0));
   if (p->again_items > 0) {
     const int rc = launch_multi_w8_again(p->d_wdescs + p->wave_descs, p->again_descs, p->again_items, p->again_lds, s);
     if (rc != DLM_OK) return rc;
@@ -541,26 +551,26 @@ int dlm_multi_plan_create(const dlm_multi_item* items, int32_t count, const dlm_
   }
   // capture: queue reset (a fill kernel, no memset node), the wave launches and
   // the persistent kernel side by side, the reruns
-  hipStream_t cs[kBranches] = {};
-  hipEvent_t ev[kBranches] = {};
+  hipStream_t cs[kStreams] = {};
+  hipEvent_t ev[kStreams] = {};
   auto release = [&]() {
-    for (size_t i = 0; i < kBranches; ++i) {
+    for (size_t i = 0; i < kStreams; ++i) {
       if (ev[i]) (void)hipEventDestroy(ev[i]);
       if (cs[i]) (void)hipStreamDestroy(cs[i]);
     }
   };
-  for (size_t i = 0; i < kBranches; ++i)
+  for (size_t i = 0; i < kStreams; ++i)
     if ((e = hipStreamCreateWithFlags(&cs[i], hipStreamNonBlocking)) != hipSuccess ||
         (e = hipEventCreateWithFlags(&ev[i], hipEventDisableTiming)) != hipSuccess) {
       release();
       return fail(e, "hipStreamCreate");
     }
-  if ((e = hipStreamBeginCapture(cs[kBranches - 1], hipStreamCaptureModeThreadLocal)) != hipSuccess) {
+  if ((e = hipStreamBeginCapture(cs[kStreams - 1], hipStreamCaptureModeThreadLocal)) != hipSuccess) {
     release();
     return fail(e, "hipStreamBeginCapture");
   }
   rc = capture_plan(p, cs, ev);
-  e = hipStreamEndCapture(cs[kBranches - 1], &p->graph);
+  e = hipStreamEndCapture(cs[kStreams - 1], &p->graph);
   release();
   if (rc != DLM_OK) {
     free_plan(p);
