@@ -45,17 +45,17 @@ METRIC = "tabu moves/sec (population, 1 GPU) + time-to-legal-k-coloring, learned
 # --pmc runs (FETCH_SIZE, WRITE_SIZE), each scaled by what the counter reads
 # for a 1 GiB device-to-device copy.  Valid only for the kernel sources they
 # were taken on (digest below) and the same table and block; otherwise null.
-MEASURED_TRAFFIC = {"sources_sha256": "90f622ede0f2d30055248402ea1008c515523046e0683b22b3d379670c082e06",
-                    "table": "wave8", "block": 0, "bytes": 27144576}  # profiles/tabucol_wave8_gnp500.md
+MEASURED_TRAFFIC = {"sources_sha256": "9791f5ec74994e5d8e72ff41da4375d3c22b81bd8a6212c5924ad4f1beb9f9c9",
+                    "table": "wave8", "block": 0, "bytes": 37910336}  # profiles/tabucol_wave8_gnp500.md
 KERNEL_SOURCES = ("paper_2109_05948_amd/csrc/tabu_body.h", "paper_2109_05948_amd/csrc/tabucol.hip",
                   "paper_2109_05948_amd/csrc/dlm_common.h", "paper_2109_05948_amd/csrc/tabu_wave.h",
                   "paper_2109_05948_amd/csrc/tabu_wave_kernel.h", "paper_2109_05948_amd/csrc/tabu_wave_launch.h",
                   "paper_2109_05948_amd/csrc/wave_util.h")
 
 
-# HBM bytes of the two distance launches of one diversity step (old x new
-# block + new x new triangle), from the same counter runs
-DIVERSITY_TRAFFIC = {"sources_sha256": "9f79de36c3bbbdb83d6884a3ccb01ff45ffbb8d43bbc23bc6ed9041fc722adea", "bytes": 1629448352}  # profiles/distance_diversity_gnp500.md
+# HBM bytes of the distance launches of one diversity step (old x new block +
+# new x new triangle, two passes each), from the same counter runs
+DIVERSITY_TRAFFIC = {"sources_sha256": "0e534e84f3aff85ac581a8ecffcffcbb94848b7a7d3e4f32ce76a67115b68d70", "bytes": 6292509792}  # profiles/distance_diversity_gnp500.md
 DIVERSITY_SOURCES = ("paper_2109_05948_amd/csrc/diversity.hip", "paper_2109_05948_amd/csrc/wave_util.h",
                      "paper_2109_05948_amd/csrc/dlm_common.h")
 
@@ -84,8 +84,8 @@ def log(*a):
 # bytes of one table entry by tier: (gamma in LDS, tabu in LDS, gamma in device memory, tabu in device memory)
 TIER_BYTES = {"lds16": (2, 2, 0, 0), "lds32": (4, 4, 0, 0), "split16": (2, 0, 0, 2),
               "split8": (1, 0, 0, 2), "global16": (0, 0, 2, 2),
-              # byte gamma whose top bit flags tabu pairs: no separate tabu entry
-              "wave8": (1, 0, 0, 0)}
+              # 4-bit gamma (at this workload) whose escape value marks tabu pairs: no separate tabu entry
+              "wave8": (0.5, 0, 0, 0)}
 # the search kernel of each table tier (the dominant kernel of a launch)
 TIER_KERNEL = {"wave8": "tabucol_w8_kernel"}
 
@@ -690,7 +690,7 @@ def bench_diversity(args, w, dlm, torch):
            "distance_ms": dist_ms, "spacing_update_ms": upd_ms, "gather_nearest_ms": rest_ms,
            "n_spaced": int(nsp.item()),
            "roofline": {"bound": "alu", "achieved": tops, "peak": ALU_PEAK_TOPS, "unit": "Tops/s",
-                        "frac": tops / ALU_PEAK_TOPS, "kernel": "distance_kernel",
+                        "frac": tops / ALU_PEAK_TOPS, "kernel": "distance_lanes_kernel",
                         "traffic": (DIVERSITY_TRAFFIC["bytes"] if p == 8192 and
                                     kernel_sources_digest(DIVERSITY_SOURCES) == DIVERSITY_TRAFFIC["sources_sha256"]
                                     else None),
