@@ -45,7 +45,7 @@ METRIC = "tabu moves/sec (population, 1 GPU) + time-to-legal-k-coloring, learned
 # --pmc runs (FETCH_SIZE, WRITE_SIZE), each scaled by what the counter reads
 # for a 1 GiB device-to-device copy.  Valid only for the kernel sources they
 # were taken on (digest below) and the same table and block; otherwise null.
-MEASURED_TRAFFIC = {"sources_sha256": "9791f5ec74994e5d8e72ff41da4375d3c22b81bd8a6212c5924ad4f1beb9f9c9",
+MEASURED_TRAFFIC = {"sources_sha256": "4c6665bbba24e59b8352d79be4b9cde0ac02a0c9371063a71bf4c269c932670f",
                     "table": "wave8", "block": 0, "bytes": 37910336}  # profiles/tabucol_wave8_gnp500.md
 KERNEL_SOURCES = ("paper_2109_05948_amd/csrc/tabu_body.h", "paper_2109_05948_amd/csrc/tabucol.hip",
                   "paper_2109_05948_amd/csrc/dlm_common.h", "paper_2109_05948_amd/csrc/tabu_wave.h",

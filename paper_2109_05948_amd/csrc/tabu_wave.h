@@ -52,7 +52,7 @@
 // eight individuals of one wave per CU: 518 vector, 288 scalar and 57 memory
 // instructions in 7,500 cycles a move, half of them the wave's own issue, the
 // rest latency (36 %) and the other wave of the SIMD.  G(1000, 0.5), k = 85, two
-// of four waves: 12,200 cycles, the waves waiting 58 % of them for one another
+// of four waves: 12,000 cycles, the waves waiting 57 % of them for one another
 // or for memory.  Measured here, in cycles: a vector operation 4, an LDS read 57, a neighbour row from the L2
 // about 200, a vector result brought to the scalar unit 31, a branch on it
 // 52, a lane-masked block 44.  So Philox (about 190) is cheaper than avoiding
